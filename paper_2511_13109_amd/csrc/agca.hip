@@ -273,6 +273,17 @@ bool fusable(const agca_hier* h, int l) {
     return op.sten == nullptr && op.blk == nullptr;
 }
 
+// Whether two consecutive products on level l run as one pass (k_smooth2.hip): the levels of
+// `fusable`, except small FP64 vector ones.  There every form is bound by the latency of its
+// z steps, and a step with two products at 2 wavefronts per SIMD is the longer one (V-cycle
+// with a finest level of 16 / 32 / 64 cells per axis: 76.2 / 102.6 / 165.9 us against 70.8 /
+// 97.3 / 167.7 as single passes; scalar and FP32: 34.5 against 35.5 and 56.2 against 57.4 us
+// at 16 cells, and the gain grows with the size).
+template <typename T>
+bool two_products(const agca_hier* h, int l) {
+    return fusable<T>(h, l) && !(h->cfg.ncomp == 3 && sizeof(T) == 8 && h->lv[l].n < 64);
+}
+
 // Mode and coefficients of smoothing pass k on level l (k >= 1 before the coarse
 // correction, where pass 0 is formed from zero; k >= 0 after it): damped Jacobi; for
 // Chebyshev, pass 0 is x + D^-1 (b - A x) / theta, pass 1 before the correction starts
@@ -350,7 +361,8 @@ int32_t do_smooth(agca_hier* h, int l, int sweeps, double omega, const T* b, T* 
 // without stored blocks the first two pre-smoothing passes from zero are one kernel
 // (the first, x = omega0 D^-1 b, is formed while loading; Chebyshev only for degree
 // 2, whose second pass needs no stored first iterate); elsewhere the first pass is
-// the elementwise x = omega0 D^-1 b.  Every further pass writes the level's other
+// the elementwise x = omega0 D^-1 b.  Where two_products holds, two passes before the
+// correction and the residual are one launch, and two passes after it another.  Every further pass writes the level's other
 // buffer (a Chebyshev pass reads the previous iterate from it at the same node), so
 // the passes ping-pong, and on the finest level the starting buffer is chosen so
 // that the last pass lands in the caller's x (no copies).
@@ -378,12 +390,29 @@ int32_t do_vcycle(agca_hier* h, const T* bL, T* xL) {
         // out-of-place launches that write this level's iterate after its first producer
         // (pre-sweeps after the first pass, then every post-sweep; the prolongation
         // adds in place)
+        const bool two = two_products<T>(h, l);
         const int first = (pre >= 2 && fuse) ? 2 : (pre > 0 ? 1 : 0);
-        const int launches = (pre - first) + post;
+        const int launches = (pre - first) + (two && post == 2 ? 1 : post);
         T* cur = (launches % 2 == 0) ? home : other;
         T* alt = (cur == home) ? other : home;
         const LevelOp<T> op = level_op<T>(h, l);
         const T om0 = cheb ? T(1.0 / Cheb(h->lam[l]).theta) : om;
+        if (two && pre == 2) {
+            // both passes and the residual in one
+            const Sweep<T> sw = cheb ? cheb_sweep<T>(Cheb(h->lam[l]), 1, nullptr) : jacobi_sweep<T>(om);
+            Smooth2<T> s2;
+            s2.b = bl;
+            s2.out = cur;
+            s2.r = static_cast<T*>(h->lv[l].r);
+            s2.om0 = sw.omega0;
+            s2.a1 = sw.alpha;
+            s2.o1 = sw.omega;
+            HIPCHK(h, launch_smooth2<T>(nc, true, op, s2, h->st));
+            xcur[l] = cur;
+            xalt[l] = alt;
+            HIPCHK(h, launch_restrict<T>(nc, h->lv[l].n, s2.r, static_cast<T*>(h->lv[l - 1].b), h->st));
+            continue;
+        }
         if (first == 2) {
             // passes 0 and 1 from zero: x1 = om0 D^-1 b, then (x_prev = 0)
             const Sweep<T> sw = cheb ? cheb_sweep<T>(Cheb(h->lam[l]), 1, nullptr) : jacobi_sweep<T>(om);
@@ -443,10 +472,26 @@ int32_t do_vcycle(agca_hier* h, const T* bL, T* xL) {
         T* cur = xcur[l];
         T* alt = xalt[l];
         HIPCHK(h, launch_prolong_add<T>(nc, h->lv[l].n, xcur[l - 1], cur, h->st));
-        for (int i = 0; i < post; ++i) {
-            TRY(pass(l, false, i, cur, bl, alt, alt));
+        if (post == 2 && two_products<T>(h, l)) {
+            Sweep<T> s0, s1;
+            (void)smooth_pass_coef<T>(h, l, false, 0, nullptr, &s0);
+            (void)smooth_pass_coef<T>(h, l, false, 1, nullptr, &s1);
+            Smooth2<T> s2;
+            s2.x = cur;
+            s2.b = bl;
+            s2.out = alt;
+            s2.a1 = s0.alpha;
+            s2.o1 = s0.omega;
+            s2.a2 = s1.alpha;
+            s2.g2 = s1.gamma;
+            s2.o2 = s1.omega;
+            HIPCHK(h, launch_smooth2<T>(nc, false, level_op<T>(h, l), s2, h->st));
             std::swap(cur, alt);
-        }
+        } else
+            for (int i = 0; i < post; ++i) {
+                TRY(pass(l, false, i, cur, bl, alt, alt));
+                std::swap(cur, alt);
+            }
         xcur[l] = cur;
     }
     if (xcur[L] != xL)  // only when pre = post = 0 parity cannot place it

@@ -98,6 +98,67 @@ AGCA_HD void cell_dca(const T (&U)[8][NC], const T (&w)[6], T (&F)[8][NC]) {
     tet_dca<5, NC, T>(U, w[5], F);
 }
 
+// Fluxes of simplex S (vector form) on its three path steps: added to f (the cell edge from
+// corner 0) and l (the cell edge into corner 7), which two simplices share (NF / NL: this
+// one is the first of them), and stored to m (its middle edge, its own).  Each off-diagonal
+// product w s[i][j] serves both steps it belongs to.
+template <int S, bool NF, bool NL, typename T>
+AGCA_HD void tet_flux(const T (&U)[8][3], T w, T (&f)[3], T (&m)[3], T (&l)[3]) {
+    constexpr int a1 = axis1(S), a2 = axis2(S), a3 = axis3(S);
+    constexpr int k1 = 1 << a1, k2 = (1 << a1) | (1 << a2);
+    T d1[3], d2[3], d3[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        d1[c] = U[k1][c] - U[0][c];
+        d2[c] = U[k2][c] - U[k1][c];
+        d3[c] = U[7][c] - U[k2][c];
+    }
+    const T w2 = w + w;
+    const T t12 = w * (d2[a1] + d1[a2]), t13 = w * (d3[a1] + d1[a3]), t23 = w * (d3[a2] + d2[a3]);
+    m[a1] = t12;
+    m[a2] = w2 * d2[a2];
+    m[a3] = t23;
+    f[a1] = NF ? w2 * d1[a1] : fma(w2, d1[a1], f[a1]);
+    f[a2] = NF ? t12 : f[a2] + t12;
+    f[a3] = NF ? t13 : f[a3] + t13;
+    l[a1] = NL ? t13 : l[a1] + t13;
+    l[a2] = NL ? t23 : l[a2] + t23;
+    l[a3] = NL ? w2 * d3[a3] : fma(w2, d3[a3], l[a3]);
+}
+
+// The same contributions, F overwritten, with the vector form's fluxes summed on the 12 cell
+// edges first (the edges at corners 0 and 7 belong to two simplices each, consecutive in
+// the order below); every corner then takes its three edges' sums: 156 additions and
+// products against cell_dca's 180.
+template <int NC, typename T>
+AGCA_HD void cell_flux(const T (&U)[8][NC], const T (&w)[6], T (&F)[8][NC]) {
+    if constexpr (NC == 1) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) F[k][0] = T(0);
+        cell_dca<NC, T>(U, w, F);
+    } else {
+        T fx[3], fy[3], fz[3], lx[3], ly[3], lz[3];
+        T mxy[3], mxz[3], myx[3], myz[3], mzx[3], mzy[3];
+        tet_flux<0, true, true>(U, w[0], fx, mxy, lz);
+        tet_flux<1, false, true>(U, w[1], fx, mxz, ly);
+        tet_flux<4, true, false>(U, w[4], fz, mzx, ly);
+        tet_flux<5, false, true>(U, w[5], fz, mzy, lx);
+        tet_flux<3, true, false>(U, w[3], fy, myz, lx);
+        tet_flux<2, false, false>(U, w[2], fy, myx, lz);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            F[0][c] = -fx[c] - fy[c] - fz[c];
+            F[1][c] = fx[c] - mxy[c] - mxz[c];
+            F[2][c] = fy[c] - myx[c] - myz[c];
+            F[4][c] = fz[c] - mzx[c] - mzy[c];
+            F[3][c] = mxy[c] + myx[c] - lz[c];
+            F[5][c] = mxz[c] + mzx[c] - ly[c];
+            F[6][c] = myz[c] + mzy[c] - lx[c];
+            F[7][c] = lx[c] + ly[c] + lz[c];
+        }
+    }
+}
+
 // add a precomputed local product y = B u_e (layout 4c + a) to the simplex's corners
 template <int S, int NC, typename T>
 AGCA_HD void tet_add_product(const T* __restrict__ y, T (&F)[8][NC]) {

@@ -57,6 +57,20 @@ hipError_t launch_cube_dot(int ncomp, const LevelOp<double>& op, const double* u
 // upper bound on the workgroups of the element loop on a level with n cells
 int cube_grid_blocks(int n);
 
+// Two products with the level operator in one pass (k_smooth2.hip; levels without stored
+// blocks).  pre: x1 = om0 D^-1 b, out = a1 x1 + o1 D^-1 (b - A x1), r = b - A out.
+// Otherwise: y = a1 x + o1 D^-1 (b - A x), out = a2 y + g2 x + o2 D^-1 (b - A y).
+template <typename T>
+struct Smooth2 {
+    const T* x = nullptr;
+    const T* b = nullptr;
+    T* out = nullptr;
+    T* r = nullptr;
+    T om0 = T(0), a1 = T(1), o1 = T(0), a2 = T(1), g2 = T(0), o2 = T(0);
+};
+template <typename T>
+hipError_t launch_smooth2(int ncomp, bool pre, const LevelOp<T>& op, const Smooth2<T>& a, hipStream_t st);
+
 // assembled 15-point stencil of a coarse level (FP64): DCA on unflagged simplices,
 // stored blocks (blk in the internal element layout) on flagged ones
 hipError_t launch_stencil_assemble(int ncomp, int n, const double* nu, double scale,
