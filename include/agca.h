@@ -70,12 +70,13 @@ typedef enum { AGCA_F64 = 0, AGCA_F32 = 1, AGCA_BF16 = 2 } agca_dtype;
 enum { AGCA_FLAG_RATIO = 0, AGCA_FLAG_MACRO = 1, AGCA_FLAG_NONE = 2, AGCA_FLAG_ALL = 3 };
 
 /* How a flagged element's Galerkin operator is kept.
- *  BLOCKS : its 4 ncomp x 4 ncomp Galerkin block (eq. (2.7)), computed in FP64 from
- *           the finest coefficient (plus an FP32 copy for the FP32 V-cycle).
- *  MEAN   : one scalar: with P1 functions the block equals the element's DCA matrix
- *           with the arithmetic mean of the finest coefficient over its descendants,
- *           so that mean replaces the element's coarse coefficient and nothing else is
- *           stored (the same operator up to rounding; agca_get_blocks then fails). */
+ *  MEAN   : one scalar: with P1 functions the Galerkin block equals the element's DCA
+ *           matrix with the arithmetic mean of the finest coefficient over its
+ *           descendants, so that mean replaces the element's coarse coefficient
+ *           (agca_get_blocks then fails).
+ *  BLOCKS : the same operators, with storage for the 4 ncomp x 4 ncomp Galerkin blocks
+ *           (eq. (2.7)) as well; agca_get_blocks forms them in FP64 from the finest
+ *           coefficient by the element-wise recursion, once per coefficient. */
 enum { AGCA_STORE_BLOCKS = 0, AGCA_STORE_MEAN = 1 };
 
 /* Smoother of the V-cycle.
@@ -129,9 +130,8 @@ void agca_default_config(agca_config* cfg);
 int32_t agca_validate_config(const agca_config* cfg);
 
 /* Build the hierarchy (Sections 2.1-2.3): copy the coefficients, check them
- * (finite, > 0), flag coarse elements, form the local Galerkin blocks of the
- * flagged elements by the element-wise recursion (2.7) in FP64, and the Jacobi
- * diagonals and the coarsest-level inverse.
+ * (finite, > 0), flag coarse elements, form the flagged elements' Galerkin coefficients
+ * (the descendant means, FP64), and the Jacobi diagonals and the coarsest-level inverse.
  *   nu_fine   : device, 6 n_L^3 doubles, finest-level coefficient by element id.
  *   nu_coarse : host array of L device pointers; nu_coarse[l] holds 6 n_l^3
  *               doubles, the coefficient evaluated on level l for DCA (eq. (2.5)).
@@ -161,7 +161,8 @@ int32_t agca_get_flags(const agca_hier* h, int32_t level, int32_t* ids_host, int
 
 /* FP64 Galerkin blocks of a coarse level, in flagged-id order: flagged x
  * (4 ncomp)^2 doubles, row (c, a) = 4 c + a, column (d, b) = 4 d + b, vertices a,b
- * in path order (lowest corner first).  Host buffer of cap doubles. */
+ * in path order (lowest corner first).  Host buffer of cap doubles.  The first call after a
+ * coefficient rebuild forms the blocks (transient device memory, AGCA_E_OOM). */
 int32_t agca_get_blocks(const agca_hier* h, int32_t level, double* blocks_host, int64_t cap);
 
 /* Jacobi diagonal of a level operator, FP64, as a host level vector (0 on the boundary). */

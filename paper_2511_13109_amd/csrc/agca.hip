@@ -33,20 +33,17 @@ struct Level {
     int n = 0;
     int64_t nodes = 0, elems = 0;
     // per-element coefficient arrays use the internal layout of kuhn.h (elem_slot)
-    double* nu64 = nullptr;      // finest: nu_L; coarse: DCA coefficient of this level
+    // finest: nu_L; coarse: the level operator's coefficient, the caller's DCA value on
+    // unflagged elements and the descendant mean of nu_L on flagged ones
+    double* nu64 = nullptr;
     float* nu32 = nullptr;       // FP32 copy (FP32 V-cycle)
     uint16_t* nubf = nullptr;    // BF16 copy of the finest coefficient (FP32 V-cycle option)
     int32_t* flag = nullptr;     // by element id
-    int32_t* blk = nullptr;      // by element id: stored block index or -1
-    int32_t* blk_soa = nullptr;  // the same in the internal layout (element loop)
+    int32_t* blk = nullptr;      // by element id: flagged element's index or -1
     int32_t* ids = nullptr;
     int64_t nflag = 0;           // flagged elements
-    int64_t nblk = 0;            // stored Galerkin blocks: nflag, or 0 when the flagged
-                                 // elements' DCA coefficient carries the descendant mean
-    double* blocks64 = nullptr;
-    float* blocks32 = nullptr;
-    double* yblk64 = nullptr;    // per-flagged-element block products (scratch)
-    float* yblk32 = nullptr;
+    int64_t nblk = 0;            // stored Galerkin blocks: nflag, or 0 with AGCA_STORE_MEAN
+    double* blocks64 = nullptr;  // formed when they are first read after a rebuild
     double* diag = nullptr;
     double* dinv64 = nullptr;
     float* dinv32 = nullptr;
@@ -83,6 +80,7 @@ struct agca_hier {
     // Stokes (velocity: finest level, pressure: level L-1)
     std::vector<double> lam;     // Chebyshev: eigenvalue estimate of D^-1 A per level
     int64_t nu_version = 0;      // bumped by every coefficient rebuild
+    int64_t blocks_version = -1; // nu_version the stored Galerkin blocks were formed for
     int64_t mass_version = -1;   // nu_version the pressure mass was formed for
     double* st_mass = nullptr;   // lumped 1/nu pressure mass (level L-1, all nodes)
     double* st_pf = nullptr;     // fine-level scalar scratch (interpolated pressure)
@@ -159,15 +157,18 @@ int32_t alloc_t(agca_hier* h, P** p, size_t count, int64_t* lb = nullptr) {
 
 bool mg32(const agca_hier* h) { return h->cfg.mg_dtype == AGCA_F32; }
 
-// Coarse levels with at most this many cells per axis keep their operator as an
-// assembled stencil (latency-bound sizes; 33^3 nodes x 135 FP64 values = 39 MB).
-// AGCA_STENCIL_MAX_N overrides it (0 turns the stencils off).
-int stencil_max_n() {
+// Coarse levels with at most this many cells per axis keep their operator as an assembled
+// stencil (latency-bound sizes).  The line is where the stencil's bytes (135 values per node
+// in vector form) cost more than the element loop's z steps: V-cycle with the line at 32 / 16
+// cells, vector FP64 65^3 164.5 / 158.7 us and 129^3 415.6 / 406.8, vector FP32 115.9 / 121.3
+// and 238.2 / 241.7, scalar FP64 129^3 169.0 / 171.2.  AGCA_STENCIL_MAX_N overrides it (0
+// turns the stencils off).
+int stencil_max_n(const agca_config& cfg) {
     static const int v = [] {
         const char* e = getenv("AGCA_STENCIL_MAX_N");
-        return e ? atoi(e) : 32;
+        return e ? atoi(e) : -1;
     }();
-    return v;
+    return v >= 0 ? v : cfg.ncomp == 3 && cfg.mg_dtype == AGCA_F64 ? 16 : 32;
 }
 size_t mg_size(const agca_hier* h) { return mg32(h) ? sizeof(float) : sizeof(double); }
 
@@ -181,11 +182,6 @@ LevelOp<double> level_op<double>(const agca_hier* h, int l) {
     op.n = L.n;
     op.nu = L.nu64;
     op.nu_kind = AGCA_F64;
-    op.blk = (l < h->cfg.L && L.nblk > 0) ? L.blk_soa : nullptr;
-    op.ids = L.ids;
-    op.nflag = L.nblk;
-    op.blocks = L.blocks64;
-    op.yblk = L.yblk64;
     op.dinv = L.dinv64;
     op.sten = L.sten64;
     return op;
@@ -202,11 +198,6 @@ LevelOp<float> level_op<float>(const agca_hier* h, int l) {
         op.nu = L.nu32;
         op.nu_kind = AGCA_F32;
     }
-    op.blk = (l < h->cfg.L && L.nblk > 0) ? L.blk_soa : nullptr;
-    op.ids = L.ids;
-    op.nflag = L.nblk;
-    op.blocks = L.blocks32;
-    op.yblk = L.yblk32;
     op.dinv = L.dinv32;
     op.sten = L.sten32;
     return op;
@@ -264,13 +255,11 @@ Sweep<T> cheb_sweep(const Cheb& ch, int k, const T* xprev) {
     return s;
 }
 
-// whether the first two pre-sweeps can be one pass on level l: the element loop
-// without stored blocks (whose products are formed from a stored u before the pass);
-// on stencil levels the separate first sweep measures as fast
+// whether the first two pre-sweeps can be one pass on level l: the element loop (on
+// stencil levels the separate first sweep measures as fast)
 template <typename T>
 bool fusable(const agca_hier* h, int l) {
-    const LevelOp<T> op = level_op<T>(h, l);
-    return op.sten == nullptr && op.blk == nullptr;
+    return level_op<T>(h, l).sten == nullptr;
 }
 
 // Whether two consecutive products on level l run as one pass (k_smooth2.hip): the levels of
@@ -358,7 +347,7 @@ int32_t do_smooth(agca_hier* h, int l, int sweeps, double omega, const T* b, T* 
 
 // One V(pre,post)-cycle from a zero initial guess, with damped Jacobi or the Chebyshev
 // smoother (pre / post = number of passes = Chebyshev degree).  On element-loop levels
-// without stored blocks the first two pre-smoothing passes from zero are one kernel
+// the first two pre-smoothing passes from zero are one kernel
 // (the first, x = omega0 D^-1 b, is formed while loading; Chebyshev only for degree
 // 2, whose second pass needs no stored first iterate); elsewhere the first pass is
 // the elementwise x = omega0 D^-1 b.  Where two_products holds, two passes before the
@@ -725,19 +714,10 @@ int32_t estimate_eigenvalues(agca_hier* h) {
 }
 
 int32_t build_coarsest(agca_hier* h) {
-    const int nc = h->cfg.ncomp, M = 4 * nc;
+    const int nc = h->cfg.ncomp;
     Level& L0 = h->lv[0];
     std::vector<double> nu(48);
     HIPCHK(h, hipMemcpyAsync(nu.data(), L0.nu64, 48 * sizeof(double), hipMemcpyDeviceToHost, h->st));
-    std::vector<int32_t> blk(48, -1);
-    std::vector<double> blocks;
-    const bool has_blocks = h->cfg.L > 0 && L0.nblk > 0;
-    if (has_blocks) {
-        HIPCHK(h, hipMemcpyAsync(blk.data(), L0.blk, 48 * sizeof(int32_t), hipMemcpyDeviceToHost, h->st));
-        blocks.resize((size_t)L0.nblk * M * M);
-        HIPCHK(h, hipMemcpyAsync(blocks.data(), L0.blocks64, blocks.size() * sizeof(double),
-                                 hipMemcpyDeviceToHost, h->st));
-    }
     HIPCHK(h, hipStreamSynchronize(h->st));
     const double scale = 1.0 / (6.0 * 2);
     double A[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
@@ -749,15 +729,9 @@ int32_t build_coarsest(agca_hier* h) {
             for (int j = 0; j < 4; ++j)
                 if (path_corner(s, j) == k) a = j;
             if (a < 0) continue;
-            const int e = 6 * cell + s;
             for (int c = 0; c < nc; ++c)
                 for (int d = 0; d < nc; ++d) {
-                    double v;
-                    if (blk[e] >= 0)
-                        v = blocks[(size_t)blk[e] * M * M + (4 * c + a) * M + 4 * d + a];
-                    else
-                        v = nu[elem_slot(s, cell, 8)] * scale * elem_entry(nc, s, c, a, d, a);
-                    A[c][d] += v;
+                    A[c][d] += nu[elem_slot(s, cell, 8)] * scale * elem_entry(nc, s, c, a, d, a);
                 }
         }
     }
@@ -785,6 +759,69 @@ int32_t build_coarsest(agca_hier* h) {
     return AGCA_OK;
 }
 
+// The stored Galerkin blocks, bottom-up by the recursion (2.7) from the finest coefficient:
+// formed when they are first read after a rebuild (the operators use the equal mean
+// coefficients and never read them).
+int32_t form_blocks(agca_hier* h) {
+    const int L = h->cfg.L, nc = h->cfg.ncomp, M = 4 * nc;
+    if (h->blocks_version == h->nu_version || h->cfg.coarse_storage == AGCA_STORE_MEAN) return AGCA_OK;
+    int lowest = -1;  // coarsest... any flagged level <= L-2 ?
+    for (int l = 0; l <= L - 2; ++l)
+        if (h->lv[l].nblk > 0) {
+            lowest = l;
+            break;
+        }
+    const double h_fine = 1.0 / h->lv[L].n;
+    if (lowest < 0) {
+        if (L >= 1 && h->lv[L - 1].nblk > 0)
+            HIPCHK(h, launch_gca_from_fine(nc, h->lv[L - 1].n, h->lv[L - 1].nblk, h->lv[L - 1].ids,
+                                           h->lv[L].nu64, h_fine, h->lv[L - 1].blocks64, h->st));
+    } else {
+        // levels L-2 .. lowest need the Galerkin matrices of every element of the level
+        // below them while any coarser level is flagged; transient ping-pong buffers
+        std::vector<void*> tmp;
+        int32_t rc = AGCA_OK;
+        for (int i = 0; i < 2; ++i) {
+            const int l = L - 2 - i;
+            if (l < lowest + 1) break;  // trans of level l is needed only if some level < l is flagged
+            void* p = nullptr;
+            hipError_t e = hipMalloc(&p, (size_t)h->lv[l].elems * M * M * sizeof(double));
+            if (e != hipSuccess) {
+                (void)hipGetLastError();
+                rc = fail(AGCA_E_OOM, "transient Galerkin buffer allocation failed");
+                break;
+            }
+            tmp.push_back(p);
+            h->trans[i] = static_cast<double*>(p);
+        }
+        if (rc == AGCA_OK) {
+            const int l2 = L - 2;
+            double* out2 = (l2 > lowest) ? h->trans[0] : nullptr;
+            hipError_t e = launch_gca_fused2(nc, h->lv[l2].n, h->lv[L].nu64, h_fine, h->lv[L - 1].blk,
+                                             h->lv[L - 1].blocks64, h->lv[l2].blk, h->lv[l2].blocks64,
+                                             out2, h->st);
+            int cur = 0;
+            for (int l = L - 3; l >= lowest && e == hipSuccess; --l) {
+                double* in = h->trans[cur];
+                // trans[1-cur] held level l+2 (no longer needed) and is large enough
+                double* out = (l > lowest) ? h->trans[1 - cur] : nullptr;
+                e = launch_gca_up(nc, h->lv[l].n, in, h->lv[l].blk, h->lv[l].blocks64, out, h->st);
+                cur = 1 - cur;
+            }
+            if (e == hipSuccess) e = hipStreamSynchronize(h->st);
+            if (e != hipSuccess) {
+                h->error = true;
+                rc = fail(AGCA_E_HIP, std::string("Galerkin kernels: ") + hipGetErrorString(e));
+            }
+        }
+        for (void* p : tmp) (void)hipFree(p);
+        h->trans[0] = h->trans[1] = nullptr;
+        if (rc != AGCA_OK) return rc;
+    }
+    h->blocks_version = h->nu_version;
+    return AGCA_OK;
+}
+
 // log_fine: nu_fine holds log nu (exponentiated while it is copied)
 int32_t build_operators(agca_hier* h, const double* nu_fine, const double* const* nu_coarse,
                         bool log_fine = false) {
@@ -803,10 +840,13 @@ int32_t build_operators(agca_hier* h, const double* nu_fine, const double* const
             return fail(AGCA_E_INVALID, std::to_string(bad) + " coefficient values on level " +
                                             std::to_string(l) + " are not finite and positive");
     }
-    // flags: min/max pyramid from level L-1 down to 0
+    // flags and the flagged elements' coefficients from level L-1 down to 0.  The Galerkin
+    // block of an element (eq. (2.7)) equals, with P1 functions and one coefficient per finest
+    // element, its DCA matrix with the mean finest coefficient over its descendants, so every
+    // coarse operator (eq. (2.9)) is a coefficient per element: the mean where an element is
+    // flagged, the caller's value elsewhere.
     {
         double *mn[2] = {nullptr, nullptr}, *mx[2] = {nullptr, nullptr}, *mean[2] = {nullptr, nullptr};
-        const bool store_mean = h->cfg.coarse_storage == AGCA_STORE_MEAN;
         const int64_t emax = h->lv[L - 1].elems;
         void* scratch = nullptr;
         size_t sbytes = 0;
@@ -834,7 +874,7 @@ int32_t build_operators(agca_hier* h, const double* nu_fine, const double* const
         for (int i = 0; i < 2 && rc == AGCA_OK; ++i) {
             rc = talloc((void**)&mn[i], emax * sizeof(double));
             if (rc == AGCA_OK) rc = talloc((void**)&mx[i], emax * sizeof(double));
-            if (rc == AGCA_OK && store_mean) rc = talloc((void**)&mean[i], emax * sizeof(double));
+            if (rc == AGCA_OK) rc = talloc((void**)&mean[i], emax * sizeof(double));
         }
         if (rc == AGCA_OK) rc = talloc(&scratch, sbytes);
         int64_t* cnt_dev = nullptr;
@@ -845,25 +885,14 @@ int32_t build_operators(agca_hier* h, const double* nu_fine, const double* const
         }
         for (int l = L - 1; l >= 0; --l) {
             const int cur = l & 1, fin = (l + 1) & 1;
-            hipError_t e = (l == L - 1)
-                               ? launch_minmax_from_fine(h->lv[l].n, h->lv[L].nu64, mn[cur], mx[cur], h->st)
-                               : launch_minmax_up(h->lv[l].n, mn[fin], mx[fin], mn[cur], mx[cur], h->st);
+            const double* nuL = h->lv[L].nu64;
+            hipError_t e = launch_coarsen(h->lv[l].n, l, l == L - 1 ? nuL : mn[fin], l == L - 1 ? nuL : mx[fin],
+                                          l == L - 1 ? nuL : mean[fin], h->cfg.flag_mode, h->cfg.flag_ratio,
+                                          macro_bits, mn[cur], mx[cur], mean[cur], h->lv[l].flag, h->lv[l].nu64,
+                                          h->st);
             if (e == hipSuccess)
-                e = (h->cfg.flag_mode == AGCA_FLAG_MACRO)
-                        ? launch_flag_macro(h->lv[l].elems, h->lv[l].n, l, macro_bits, h->lv[l].flag, h->st)
-                        : launch_flag(h->lv[l].elems, mn[cur], mx[cur], h->cfg.flag_ratio, h->cfg.flag_mode,
-                                      h->lv[l].flag, h->st);
-            if (e == hipSuccess && store_mean) {
-                // the flagged elements' Galerkin blocks equal their DCA element matrices with
-                // the mean finest coefficient: keep that mean as their coefficient instead
-                e = (l == L - 1) ? launch_mean_from_fine(h->lv[l].n, h->lv[L].nu64, mean[cur], h->st)
-                                 : launch_mean_up(h->lv[l].n, mean[fin], mean[cur], h->st);
-                if (e == hipSuccess)
-                    e = launch_override_mean(h->lv[l].elems, h->lv[l].flag, mean[cur], h->lv[l].nu64, h->st);
-            }
-            if (e == hipSuccess)
-                e = launch_compact(h->lv[l].elems, h->lv[l].flag, h->lv[l].blk, h->lv[l].blk_soa,
-                                   h->lv[l].ids, cnt_dev + l, scratch, sbytes, h->st);
+                e = launch_compact(h->lv[l].elems, h->lv[l].flag, h->lv[l].blk, h->lv[l].ids,
+                                   cnt_dev + l, scratch, sbytes, h->st);
             if (e != hipSuccess) {
                 release();
                 h->error = true;
@@ -884,82 +913,17 @@ int32_t build_operators(agca_hier* h, const double* nu_fine, const double* const
             h->lv[l].nblk = (h->cfg.coarse_storage == AGCA_STORE_MEAN) ? 0 : counts[l];
         }
     }
-    // block storage
+    // block storage (filled by form_blocks)
     for (int l = 0; l < L; ++l) {
         Level& lv = h->lv[l];
         lv.blocks64 = nullptr;
-        lv.blocks32 = nullptr;
-        if (lv.nblk > 0) {
-            TRY(alloc_t(h, &lv.blocks64, (size_t)lv.nblk * M * M, &lv.bytes));
-            TRY(alloc_t(h, &lv.yblk64, (size_t)lv.nblk * M, &lv.bytes));
-            if (mg32(h)) {
-                TRY(alloc_t(h, &lv.blocks32, (size_t)lv.nblk * M * M, &lv.bytes));
-                TRY(alloc_t(h, &lv.yblk32, (size_t)lv.nblk * M, &lv.bytes));
-            }
-        }
-    }
-    // Galerkin blocks, bottom-up (eq. (2.7))
-    {
-        int lowest = -1;  // coarsest... any flagged level <= L-2 ?
-        for (int l = 0; l <= L - 2; ++l)
-            if (h->lv[l].nblk > 0) {
-                lowest = l;
-                break;
-            }
-        const double h_fine = 1.0 / h->lv[L].n;
-        if (lowest < 0) {
-            if (L >= 1 && h->lv[L - 1].nblk > 0)
-                HIPCHK(h, launch_gca_from_fine(nc, h->lv[L - 1].n, h->lv[L - 1].nblk, h->lv[L - 1].ids,
-                                               h->lv[L].nu64, h_fine, h->lv[L - 1].blocks64, h->st));
-        } else {
-            // levels L-2 .. lowest need the Galerkin matrices of every element of the level
-            // below them while any coarser level is flagged; transient ping-pong buffers
-            std::vector<void*> tmp;
-            int32_t rc = AGCA_OK;
-            for (int i = 0; i < 2; ++i) {
-                const int l = L - 2 - i;
-                if (l < lowest + 1) break;  // trans of level l is needed only if some level < l is flagged
-                void* p = nullptr;
-                hipError_t e = hipMalloc(&p, (size_t)h->lv[l].elems * M * M * sizeof(double));
-                if (e != hipSuccess) {
-                    (void)hipGetLastError();
-                    rc = fail(AGCA_E_OOM, "transient Galerkin buffer allocation failed");
-                    break;
-                }
-                tmp.push_back(p);
-                h->trans[i] = static_cast<double*>(p);
-            }
-            if (rc == AGCA_OK) {
-                const int l2 = L - 2;
-                double* out2 = (l2 > lowest) ? h->trans[0] : nullptr;
-                hipError_t e = launch_gca_fused2(nc, h->lv[l2].n, h->lv[L].nu64, h_fine, h->lv[L - 1].blk,
-                                                 h->lv[L - 1].blocks64, h->lv[l2].blk, h->lv[l2].blocks64,
-                                                 out2, h->st);
-                int cur = 0;
-                for (int l = L - 3; l >= lowest && e == hipSuccess; --l) {
-                    double* in = h->trans[cur];
-                    // trans[1-cur] held level l+2 (no longer needed) and is large enough
-                    double* out = (l > lowest) ? h->trans[1 - cur] : nullptr;
-                    e = launch_gca_up(nc, h->lv[l].n, in, h->lv[l].blk, h->lv[l].blocks64, out, h->st);
-                    cur = 1 - cur;
-                }
-                if (e == hipSuccess) e = hipStreamSynchronize(h->st);
-                if (e != hipSuccess) {
-                    h->error = true;
-                    rc = fail(AGCA_E_HIP, std::string("Galerkin kernels: ") + hipGetErrorString(e));
-                }
-            }
-            for (void* p : tmp) (void)hipFree(p);
-            h->trans[0] = h->trans[1] = nullptr;
-            if (rc != AGCA_OK) return rc;
-        }
+        if (lv.nblk > 0) TRY(alloc_t(h, &lv.blocks64, (size_t)lv.nblk * M * M, &lv.bytes));
     }
     // diagonals, FP32 copies
     for (int l = 0; l <= L; ++l) {
         Level& lv = h->lv[l];
         const double scale = 1.0 / (6.0 * lv.n);
-        HIPCHK(h, launch_diagonal(nc, lv.n, lv.nu64, scale, (l < L && lv.nblk > 0) ? lv.blk : nullptr,
-                                  lv.blocks64, lv.diag, h->st));
+        HIPCHK(h, launch_diagonal(nc, lv.n, lv.nu64, scale, lv.diag, h->st));
         const int64_t cnt = (int64_t)nc * lv.nodes;
         if (mg32(h)) {
             HIPCHK(h, launch_invert_diag<float>(cnt, lv.diag, lv.dinv32, h->st));
@@ -968,15 +932,11 @@ int32_t build_operators(agca_hier* h, const double* nu_fine, const double* const
                 HIPCHK(h, launch_cast(AGCA_F64, AGCA_BF16, lv.nu64, lv.nubf, lv.elems, h->st));
             else
                 HIPCHK(h, launch_cast(AGCA_F64, AGCA_F32, lv.nu64, lv.nu32, lv.elems, h->st));
-            if (lv.blocks32)
-                HIPCHK(h, launch_cast(AGCA_F64, AGCA_F32, lv.blocks64, lv.blocks32,
-                                      (int64_t)lv.nblk * M * M, h->st));
         } else {
             HIPCHK(h, launch_invert_diag<double>(cnt, lv.diag, lv.dinv64, h->st));
         }
         if (lv.sten64) {
-            HIPCHK(h, launch_stencil_assemble(nc, lv.n, lv.nu64, scale, lv.nblk > 0 ? lv.blk_soa : nullptr,
-                                              lv.blocks64, lv.sten64, h->st));
+            HIPCHK(h, launch_stencil_assemble(nc, lv.n, lv.nu64, scale, lv.sten64, h->st));
             if (lv.sten32)
                 HIPCHK(h, launch_cast(AGCA_F64, AGCA_F32, lv.sten64, lv.sten32,
                                       (int64_t)nc * nc * 15 * lv.nodes, h->st));
@@ -1001,26 +961,17 @@ void free_all(agca_hier* h) {
 int32_t free_blocks(agca_hier* h) {
     // blocks are re-sized on every rebuild: drop the old ones from the allocation list
     for (auto& lv : h->lv) {
-        for (void* p : {(void*)lv.blocks64, (void*)lv.blocks32, (void*)lv.yblk64, (void*)lv.yblk32}) {
-            if (!p) continue;
-            for (size_t i = 0; i < h->allocs.size(); ++i)
-                if (h->allocs[i] == p) {
-                    (void)hipFree(p);
-                    h->allocs.erase(h->allocs.begin() + i);
-                    break;
-                }
-        }
+        for (size_t i = 0; lv.blocks64 && i < h->allocs.size(); ++i)
+            if (h->allocs[i] == lv.blocks64) {
+                (void)hipFree(lv.blocks64);
+                h->allocs.erase(h->allocs.begin() + i);
+                break;
+            }
         const int M = 4 * h->cfg.ncomp;
-        const int64_t freed = (lv.blocks64 ? lv.nblk * M * M * (int64_t)sizeof(double) : 0) +
-                              (lv.blocks32 ? lv.nblk * M * M * (int64_t)sizeof(float) : 0) +
-                              (lv.yblk64 ? lv.nblk * M * (int64_t)sizeof(double) : 0) +
-                              (lv.yblk32 ? lv.nblk * M * (int64_t)sizeof(float) : 0);
+        const int64_t freed = lv.blocks64 ? lv.nblk * M * M * (int64_t)sizeof(double) : 0;
         h->bytes -= freed;
         lv.bytes -= freed;
         lv.blocks64 = nullptr;
-        lv.blocks32 = nullptr;
-        lv.yblk64 = nullptr;
-        lv.yblk32 = nullptr;
         lv.nflag = 0;
         lv.nblk = 0;
     }
@@ -1174,12 +1125,11 @@ int32_t agca_create(const agca_config* cfg, const double* nu_fine, const double*
             rc = alloc_t(h, &lv.nubf, lv.elems, &lv.bytes);
         if (rc == AGCA_OK && l < L) rc = alloc_t(h, &lv.flag, lv.elems, &lv.bytes);
         if (rc == AGCA_OK && l < L) rc = alloc_t(h, &lv.blk, lv.elems, &lv.bytes);
-        if (rc == AGCA_OK && l < L) rc = alloc_t(h, &lv.blk_soa, lv.elems, &lv.bytes);
         if (rc == AGCA_OK && l < L) rc = alloc_t(h, &lv.ids, lv.elems, &lv.bytes);
         if (rc == AGCA_OK) rc = alloc_t(h, &lv.diag, nv, &lv.bytes);
         if (rc == AGCA_OK && mg32(h)) rc = alloc_t(h, &lv.dinv32, nv, &lv.bytes);
         if (rc == AGCA_OK && !mg32(h)) rc = alloc_t(h, &lv.dinv64, nv, &lv.bytes);
-        if (rc == AGCA_OK && l >= 1 && l < L && lv.n <= stencil_max_n()) {
+        if (rc == AGCA_OK && l >= 1 && l < L && lv.n <= stencil_max_n(*cfg)) {
             rc = alloc_t(h, &lv.sten64, (size_t)nv * nc * 15, &lv.bytes);
             if (rc == AGCA_OK && mg32(h)) rc = alloc_t(h, &lv.sten32, (size_t)nv * nc * 15, &lv.bytes);
         }
@@ -1239,7 +1189,7 @@ int32_t agca_query(const agca_hier* h, int32_t level, agca_level_info* out) {
     out->free_nodes = (int64_t)(lv.n - 1) * (lv.n - 1) * (lv.n - 1);
     out->elements = lv.elems;
     out->flagged = level < h->cfg.L ? lv.nflag : 0;
-    out->block_bytes = (lv.blocks64 ? lv.nblk * M * M * 8 : 0) + (lv.blocks32 ? lv.nblk * M * M * 4 : 0);
+    out->block_bytes = lv.blocks64 ? lv.nblk * M * M * 8 : 0;
     out->level_bytes = lv.bytes;
     out->lambda_max = (size_t)level < h->lam.size() ? h->lam[level] : 0.0;
     return AGCA_OK;
@@ -1269,6 +1219,7 @@ int32_t agca_get_blocks(const agca_hier* h, int32_t level, double* blocks_host, 
     if (cap < lv.nblk * M * M) return fail(AGCA_E_INVALID, "blocks buffer too small");
     agca_hier* hh = const_cast<agca_hier*>(h);
     if (lv.nblk > 0) {
+        TRY(form_blocks(hh));
         HIPCHK(hh, hipMemcpyAsync(blocks_host, lv.blocks64, lv.nblk * M * M * sizeof(double),
                                   hipMemcpyDeviceToHost, h->st));
         HIPCHK(hh, hipStreamSynchronize(h->st));

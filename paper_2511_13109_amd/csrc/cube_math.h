@@ -69,24 +69,6 @@ AGCA_HD void tet_dca(const T (&U)[8][NC], T w, T (&F)[8][NC]) {
     }
 }
 
-// stored local matrix B (row (c,a) = 4c+a, column (d,b) = 4d+b, path-ordered vertices)
-template <int S, int NC, typename T, typename BT>
-AGCA_HD void tet_block(const T (&U)[8][NC], const BT* __restrict__ B, T (&F)[8][NC]) {
-    constexpr int M = 4 * NC;
-    T x[M];
-#pragma unroll
-    for (int d = 0; d < NC; ++d)
-#pragma unroll
-        for (int bb = 0; bb < 4; ++bb) x[4 * d + bb] = U[path_corner(S, bb)][d];
-#pragma unroll
-    for (int r = 0; r < M; ++r) {
-        T y = T(0);
-#pragma unroll
-        for (int c = 0; c < M; ++c) y += T(B[r * M + c]) * x[c];
-        F[path_corner(S, r & 3)][r >> 2] += y;
-    }
-}
-
 // all six simplices of a cell with coefficients w[s] (already multiplied by h/6)
 template <int NC, typename T>
 AGCA_HD void cell_dca(const T (&U)[8][NC], const T (&w)[6], T (&F)[8][NC]) {
@@ -157,37 +139,6 @@ AGCA_HD void cell_flux(const T (&U)[8][NC], const T (&w)[6], T (&F)[8][NC]) {
             F[7][c] = lx[c] + ly[c] + lz[c];
         }
     }
-}
-
-// add a precomputed local product y = B u_e (layout 4c + a) to the simplex's corners
-template <int S, int NC, typename T>
-AGCA_HD void tet_add_product(const T* __restrict__ y, T (&F)[8][NC]) {
-#pragma unroll
-    for (int c = 0; c < NC; ++c)
-#pragma unroll
-        for (int a = 0; a < 4; ++a) F[path_corner(S, a)][c] += y[4 * c + a];
-}
-
-template <int S, int NC, typename T>
-AGCA_HD void tet_mixed(const T (&U)[8][NC], T w, int32_t bi, const T* __restrict__ yblk,
-                       T (&F)[8][NC]) {
-    if (bi >= 0)
-        tet_add_product<S, NC, T>(yblk + (int64_t)bi * (4 * NC), F);
-    else
-        tet_dca<S, NC, T>(U, w, F);
-}
-
-// cell with per-simplex choice: the stored block's product (computed beforehand for every
-// flagged simplex) where bi[s] >= 0, DCA otherwise
-template <int NC, typename T>
-AGCA_HD void cell_mixed(const T (&U)[8][NC], const T (&w)[6], const int32_t (&bi)[6],
-                        const T* __restrict__ yblk, T (&F)[8][NC]) {
-    tet_mixed<0, NC, T>(U, w[0], bi[0], yblk, F);
-    tet_mixed<1, NC, T>(U, w[1], bi[1], yblk, F);
-    tet_mixed<2, NC, T>(U, w[2], bi[2], yblk, F);
-    tet_mixed<3, NC, T>(U, w[3], bi[3], yblk, F);
-    tet_mixed<4, NC, T>(U, w[4], bi[4], yblk, F);
-    tet_mixed<5, NC, T>(U, w[5], bi[5], yblk, F);
 }
 
 }  // namespace agca

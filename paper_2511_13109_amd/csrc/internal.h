@@ -17,11 +17,6 @@ struct LevelOp {
     int n = 0;                 // cells per axis
     const void* nu = nullptr;  // 6 n^3 coefficients, internal layout (T, or uint16 bf16 bits)
     int nu_kind = 0;           // AGCA_F64 / AGCA_F32 / AGCA_BF16 storage of nu
-    const int32_t* blk = nullptr;  // per element (internal layout): stored block index or -1
-    const int32_t* ids = nullptr;  // sorted ids of the flagged elements
-    int64_t nflag = 0;
-    const T* blocks = nullptr;     // flagged x (4 ncomp)^2 entries
-    T* yblk = nullptr;             // scratch: flagged x 4 ncomp products B u_e
     const T* dinv = nullptr;       // inverse Jacobi diagonal, level vector (0 on the boundary)
     const T* sten = nullptr;       // assembled stencil (k_stencil.hip layout) or null
 };
@@ -57,8 +52,7 @@ hipError_t launch_cube_dot(int ncomp, const LevelOp<double>& op, const double* u
 // upper bound on the workgroups of the element loop on a level with n cells
 int cube_grid_blocks(int n);
 
-// Two products with the level operator in one pass (k_smooth2.hip; levels without stored
-// blocks).  pre: x1 = om0 D^-1 b, out = a1 x1 + o1 D^-1 (b - A x1), r = b - A out.
+// Two products with the level operator in one pass (k_smooth2.hip).  pre: x1 = om0 D^-1 b, out = a1 x1 + o1 D^-1 (b - A x1), r = b - A out.
 // Otherwise: y = a1 x + o1 D^-1 (b - A x), out = a2 y + g2 x + o2 D^-1 (b - A y).
 template <typename T>
 struct Smooth2 {
@@ -71,11 +65,8 @@ struct Smooth2 {
 template <typename T>
 hipError_t launch_smooth2(int ncomp, bool pre, const LevelOp<T>& op, const Smooth2<T>& a, hipStream_t st);
 
-// assembled 15-point stencil of a coarse level (FP64): DCA on unflagged simplices,
-// stored blocks (blk in the internal element layout) on flagged ones
-hipError_t launch_stencil_assemble(int ncomp, int n, const double* nu, double scale,
-                                   const int32_t* blk, const double* blocks, double* S,
-                                   hipStream_t st);
+// assembled 15-point stencil of a coarse level (FP64)
+hipError_t launch_stencil_assemble(int ncomp, int n, const double* nu, double scale, double* S, hipStream_t st);
 // apply / residual / Jacobi-type passes (MODE_APPLY, MODE_RESIDUAL, MODE_JACOBI, MODE_CHEB)
 // with an assembled stencil
 template <typename T>
@@ -169,27 +160,18 @@ hipError_t launch_to_internal(int64_t cells, const double* by_id, double* intern
                               hipStream_t st);
 
 // setup kernels (Sections 2.2-2.3)
-hipError_t launch_minmax_from_fine(int n_coarse, const double* nu_fine, double* mn, double* mx,
-                                   hipStream_t st);
-hipError_t launch_minmax_up(int n_coarse, const double* mn_f, const double* mx_f, double* mn,
-                            double* mx, hipStream_t st);
-hipError_t launch_flag(int64_t ne, const double* mn, const double* mx, double tau, int mode,
-                       int32_t* flag, hipStream_t st);
-// descendant means of the finest coefficient (canonical ids), and their use as the DCA
-// coefficient of the flagged elements (nu in the internal layout)
-hipError_t launch_mean_from_fine(int n_coarse, const double* nu_fine, double* mean, hipStream_t st);
-hipError_t launch_mean_up(int n_coarse, const double* mean_f, double* mean, hipStream_t st);
-hipError_t launch_override_mean(int64_t ne, const int32_t* flag, const double* mean, double* nu,
-                                hipStream_t st);
-// flag = 1 for the level-l elements (n = 2^(l+1) cells per axis) inside the macro
-// elements whose bit is set in `bits` (bit k = level-0 element id k)
-hipError_t launch_flag_macro(int64_t ne, int n, int l, uint64_t bits, int32_t* flag, hipStream_t st);
+// One coarse level (n cells per axis, level l) from the level below it (its 8 children per
+// element, by element id; the finest level passes its coefficient three times): minimum,
+// maximum and mean of the finest coefficient over the descendants, the flag (AGCA_FLAG_*;
+// `bits`: bit k = macro element k is flagged), and nu <- mean where flagged (internal layout)
+hipError_t launch_coarsen(int n, int l, const double* mn_f, const double* mx_f, const double* mean_f, int mode,
+                          double tau, uint64_t bits, double* mn, double* mx, double* mean, int32_t* flag,
+                          double* nu, hipStream_t st);
 // per macro element the largest |grad eta_h| over the finest elements of level L, as the
 // bit patterns of non-negative doubles, max-combined into gbits[48] (zeroed by the caller)
 hipError_t launch_macro_grad_max(int L, const double* eta, unsigned long long* gbits, hipStream_t st);
 // exclusive scan of flags -> blk index (or -1) and total count (device int64)
-hipError_t launch_compact(int64_t ne, const int32_t* flag, int32_t* blk, int32_t* blk_soa,
-                          int32_t* ids, int64_t* count_dev, void* scratch, size_t scratch_bytes,
+hipError_t launch_compact(int64_t ne, const int32_t* flag, int32_t* blk, int32_t* ids, int64_t* count_dev, void* scratch, size_t scratch_bytes,
                           hipStream_t st);
 hipError_t compact_scratch_bytes(int64_t ne, size_t* bytes);
 
@@ -209,9 +191,8 @@ hipError_t launch_gca_from_fine(int ncomp, int n, int64_t nflag, const int32_t* 
 hipError_t launch_gca_up(int ncomp, int n, const double* trans_in, const int32_t* blk_self,
                          double* blocks_self, double* trans_out, hipStream_t st);
 
-// diagonal of a level operator (FP64): D = sum of element diagonals (DCA or stored block)
-hipError_t launch_diagonal(int ncomp, int n, const double* nu, double scale, const int32_t* blk,
-                           const double* blocks, double* diag, hipStream_t st);
+// diagonal of a level operator (FP64): D = sum of element diagonals
+hipError_t launch_diagonal(int ncomp, int n, const double* nu, double scale, double* diag, hipStream_t st);
 template <typename T>
 hipError_t launch_invert_diag(int64_t count, const double* diag, T* dinv, hipStream_t st);
 

@@ -90,13 +90,12 @@ struct CubeStrip {
 // The shape is a runtime value so that both shapes share one body (and one register
 // allocation).  ubuf_raw / ybuf_raw: the workgroup's LDS ring of u layers and its
 // y-exchange buffer.
-template <int NC, typename T, typename NT, int MODE, bool BLK>
+template <int NC, typename T, typename NT, int MODE>
 __device__ __forceinline__ void cube_tile(T* __restrict__ ubuf_raw, T* __restrict__ ybuf_raw,
                                           double& dot_acc, const int tw, const int X0, const int Y0,
                                           const int Z0,
                                           const int n, const int zc, const T* __restrict__ u,
-                                          const NT* __restrict__ nu, const int32_t* __restrict__ blk,
-                                          const T* __restrict__ yblk, const T* __restrict__ b,
+                                          const NT* __restrict__ nu, const T* __restrict__ b,
                                           const T* __restrict__ dinv, T* __restrict__ out,
                                           const T scale, const T omega, const T alpha, const T gamma,
                                           const T omega0, const T* __restrict__ xprev) {
@@ -191,30 +190,21 @@ __device__ __forceinline__ void cube_tile(T* __restrict__ ubuf_raw, T* __restric
     // cell and node columns of this thread, clamped
     const int64_t cellcol = min(max(cx, 0), n - 1) + (int64_t)n * min(max(cy, 0), n - 1);
     const NT* pnu = nu + elem_slot(0, cellcol, cells);
-    const int32_t* pblk = blk ? blk + elem_slot(0, cellcol, cells) : nullptr;
     constexpr int64_t kSlotsPerCell = AGCA_ELEM_SOA ? 1 : 6;  // z-layer stride factor
     const int64_t col = min(max(cx, 0), n) + n1 * min(max(cy, 0), n);
 
     struct RawCell {
         RawNu<NT> nu;
-        int32_t bi[6];
         bool ok;
     };
     auto load_cell = [&](int z, RawCell& r) {
         r.ok = col_ok && z >= 0 && z < n;
         const int64_t off = (int64_t)min(max(z, 0), n - 1) * clayer * kSlotsPerCell;
         r.nu.load(pnu + off, cells);
-        if constexpr (BLK) {
-#pragma unroll
-            for (int s = 0; s < 6; ++s) r.bi[s] = pblk[off + elem_slot(s, 0, cells)];
-        }
     };
-    auto decode_cell = [&](const RawCell& r, T (&w)[6], int32_t (&bi)[6]) {
+    auto decode_cell = [&](const RawCell& r, T (&w)[6]) {
 #pragma unroll
-        for (int s = 0; s < 6; ++s) {
-            w[s] = r.ok ? r.nu.template get<T>(s) * scale : T(0);
-            if constexpr (BLK) bi[s] = r.ok ? r.bi[s] : -1;
-        }
+        for (int s = 0; s < 6; ++s) w[s] = r.ok ? r.nu.template get<T>(s) * scale : T(0);
     };
     auto load_node = [&](int z, T (&bq)[NC], T (&dq)[NC]) {
         if constexpr (NEEDS_B) {
@@ -279,8 +269,7 @@ __device__ __forceinline__ void cube_tile(T* __restrict__ ubuf_raw, T* __restric
         else
             gather(std::integral_constant<int, SX + 1>{});
         T w_cur[6];
-        int32_t bi_cur[6];
-        decode_cell(rc, w_cur, bi_cur);
+        decode_cell(rc, w_cur);
         T self[NC];  // u at this thread's output node (cell corner 0)
 #pragma unroll
         for (int c = 0; c < NC; ++c) self[c] = U[0][c];
@@ -298,10 +287,7 @@ __device__ __forceinline__ void cube_tile(T* __restrict__ ubuf_raw, T* __restric
         for (int k = 0; k < 8; ++k)
 #pragma unroll
             for (int c = 0; c < NC; ++c) F[k][c] = T(0);
-        if constexpr (BLK)
-            cell_mixed<NC, T>(U, w_cur, bi_cur, yblk, F);
-        else
-            cell_dca<NC, T>(U, w_cur, F);
+        cell_dca<NC, T>(U, w_cur, F);
 
         // x: add the left neighbour's dx=1 corners to my dx=0 corners -> P[dy][dz]
         T P[2][2][NC];
@@ -375,12 +361,11 @@ __device__ __forceinline__ void cube_tile(T* __restrict__ ubuf_raw, T* __restric
     }
 }
 
-template <int NC, typename T, typename NT, int MODE, bool BLK>
+template <int NC, typename T, typename NT, int MODE>
 __global__ void __launch_bounds__(NTHREADS)
 __attribute__((amdgpu_waves_per_eu(CubeWaves<NC, T>::value > 0 ? CubeWaves<NC, T>::value : 1)))
 k_cube(const int n, const int zc, const int gx, const int gy, const int gs, const int gz,
-       const T* __restrict__ u, const NT* __restrict__ nu, const int32_t* __restrict__ blk,
-       const T* __restrict__ yblk, const T* __restrict__ b, const T* __restrict__ dinv,
+       const T* __restrict__ u, const NT* __restrict__ nu, const T* __restrict__ b, const T* __restrict__ dinv,
        T* __restrict__ out, const T scale, const T omega, const T alpha, const T gamma,
        const T omega0, const T* __restrict__ xprev, double* __restrict__ partial) {
     constexpr int UB = (TX + 1) * (TY + 1) + 64;
@@ -396,8 +381,7 @@ k_cube(const int n, const int zc, const int gx, const int gy, const int gs, cons
     const int tw = main_tile ? TX : SX;
     const int X0 = main_tile ? (c % gx) * (TX - 1) : gx * (TX - 1);
     const int Y0 = main_tile ? (c / gx) * (TY - 1) : (c - gx * gy) * (SY - 1);
-    cube_tile<NC, T, NT, MODE, BLK>(ubuf, ybuf, dot_acc, tw, X0, Y0, bz * zc, n, zc, u, nu, blk, yblk, b,
-                                    dinv, out, scale, omega, alpha, gamma, omega0, xprev);
+    cube_tile<NC, T, NT, MODE>(ubuf, ybuf, dot_acc, tw, X0, Y0, bz * zc, n, zc, u, nu, b, dinv, out, scale, omega, alpha, gamma, omega0, xprev);
     if constexpr (MODE == MODE_APPLY_DOT) {
         // fixed-order workgroup reduction: wavefront shuffle, then the 4 wavefronts
         __shared__ double red[NTHREADS / 64];
@@ -412,45 +396,6 @@ k_cube(const int n, const int zc, const int gx, const int gy, const int gs, cons
             partial[blockIdx.x] = sum;
         }
     }
-}
-
-// Products y_f = B_f u_e of the stored Galerkin blocks of all flagged simplices of a
-// level, one thread per (flagged simplex, block row); the element loop then adds
-// y_f to the simplex's corners.  Reads each block once, coalesced by rows.
-template <int NC, typename T>
-__global__ void __launch_bounds__(256)
-k_block_products(const int n, const int64_t nflag, const int32_t* __restrict__ ids,
-                 const T* __restrict__ blocks, const T* __restrict__ u, T* __restrict__ y) {
-    constexpr int M = 4 * NC;
-    const int64_t t = blockIdx.x * (int64_t)256 + threadIdx.x;
-    if (t >= nflag * M) return;
-    const int64_t f = t / M;
-    const int r = (int)(t % M);
-    const int64_t e = ids[f];
-    const int s = (int)(e % 6);
-    int64_t cell = e / 6;
-    const int cx = (int)(cell % n);
-    cell /= n;
-    const int cy = (int)(cell % n);
-    const int cz = (int)(cell / n);
-    const int64_t n1 = n + 1, N = n1 * n1 * n1;
-    const int k1 = 1 << axis1(s), k2 = k1 | (1 << axis2(s));
-    const int corner[4] = {0, k1, k2, 7};
-    T xv[M];
-#pragma unroll
-    for (int a = 0; a < 4; ++a) {
-        const int k = corner[a];
-        const int x = cx + (k & 1), yy = cy + ((k >> 1) & 1), z = cz + ((k >> 2) & 1);
-        const bool bd = x == 0 || yy == 0 || z == 0 || x == n || yy == n || z == n;
-        const int64_t p = x + n1 * (yy + n1 * (int64_t)z);
-#pragma unroll
-        for (int c = 0; c < NC; ++c) xv[4 * c + a] = bd ? T(0) : u[c * N + p];
-    }
-    const T* row = blocks + f * (M * M) + r * M;
-    T acc = T(0);
-#pragma unroll
-    for (int c = 0; c < M; ++c) acc += row[c] * xv[c];
-    y[t] = acc;
 }
 
 // Tile columns of a level with n cells per axis: gx x gy main tiles and gs strip tiles
@@ -518,11 +463,11 @@ int resident_slots(K kernel) {
     return per_cu * cus;
 }
 
-template <int NC, typename T, typename NT, int MODE, bool BLK>
+template <int NC, typename T, typename NT, int MODE>
 hipError_t launch_t(const LevelOp<T>& op, const T* u, const T* b, T* out, const Sweep<T>& sw,
                     hipStream_t st, double* partial = nullptr, int* nblocks = nullptr) {
     const int n = op.n;
-    static const int slots = resident_slots(k_cube<NC, T, NT, MODE, BLK>);
+    static const int slots = resident_slots(k_cube<NC, T, NT, MODE>);
     const int zc = pick_zc(n, slots, CubeStrip<MODE>::value);
     const CubeGrid g = cube_grid(n, CubeStrip<MODE>::value);
     const int gz = (n + 1 + zc - 1) / zc;
@@ -530,23 +475,14 @@ hipError_t launch_t(const LevelOp<T>& op, const T* u, const T* b, T* out, const 
     const dim3 block = CubeStrip<MODE>::value ? dim3(NTHREADS, 1, 1) : dim3(TX, TY, 1);
     dim3 grid((unsigned)nwg, 1, 1);
     const T scale = T(1.0 / (6.0 * n));
-    if constexpr (BLK && MODE != MODE_JACOBI0) {
-        if (op.nflag > 0) {
-            const int64_t threads = op.nflag * 4 * NC;
-            hipLaunchKernelGGL((k_block_products<NC, T>), dim3((unsigned)((threads + 255) / 256)),
-                               dim3(256), 0, st, n, op.nflag, op.ids, op.blocks, u, op.yblk);
-            hipError_t e = hipGetLastError();
-            if (e != hipSuccess) return e;
-        }
-    }
     static const bool xcd_map = [] {
         const char* e = getenv("AGCA_CUBE_XCD");
         return e ? atoi(e) != 0 : true;
     }();
     if (nblocks) *nblocks = nwg;
-    hipLaunchKernelGGL((k_cube<NC, T, NT, MODE, BLK>), grid, block, 0, st, n, zc, g.gx, g.gy, g.gs,
+    hipLaunchKernelGGL((k_cube<NC, T, NT, MODE>), grid, block, 0, st, n, zc, g.gx, g.gy, g.gs,
                        xcd_map ? gz : -gz, u,
-                       reinterpret_cast<const NT*>(op.nu), op.blk, op.yblk, b, op.dinv, out,
+                       reinterpret_cast<const NT*>(op.nu), b, op.dinv, out,
                        scale, sw.omega, sw.alpha, sw.gamma, sw.omega0, sw.xprev, partial);
     return hipGetLastError();
 }
@@ -560,25 +496,11 @@ hipError_t dispatch_nu(const LevelOp<T>& op, const T* u, const T* b, T* out, con
     if ((MODE == MODE_JACOBI || MODE == MODE_JACOBI0 || MODE == MODE_CHEB) && !op.dinv)
         return hipErrorInvalidValue;
     if (MODE == MODE_CHEB && !sw.xprev) return hipErrorInvalidValue;
-    if (op.blk && (!op.blocks || !op.ids || !op.yblk || op.nflag <= 0)) return hipErrorInvalidValue;
-    // the stored-block products are formed from u before the element loop, which
-    // MODE_JACOBI0 never stores
-    if (MODE == MODE_JACOBI0 && op.blk) return hipErrorInvalidValue;
-    const bool blk = op.blk != nullptr;
     if constexpr (sizeof(T) == 8) {
-        if (op.nu_kind != AGCA_F64) return hipErrorInvalidValue;
-        if constexpr (MODE != MODE_JACOBI0)
-            if (blk) return launch_t<NC, T, double, MODE, true>(op, u, b, out, sw, st);
-        return launch_t<NC, T, double, MODE, false>(op, u, b, out, sw, st);
+        return op.nu_kind == AGCA_F64 ? launch_t<NC, T, double, MODE>(op, u, b, out, sw, st) : hipErrorInvalidValue;
     } else {
-        if (op.nu_kind == AGCA_F32) {
-            if constexpr (MODE != MODE_JACOBI0)
-                if (blk) return launch_t<NC, T, float, MODE, true>(op, u, b, out, sw, st);
-            return launch_t<NC, T, float, MODE, false>(op, u, b, out, sw, st);
-        }
-        if (op.nu_kind == AGCA_BF16 && !blk)
-            return launch_t<NC, T, uint16_t, MODE, false>(op, u, b, out, sw, st);
-        return hipErrorInvalidValue;
+        if (op.nu_kind == AGCA_F32) return launch_t<NC, T, float, MODE>(op, u, b, out, sw, st);
+        return op.nu_kind == AGCA_BF16 ? launch_t<NC, T, uint16_t, MODE>(op, u, b, out, sw, st) : hipErrorInvalidValue;
     }
 }
 
@@ -594,16 +516,8 @@ hipError_t launch_cube_dot(int ncomp, const LevelOp<double>& op, const double* u
                            double* partial, int* nblocks, hipStream_t st) {
     if (!op.nu || !u || !out || !partial || !nblocks || op.n < 2 || op.nu_kind != AGCA_F64)
         return hipErrorInvalidValue;
-    if (op.blk && (!op.blocks || !op.ids || !op.yblk || op.nflag <= 0)) return hipErrorInvalidValue;
-    if (ncomp == 1)
-        return op.blk ? launch_t<1, double, double, MODE_APPLY_DOT, true>(op, u, nullptr, out, Sweep<double>{}, st,
-                                                                           partial, nblocks)
-                      : launch_t<1, double, double, MODE_APPLY_DOT, false>(op, u, nullptr, out, Sweep<double>{}, st,
-                                                                            partial, nblocks);
-    return op.blk ? launch_t<3, double, double, MODE_APPLY_DOT, true>(op, u, nullptr, out, Sweep<double>{}, st,
-                                                                       partial, nblocks)
-                  : launch_t<3, double, double, MODE_APPLY_DOT, false>(op, u, nullptr, out, Sweep<double>{}, st,
-                                                                        partial, nblocks);
+    return ncomp == 1 ? launch_t<1, double, double, MODE_APPLY_DOT>(op, u, nullptr, out, Sweep<double>{}, st, partial, nblocks)
+                      : launch_t<3, double, double, MODE_APPLY_DOT>(op, u, nullptr, out, Sweep<double>{}, st, partial, nblocks);
 }
 
 template <int NC, typename T>

@@ -14,96 +14,6 @@ constexpr int NT = 256;
 
 inline unsigned grid_for(int64_t n) { return (unsigned)((n + NT - 1) / NT); }
 
-// ---------------------------------------------------------------------------
-// Flags.  For every element of a coarse level the minimum and maximum of the
-// finest coefficient over its finest descendants, built bottom-up (min and max
-// are exact, so the pyramid equals the direct definition); then the strict
-// ratio test in FP64.
-// ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(NT)
-k_minmax_from_fine(int n, const double* __restrict__ nu_fine, double* __restrict__ mn,
-                   double* __restrict__ mx) {
-    const int64_t ne = 6LL * n * n * n;
-    const int64_t e = blockIdx.x * (int64_t)NT + threadIdx.x;
-    if (e >= ne) return;
-    const int64_t cells_f = 8LL * n * n * n;
-    double a = INFINITY, b = -INFINITY;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        const double v = nu_fine[elem_index(child_id(n, e, k), cells_f)];
-        a = fmin(a, v);
-        b = fmax(b, v);
-    }
-    mn[e] = a;
-    mx[e] = b;
-}
-
-__global__ void __launch_bounds__(NT)
-k_minmax_up(int n, const double* __restrict__ mn_f, const double* __restrict__ mx_f,
-            double* __restrict__ mn, double* __restrict__ mx) {
-    const int64_t ne = 6LL * n * n * n;
-    const int64_t e = blockIdx.x * (int64_t)NT + threadIdx.x;
-    if (e >= ne) return;
-    double a = INFINITY, b = -INFINITY;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        const int64_t c = child_id(n, e, k);
-        a = fmin(a, mn_f[c]);
-        b = fmax(b, mx_f[c]);
-    }
-    mn[e] = a;
-    mx[e] = b;
-}
-
-__global__ void __launch_bounds__(NT)
-k_flag(int64_t ne, const double* __restrict__ mn, const double* __restrict__ mx, double tau,
-       int mode, int32_t* __restrict__ flag) {
-    const int64_t e = blockIdx.x * (int64_t)NT + threadIdx.x;
-    if (e >= ne) return;
-    int32_t f = 0;
-    if (mode == AGCA_FLAG_ALL) f = 1;
-    else if (mode == AGCA_FLAG_RATIO) f = (mx[e] > tau * mn[e]) ? 1 : 0;
-    flag[e] = f;
-}
-
-// Descendant means of the finest coefficient.  For P1 functions the Galerkin
-// product of a coarse element (eq. (2.7)) sums the finest element matrices
-// nu_d K_d of its descendants against the constant gradients of the coarse hat
-// functions; all descendants have the same volume, so the block is the coarse
-// element matrix with the arithmetic mean of nu_d.  The mean of equal-size
-// groups is the mean of the group means, so the pyramid is exact up to rounding.
-__global__ void __launch_bounds__(NT)
-k_mean_from_fine(int n, const double* __restrict__ nu_fine, double* __restrict__ mean) {
-    const int64_t ne = 6LL * n * n * n;
-    const int64_t e = blockIdx.x * (int64_t)NT + threadIdx.x;
-    if (e >= ne) return;
-    const int64_t cells_f = 8LL * n * n * n;
-    double s = 0.0;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) s += nu_fine[elem_index(child_id(n, e, k), cells_f)];
-    mean[e] = 0.125 * s;
-}
-
-__global__ void __launch_bounds__(NT)
-k_mean_up(int n, const double* __restrict__ mean_f, double* __restrict__ mean) {
-    const int64_t ne = 6LL * n * n * n;
-    const int64_t e = blockIdx.x * (int64_t)NT + threadIdx.x;
-    if (e >= ne) return;
-    double s = 0.0;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) s += mean_f[child_id(n, e, k)];
-    mean[e] = 0.125 * s;
-}
-
-// nu_l(e) <- mean(e) on flagged elements (nu in the internal layout)
-__global__ void __launch_bounds__(NT)
-k_override_mean(int64_t ne, const int32_t* __restrict__ flag, const double* __restrict__ mean,
-                double* __restrict__ nu) {
-    const int64_t e = blockIdx.x * (int64_t)NT + threadIdx.x;
-    if (e >= ne || !flag[e]) return;
-    nu[elem_index(e, ne / 6)] = mean[e];
-}
-
 // Macro-element granularity (eqs. (2.8)-(2.9)).  A level-l element (cell c, order s)
 // lies in the macro cube c >> l; inside that cube the Kuhn simplex with axis order
 // (a1, a2, a3) is the set x_a1 >= x_a2 >= x_a3 of relative coordinates, so the macro
@@ -125,11 +35,41 @@ __device__ __forceinline__ int macro_of(int64_t e, int n, int l) {
     return order_index(a1, 3 - a1 - a3, a3) + 6 * (mx + 2 * (my + 2 * mz));
 }
 
+// Flags and effective coefficients.  For every element of a coarse level the minimum,
+// maximum and mean of the finest coefficient over its finest descendants, built bottom-up:
+// min and max are exact, so the pyramid equals the direct definition of the strict ratio test
+// in FP64; all descendants have the same volume, so the mean of the children's means is the
+// mean.  A flagged element's operator is its DCA matrix with that mean: for P1 functions the
+// Galerkin product (eq. (2.7)) sums the finest element matrices nu_d K_d of its descendants
+// against the constant gradients of the coarse hat functions.  Bound by the reads of the
+// level below (8 children in runs of up to 48 bytes).  FROM_FINE: the three inputs are the
+// finest coefficient.
+template <bool FROM_FINE>
 __global__ void __launch_bounds__(NT)
-k_flag_macro(int64_t ne, int n, int l, uint64_t bits, int32_t* __restrict__ flag) {
+k_coarsen(int n, int l, const double* __restrict__ mn_f, const double* __restrict__ mx_f,
+          const double* __restrict__ mean_f, int mode, double tau, uint64_t bits, double* __restrict__ mn,
+          double* __restrict__ mx, double* __restrict__ mean, int32_t* __restrict__ flag, double* __restrict__ nu) {
+    const int64_t ne = 6LL * n * n * n;
     const int64_t e = blockIdx.x * (int64_t)NT + threadIdx.x;
     if (e >= ne) return;
-    flag[e] = (int32_t)((bits >> macro_of(e, n, l)) & 1u);
+    const int64_t cells_f = 8LL * n * n * n;
+    double a = INFINITY, b = -INFINITY, s = 0.0;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        const int64_t id = child_id(n, e, k), c = FROM_FINE ? elem_index(id, cells_f) : id;
+        const double v = mn_f[c];
+        a = fmin(a, v);
+        b = fmax(b, FROM_FINE ? v : mx_f[c]);
+        s += FROM_FINE ? v : mean_f[c];
+    }
+    s *= 0.125;
+    mn[e] = a;
+    mx[e] = b;
+    mean[e] = s;
+    const bool f = mode == AGCA_FLAG_ALL || (mode == AGCA_FLAG_RATIO && b > tau * a) ||
+                   (mode == AGCA_FLAG_MACRO && ((bits >> macro_of(e, n, l)) & 1u));
+    flag[e] = f ? 1 : 0;
+    if (f) nu[elem_index(e, ne / 6)] = s;
 }
 
 // max over the finest elements of each macro element of |grad eta_h| (P1 interpolant):
@@ -165,14 +105,12 @@ k_macro_grad_max(int n, int l, const double* __restrict__ eta, unsigned long lon
 
 __global__ void __launch_bounds__(NT)
 k_scatter_ids(int64_t ne, const int32_t* __restrict__ flag, const int32_t* __restrict__ pos,
-              int32_t* __restrict__ blk, int32_t* __restrict__ blk_soa, int32_t* __restrict__ ids,
-              int64_t* __restrict__ count) {
+              int32_t* __restrict__ blk, int32_t* __restrict__ ids, int64_t* __restrict__ count) {
     const int64_t e = blockIdx.x * (int64_t)NT + threadIdx.x;
     if (e >= ne) return;
     const int32_t f = flag[e];
     const int32_t p = pos[e];
     blk[e] = f ? p : -1;
-    blk_soa[elem_index(e, ne / 6)] = f ? p : -1;  // internal layout
     if (f) ids[p] = (int32_t)e;
     if (e == ne - 1) *count = (int64_t)p + f;
 }
@@ -283,19 +221,16 @@ k_gca_up(int ncomp, int n, const double* __restrict__ trans_in, const int32_t* _
 
 // ---------------------------------------------------------------------------
 // Diagonal of a level operator: each node gathers the diagonal entries of the
-// (up to 24) simplices that contain it, from the DCA element matrix or from the
-// stored block.  Boundary nodes get 0.
+// (up to 24) simplices that contain it.  Boundary nodes get 0.
 // ---------------------------------------------------------------------------
 template <int NC>
 __global__ void __launch_bounds__(NT)
-k_diagonal(int n, const double* __restrict__ nu, double scale, const int32_t* __restrict__ blk,
-           const double* __restrict__ blocks, double* __restrict__ diag) {
+k_diagonal(int n, const double* __restrict__ nu, double scale, double* __restrict__ diag) {
     const int64_t n1 = n + 1, N = n1 * n1 * n1;
     const int64_t p = blockIdx.x * (int64_t)NT + threadIdx.x;
     if (p >= N) return;
     const int x = (int)(p % n1), y = (int)((p / n1) % n1), z = (int)(p / (n1 * n1));
     const bool bd = x == 0 || y == 0 || z == 0 || x == n || y == n || z == n;
-    constexpr int M = 4 * NC;
     const int64_t cells = (int64_t)n * n * n;
     double acc[NC];
 #pragma unroll
@@ -309,15 +244,9 @@ k_diagonal(int n, const double* __restrict__ nu, double scale, const int32_t* __
                 for (int j = 0; j < 4; ++j)
                     if (path_corner(s, j) == k) a = j;
                 if (a < 0) continue;
-                const int64_t e = 6 * cell + s;
-                const int32_t bi = blk ? blk[e] : -1;
 #pragma unroll
-                for (int c = 0; c < NC; ++c) {
-                    if (bi >= 0)
-                        acc[c] += blocks[(int64_t)bi * M * M + (4 * c + a) * M + 4 * c + a];
-                    else
-                        acc[c] += nu[elem_slot(s, cell, cells)] * scale * (double)elem_entry(NC, s, c, a, c, a);
-                }
+                for (int c = 0; c < NC; ++c)
+                    acc[c] += nu[elem_slot(s, cell, cells)] * scale * (double)elem_entry(NC, s, c, a, c, a);
             }
         }
     }
@@ -336,49 +265,17 @@ k_invert_diag(int64_t count, const double* __restrict__ diag, T* __restrict__ di
 
 }  // namespace
 
-hipError_t launch_minmax_from_fine(int n_coarse, const double* nu_fine, double* mn, double* mx,
-                                   hipStream_t st) {
-    if (!nu_fine || !mn || !mx) return hipErrorInvalidValue;
-    const int64_t ne = 6LL * n_coarse * n_coarse * n_coarse;
-    hipLaunchKernelGGL(k_minmax_from_fine, dim3(grid_for(ne)), dim3(NT), 0, st, n_coarse, nu_fine,
-                       mn, mx);
-    return hipGetLastError();
-}
-hipError_t launch_minmax_up(int n_coarse, const double* mn_f, const double* mx_f, double* mn,
-                            double* mx, hipStream_t st) {
-    if (!mn_f || !mx_f || !mn || !mx) return hipErrorInvalidValue;
-    const int64_t ne = 6LL * n_coarse * n_coarse * n_coarse;
-    hipLaunchKernelGGL(k_minmax_up, dim3(grid_for(ne)), dim3(NT), 0, st, n_coarse, mn_f, mx_f, mn,
-                       mx);
-    return hipGetLastError();
-}
-hipError_t launch_flag(int64_t ne, const double* mn, const double* mx, double tau, int mode,
-                       int32_t* flag, hipStream_t st) {
-    if (!mn || !mx || !flag) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_flag, dim3(grid_for(ne)), dim3(NT), 0, st, ne, mn, mx, tau, mode, flag);
-    return hipGetLastError();
-}
-hipError_t launch_mean_from_fine(int n_coarse, const double* nu_fine, double* mean, hipStream_t st) {
-    if (!nu_fine || !mean || n_coarse < 2) return hipErrorInvalidValue;
-    const int64_t ne = 6LL * n_coarse * n_coarse * n_coarse;
-    hipLaunchKernelGGL(k_mean_from_fine, dim3(grid_for(ne)), dim3(NT), 0, st, n_coarse, nu_fine, mean);
-    return hipGetLastError();
-}
-hipError_t launch_mean_up(int n_coarse, const double* mean_f, double* mean, hipStream_t st) {
-    if (!mean_f || !mean || n_coarse < 2) return hipErrorInvalidValue;
-    const int64_t ne = 6LL * n_coarse * n_coarse * n_coarse;
-    hipLaunchKernelGGL(k_mean_up, dim3(grid_for(ne)), dim3(NT), 0, st, n_coarse, mean_f, mean);
-    return hipGetLastError();
-}
-hipError_t launch_override_mean(int64_t ne, const int32_t* flag, const double* mean, double* nu,
-                                hipStream_t st) {
-    if (!flag || !mean || !nu || ne <= 0 || ne % 6) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_override_mean, dim3(grid_for(ne)), dim3(NT), 0, st, ne, flag, mean, nu);
-    return hipGetLastError();
-}
-hipError_t launch_flag_macro(int64_t ne, int n, int l, uint64_t bits, int32_t* flag, hipStream_t st) {
-    if (!flag || ne != 6LL * n * n * n || n != (2 << l)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_flag_macro, dim3(grid_for(ne)), dim3(NT), 0, st, ne, n, l, bits, flag);
+hipError_t launch_coarsen(int n, int l, const double* mn_f, const double* mx_f, const double* mean_f, int mode,
+                          double tau, uint64_t bits, double* mn, double* mx, double* mean, int32_t* flag,
+                          double* nu, hipStream_t st) {
+    if (!mn_f || !mx_f || !mean_f || !mn || !mx || !mean || !flag || !nu || n != (2 << l)) return hipErrorInvalidValue;
+    const int64_t ne = 6LL * n * n * n;
+    if (mn_f == mx_f)
+        hipLaunchKernelGGL(k_coarsen<true>, dim3(grid_for(ne)), dim3(NT), 0, st, n, l, mn_f, mx_f, mean_f, mode, tau,
+                           bits, mn, mx, mean, flag, nu);
+    else
+        hipLaunchKernelGGL(k_coarsen<false>, dim3(grid_for(ne)), dim3(NT), 0, st, n, l, mn_f, mx_f, mean_f, mode, tau,
+                           bits, mn, mx, mean, flag, nu);
     return hipGetLastError();
 }
 hipError_t launch_macro_grad_max(int L, const double* eta, unsigned long long* gbits, hipStream_t st) {
@@ -396,10 +293,9 @@ hipError_t compact_scratch_bytes(int64_t ne, size_t* bytes) {
     *bytes = tmp + (size_t)ne * sizeof(int32_t) + 256;
     return err;
 }
-hipError_t launch_compact(int64_t ne, const int32_t* flag, int32_t* blk, int32_t* blk_soa,
-                          int32_t* ids, int64_t* count_dev, void* scratch, size_t scratch_bytes,
+hipError_t launch_compact(int64_t ne, const int32_t* flag, int32_t* blk, int32_t* ids, int64_t* count_dev, void* scratch, size_t scratch_bytes,
                           hipStream_t st) {
-    if (!flag || !blk || !blk_soa || !ids || !count_dev || !scratch) return hipErrorInvalidValue;
+    if (!flag || !blk || !ids || !count_dev || !scratch) return hipErrorInvalidValue;
     // scratch: [pos (ne int32, 256-aligned)] [cub temp]
     int32_t* pos = static_cast<int32_t*>(scratch);
     size_t off = (((size_t)ne * sizeof(int32_t)) + 255) & ~(size_t)255;
@@ -407,8 +303,7 @@ hipError_t launch_compact(int64_t ne, const int32_t* flag, int32_t* blk, int32_t
     size_t tmp_bytes = scratch_bytes - off;
     hipError_t err = hipcub::DeviceScan::ExclusiveSum(tmp, tmp_bytes, flag, pos, (int)ne, st);
     if (err != hipSuccess) return err;
-    hipLaunchKernelGGL(k_scatter_ids, dim3(grid_for(ne)), dim3(NT), 0, st, ne, flag, pos, blk, blk_soa,
-                       ids, count_dev);
+    hipLaunchKernelGGL(k_scatter_ids, dim3(grid_for(ne)), dim3(NT), 0, st, ne, flag, pos, blk, ids, count_dev);
     return hipGetLastError();
 }
 hipError_t launch_gca_fused2(int ncomp, int n, const double* nu_fine, double h_fine,
@@ -438,16 +333,13 @@ hipError_t launch_gca_up(int ncomp, int n, const double* trans_in, const int32_t
                        blk_self, blocks_self, trans_out);
     return hipGetLastError();
 }
-hipError_t launch_diagonal(int ncomp, int n, const double* nu, double scale, const int32_t* blk,
-                           const double* blocks, double* diag, hipStream_t st) {
-    if (!nu || !diag || (blk && !blocks)) return hipErrorInvalidValue;
+hipError_t launch_diagonal(int ncomp, int n, const double* nu, double scale, double* diag, hipStream_t st) {
+    if (!nu || !diag) return hipErrorInvalidValue;
     const int64_t N = (int64_t)(n + 1) * (n + 1) * (n + 1);
     if (ncomp == 1)
-        hipLaunchKernelGGL(k_diagonal<1>, dim3(grid_for(N)), dim3(NT), 0, st, n, nu, scale, blk,
-                           blocks, diag);
+        hipLaunchKernelGGL(k_diagonal<1>, dim3(grid_for(N)), dim3(NT), 0, st, n, nu, scale, diag);
     else
-        hipLaunchKernelGGL(k_diagonal<3>, dim3(grid_for(N)), dim3(NT), 0, st, n, nu, scale, blk,
-                           blocks, diag);
+        hipLaunchKernelGGL(k_diagonal<3>, dim3(grid_for(N)), dim3(NT), 0, st, n, nu, scale, diag);
     return hipGetLastError();
 }
 template <typename T>

@@ -382,7 +382,7 @@ hipError_t launch_nu(const LevelOp<T>& op, const Smooth2<T>& a, hipStream_t st) 
 
 template <typename T>
 hipError_t launch_smooth2(int ncomp, bool pre, const LevelOp<T>& op, const Smooth2<T>& a, hipStream_t st) {
-    if (!op.nu || !op.dinv || op.blk || op.n < 2 || !a.b || !a.out || (pre ? !a.r : !a.x || a.x == a.out))
+    if (!op.nu || !op.dinv || op.n < 2 || !a.b || !a.out || (pre ? !a.r : !a.x || a.x == a.out))
         return hipErrorInvalidValue;
     if (ncomp == 1) return pre ? launch_nu<1, T, true>(op, a, st) : launch_nu<1, T, false>(op, a, st);
     return pre ? launch_nu<3, T, true>(op, a, st) : launch_nu<3, T, false>(op, a, st);

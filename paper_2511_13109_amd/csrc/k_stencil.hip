@@ -1,10 +1,8 @@
 // Assembled operators of the small coarse levels.
 //
-// On a level with few nodes the element loop is bound by latency, not by
-// bandwidth: a z march of a few steps per workgroup plus a separate pass for the
-// stored-block products.  There the level operator of eq. (2.9) (DCA on unflagged
-// simplices, the stored Galerkin block on flagged ones) is assembled once per
-// coefficient into its 15-point node stencil, and apply, residual and the Jacobi
+// On a level with few nodes the element loop is bound by latency, not by bandwidth: a z
+// march of a few steps per workgroup.  There the level operator of eq. (2.9) is assembled
+// once per coefficient into its 15-point node stencil, and apply, residual and the Jacobi
 // sweeps become one fully parallel gather per (node, component).  The stencil
 // holds exactly the sum of the element matrices, so the operator is unchanged up
 // to the order of the additions.
@@ -30,8 +28,7 @@ constexpr int NNB = kStencilPoints;
 // is a compile-time constant after unrolling.
 template <int NC>
 __global__ void __launch_bounds__(NT)
-k_stencil_assemble(int n, const double* __restrict__ nu, double scale, const int32_t* __restrict__ blk,
-                   const double* __restrict__ blocks, double* __restrict__ S) {
+k_stencil_assemble(int n, const double* __restrict__ nu, double scale, double* __restrict__ S) {
     const int64_t n1 = n + 1, N = n1 * n1 * n1;
     const int64_t p = blockIdx.x * (int64_t)NT + threadIdx.x;
     const int c = blockIdx.y / NC, d = blockIdx.y % NC;
@@ -39,7 +36,6 @@ k_stencil_assemble(int n, const double* __restrict__ nu, double scale, const int
     int x, y, z;
     node_coords(p, n, x, y, z);
     const bool interior = x > 0 && y > 0 && z > 0 && x < n && y < n && z < n;
-    constexpr int M = 4 * NC;
     const int64_t cells = (int64_t)n * n * n;
     double acc[NNB];
 #pragma unroll
@@ -55,20 +51,12 @@ k_stencil_assemble(int n, const double* __restrict__ nu, double scale, const int
 #pragma unroll
                 for (int a = 0; a < 4; ++a) {
                     if (path_corner(s, a) != k) continue;
-                    const int64_t slot = elem_slot(s, cell, cells);
-                    const int32_t bi = blk ? blk[slot] : -1;
-                    if (bi >= 0) {
-                        const double* row = blocks + (int64_t)bi * M * M + (4 * c + a) * M + 4 * d;
+                    const double w = nu[elem_slot(s, cell, cells)] * scale;
 #pragma unroll
-                        for (int bv = 0; bv < 4; ++bv) acc[nbr_of(s, a, bv)] += row[bv];
-                    } else {
-                        const double w = nu[slot] * scale;
-#pragma unroll
-                        for (int bv = 0; bv < 4; ++bv) {
-                            // the unit entry depends on the runtime component pair
-                            const int e = NC == 1 ? path_lap(a, bv) : unit_entry(s, c, a, d, bv);
-                            acc[nbr_of(s, a, bv)] += w * (double)e;
-                        }
+                    for (int bv = 0; bv < 4; ++bv) {
+                        // the unit entry depends on the runtime component pair
+                        const int e = NC == 1 ? path_lap(a, bv) : unit_entry(s, c, a, d, bv);
+                        acc[nbr_of(s, a, bv)] += w * (double)e;
                     }
                 }
             }
@@ -114,15 +102,14 @@ hipError_t launch_nc(int mode, int n, const T* S, const T* u, const T* b, const 
 }  // namespace
 
 hipError_t launch_stencil_assemble(int ncomp, int n, const double* nu, double scale,
-                                   const int32_t* blk, const double* blocks, double* S,
-                                   hipStream_t st) {
-    if (!nu || !S || n < 2 || (blk && !blocks)) return hipErrorInvalidValue;
+                                   double* S, hipStream_t st) {
+    if (!nu || !S || n < 2) return hipErrorInvalidValue;
     const int64_t N = (int64_t)(n + 1) * (n + 1) * (n + 1);
     const dim3 grid((unsigned)((N + NT - 1) / NT), ncomp * ncomp);
     if (ncomp == 1)
-        hipLaunchKernelGGL(k_stencil_assemble<1>, grid, dim3(NT), 0, st, n, nu, scale, blk, blocks, S);
+        hipLaunchKernelGGL(k_stencil_assemble<1>, grid, dim3(NT), 0, st, n, nu, scale, S);
     else
-        hipLaunchKernelGGL(k_stencil_assemble<3>, grid, dim3(NT), 0, st, n, nu, scale, blk, blocks, S);
+        hipLaunchKernelGGL(k_stencil_assemble<3>, grid, dim3(NT), 0, st, n, nu, scale, S);
     return hipGetLastError();
 }
 
