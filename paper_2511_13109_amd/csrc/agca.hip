@@ -49,6 +49,8 @@ struct Level {
     float* dinv32 = nullptr;
     double* sten64 = nullptr;    // assembled 15-point stencil (small coarse levels only)
     float* sten32 = nullptr;
+    double* w64 = nullptr;       // scalar: edge weights of the seven-point form
+    float* w32 = nullptr;
     void* b = nullptr;  // V-cycle work vectors, mg precision
     void* x = nullptr;
     void* t = nullptr;
@@ -122,13 +124,47 @@ int64_t elems_of(int n) { return 6LL * n * n * n; }
         }                                                                                      \
     } while (0)
 
-int32_t dev_alloc(agca_hier* h, void** p, size_t bytes, int64_t* level_bytes = nullptr) {
+void forget_alloc(agca_hier* h, void* p) {
+    const auto i = std::find(h->allocs.begin(), h->allocs.end(), p);
+    if (i != h->allocs.end()) h->allocs.erase(i);
+}
+
+// The scalar levels' edge weights are a faster form of an operator that the element
+// coefficients give as well: they are taken while memory is left, and given up (all of them)
+// when an allocation that a call cannot do without fails beside them.  True if there were any.
+bool drop_weights(agca_hier* h) {
+    bool any = false;
+    for (Level& lv : h->lv) {
+        const size_t count = 3 * (size_t)nodes_of(lv.n);
+        auto drop = [&](auto*& p) {
+            if (!p) return;
+            any = true;
+            forget_alloc(h, p);
+            (void)hipFree(p);  // waits for the work that reads them
+            h->bytes -= (int64_t)(count * sizeof(*p));
+            lv.bytes -= (int64_t)(count * sizeof(*p));
+            p = nullptr;
+        };
+        drop(lv.w64);
+        drop(lv.w32);
+    }
+    return any;
+}
+
+int32_t dev_alloc(agca_hier* h, void** p, size_t bytes, int64_t* level_bytes = nullptr, bool optional = false) {
     *p = nullptr;
     if (bytes == 0) return AGCA_OK;
+    if (!optional && h->cfg.mem_limit_bytes &&
+        (uint64_t)(h->bytes + (int64_t)bytes) > h->cfg.mem_limit_bytes)
+        drop_weights(h);
     if (h->cfg.mem_limit_bytes && (uint64_t)(h->bytes + (int64_t)bytes) > h->cfg.mem_limit_bytes)
         return fail(AGCA_E_OOM, "mem_limit_bytes exceeded (" + std::to_string(h->bytes + bytes) +
                                     " > " + std::to_string(h->cfg.mem_limit_bytes) + ")");
     hipError_t e = hipMalloc(p, bytes);
+    if (e == hipErrorOutOfMemory && !optional) {
+        (void)hipGetLastError();
+        if (drop_weights(h)) e = hipMalloc(p, bytes);
+    }
     if (e != hipSuccess) {
         *p = nullptr;
         (void)hipGetLastError();
@@ -157,11 +193,11 @@ int32_t alloc_t(agca_hier* h, P** p, size_t count, int64_t* lb = nullptr) {
 
 bool mg32(const agca_hier* h) { return h->cfg.mg_dtype == AGCA_F32; }
 
-// Coarse levels with at most this many cells per axis keep their operator as an assembled
+// Coarse levels of vector hierarchies with at most this many cells per axis keep their operator as an assembled
 // stencil (latency-bound sizes).  The line is where the stencil's bytes (135 values per node
 // in vector form) cost more than the element loop's z steps: V-cycle with the line at 32 / 16
 // cells, vector FP64 65^3 164.5 / 158.7 us and 129^3 415.6 / 406.8, vector FP32 115.9 / 121.3
-// and 238.2 / 241.7, scalar FP64 129^3 169.0 / 171.2.  AGCA_STENCIL_MAX_N overrides it (0
+// and 238.2 / 241.7.  AGCA_STENCIL_MAX_N overrides it (0
 // turns the stencils off).
 int stencil_max_n(const agca_config& cfg) {
     static const int v = [] {
@@ -184,6 +220,7 @@ LevelOp<double> level_op<double>(const agca_hier* h, int l) {
     op.nu_kind = AGCA_F64;
     op.dinv = L.dinv64;
     op.sten = L.sten64;
+    op.wts = L.w64;
     return op;
 }
 template <>
@@ -200,6 +237,7 @@ LevelOp<float> level_op<float>(const agca_hier* h, int l) {
     }
     op.dinv = L.dinv32;
     op.sten = L.sten32;
+    op.wts = L.w32;
     return op;
 }
 
@@ -220,13 +258,15 @@ int32_t check_dtype(const agca_hier* h, int dtype, bool need_mg) {
 // ---------------------------------------------------------------------------
 // level operations (templated on the vector precision)
 // ---------------------------------------------------------------------------
-// one pass of the level operator: the assembled stencil where the level has one,
-// the element loop otherwise
+// one pass of the level operator: the seven-point form or the assembled stencil where the
+// level has one, the element loop otherwise
 template <typename T>
 int32_t do_cube(agca_hier* h, int l, int mode, const T* u, const T* b, T* out, const Sweep<T>& sw) {
     const LevelOp<T> op = level_op<T>(h, l);
-    if (op.sten)
-        HIPCHK(h, launch_stencil<T>(h->cfg.ncomp, mode, op.n, op.sten, u, b, op.dinv, out, sw, h->st));
+    if (op.wts)
+        HIPCHK(h, launch_product7<T>(mode, op.n, op.wts, u, b, op.dinv, out, sw, h->st));
+    else if (op.sten)
+        HIPCHK(h, launch_stencil<T>(mode, op.n, op.sten, u, b, op.dinv, out, sw, h->st));
     else
         HIPCHK(h, launch_cube<T>(h->cfg.ncomp, mode, op, u, b, out, sw, h->st));
     return AGCA_OK;
@@ -234,6 +274,27 @@ int32_t do_cube(agca_hier* h, int l, int mode, const T* u, const T* b, T* out, c
 template <typename T>
 int32_t do_cube(agca_hier* h, int l, int mode, const T* u, const T* b, T* out, T omega) {
     return do_cube<T>(h, l, mode, u, b, out, jacobi_sweep<T>(omega));
+}
+
+// v = A_l u in FP64 with partial sums of u . v in h->partial (*nb of them)
+int32_t do_product_dot(agca_hier* h, int l, const double* u, double* v, int* nb) {
+    const LevelOp<double> op = level_op<double>(h, l);
+    if (op.wts)
+        HIPCHK(h, launch_product7_dot(op.n, op.wts, u, v, h->partial, nb, h->st));
+    else
+        HIPCHK(h, launch_cube_dot(h->cfg.ncomp, op, u, v, h->partial, nb, h->st));
+    return AGCA_OK;
+}
+
+// two products in one pass (launch_smooth2)
+template <typename T>
+int32_t do_two_products(agca_hier* h, int l, bool pre, const Smooth2<T>& a) {
+    const LevelOp<T> op = level_op<T>(h, l);
+    if (op.wts)
+        HIPCHK(h, launch_two7<T>(pre, op.n, op.wts, op.dinv, a, h->st));
+    else
+        HIPCHK(h, launch_smooth2<T>(h->cfg.ncomp, pre, op, a, h->st));
+    return AGCA_OK;
 }
 
 // Chebyshev pass coefficients (Cheb, level_ops.h) as a Sweep
@@ -259,7 +320,8 @@ Sweep<T> cheb_sweep(const Cheb& ch, int k, const T* xprev) {
 // stencil levels the separate first sweep measures as fast)
 template <typename T>
 bool fusable(const agca_hier* h, int l) {
-    return level_op<T>(h, l).sten == nullptr;
+    const LevelOp<T> op = level_op<T>(h, l);
+    return op.sten == nullptr && op.wts == nullptr;
 }
 
 // Whether two consecutive products on level l run as one pass (k_smooth2.hip): the levels of
@@ -270,6 +332,7 @@ bool fusable(const agca_hier* h, int l) {
 // at 16 cells, and the gain grows with the size).
 template <typename T>
 bool two_products(const agca_hier* h, int l) {
+    if (level_op<T>(h, l).wts) return true;
     return fusable<T>(h, l) && !(h->cfg.ncomp == 3 && sizeof(T) == 8 && h->lv[l].n < 64);
 }
 
@@ -298,18 +361,15 @@ int smooth_pass_coef(const agca_hier* h, int l, bool pre, int k, const T* xprev,
 }
 
 // Levels 1..K that the coarse end of a V-cycle runs in one workgroup (k_coarse_cycle.hip):
-// consecutive assembled-stencil levels from level 1 up, each below the finest level, whose
-// stencil one compute unit reads per pass in about a microsecond (at most
-// kFuseStencilBytes: levels 1-2 of a scalar hierarchy, level 1 of a vector one; beyond
-// that the one workgroup is slower than a launch per pass spread over the chip), with at
-// most AGCA_FUSE_MAX_N cells per axis (default 8; 0 turns the fused cycle off) and the
-// LDS of levels 0..K within 64 KiB; 0 when level 1 does not qualify or a smoothing phase
-// has more passes than the fused cycle takes.
-constexpr size_t kFuseStencilBytes = 160 * 1024;
+// consecutive levels from level 1 up that have their operator in the form it reads (scalar:
+// edge weights, up to the finest level; vector: assembled stencils, below the finest level),
+// as many as its registers and LDS take (coarse_cycle_max_level), with at most
+// AGCA_FUSE_MAX_N cells per axis (default no bound; 0 turns the fused cycle off); 0 when level
+// 1 does not qualify or a smoothing phase has more passes than the fused cycle takes.
 int fuse_max_n() {
     static const int v = [] {
         const char* e = getenv("AGCA_FUSE_MAX_N");
-        return e ? atoi(e) : 8;
+        return e ? atoi(e) : 1 << 20;
     }();
     return v;
 }
@@ -318,11 +378,9 @@ int coarse_cycle_levels(const agca_hier* h) {
     if (h->cfg.pre_sweeps > kCyclePasses || h->cfg.post_sweeps > kCyclePasses) return 0;
     const int nc = h->cfg.ncomp;
     int K = 0;
-    for (int l = 1; l <= kCycleLevels && l < h->cfg.L; ++l) {
-        const Level& lv = h->lv[l];
-        if (!level_op<T>(h, l).sten || lv.n != (2 << l) || lv.n > fuse_max_n()) break;
-        if ((size_t)nc * nc * kStencilPoints * lv.nodes * sizeof(T) > kFuseStencilBytes) break;
-        if (coarse_cycle_lds(nc, l, sizeof(T)) > 65536) break;
+    for (int l = 1; l <= coarse_cycle_max_level(nc, sizeof(T)) && l <= h->cfg.L; ++l) {
+        const LevelOp<T> op = level_op<T>(h, l);
+        if (!(nc == 1 ? op.wts : op.sten) || op.n != (2 << l) || op.n > fuse_max_n()) break;
         K = l;
     }
     return K;
@@ -380,7 +438,7 @@ int32_t do_vcycle(agca_hier* h, const T* bL, T* xL) {
         // (pre-sweeps after the first pass, then every post-sweep; the prolongation
         // adds in place)
         const bool two = two_products<T>(h, l);
-        const int first = (pre >= 2 && fuse) ? 2 : (pre > 0 ? 1 : 0);
+        const int first = (pre >= 2 && (fuse || (two && pre == 2))) ? 2 : (pre > 0 ? 1 : 0);
         const int launches = (pre - first) + (two && post == 2 ? 1 : post);
         T* cur = (launches % 2 == 0) ? home : other;
         T* alt = (cur == home) ? other : home;
@@ -396,7 +454,7 @@ int32_t do_vcycle(agca_hier* h, const T* bL, T* xL) {
             s2.om0 = sw.omega0;
             s2.a1 = sw.alpha;
             s2.o1 = sw.omega;
-            HIPCHK(h, launch_smooth2<T>(nc, true, op, s2, h->st));
+            TRY(do_two_products<T>(h, l, true, s2));
             xcur[l] = cur;
             xalt[l] = alt;
             HIPCHK(h, launch_restrict<T>(nc, h->lv[l].n, s2.r, static_cast<T*>(h->lv[l - 1].b), h->st));
@@ -428,6 +486,7 @@ int32_t do_vcycle(agca_hier* h, const T* bL, T* xL) {
         for (int l = 1; l <= K; ++l) {
             const LevelOp<T> op = level_op<T>(h, l);
             cc.sten[l] = op.sten;
+            cc.wts[l] = op.wts;
             cc.dinv[l] = op.dinv;
             cc.first_omega[l] = cheb ? T(1.0 / Cheb(h->lam[l]).theta) : om;
             for (int k = 0; k < kCyclePasses; ++k) {
@@ -447,8 +506,8 @@ int32_t do_vcycle(agca_hier* h, const T* bL, T* xL) {
             }
         }
         cc.ainv = h->ainv0;
-        cc.b = static_cast<const T*>(h->lv[K].b);
-        cc.x = static_cast<T*>(h->lv[K].x);
+        cc.b = K == L ? bL : static_cast<const T*>(h->lv[K].b);
+        cc.x = K == L ? xL : static_cast<T*>(h->lv[K].x);
         HIPCHK(h, launch_coarse_cycle<T>(nc, K, cc, h->st));
         xcur[K] = cc.x;
     } else {
@@ -474,7 +533,7 @@ int32_t do_vcycle(agca_hier* h, const T* bL, T* xL) {
             s2.a2 = s1.alpha;
             s2.g2 = s1.gamma;
             s2.o2 = s1.omega;
-            HIPCHK(h, launch_smooth2<T>(nc, false, level_op<T>(h, l), s2, h->st));
+            TRY(do_two_products<T>(h, l, false, s2));
             std::swap(cur, alt);
         } else
             for (int i = 0; i < post; ++i) {
@@ -681,7 +740,7 @@ int32_t estimate_eigenvalues(agca_hier* h) {
             } else {
                 // element-loop level: y = A v with v . A v in the same pass
                 int nbq = 0;
-                HIPCHK(h, launch_cube_dot(nc, op, v, y, h->partial, &nbq, h->st));
+                TRY(do_product_dot(h, l, v, y, &nbq));
                 TRY(reduce_to(h, h->partial, nbq, k));
             }
             HIPCHK(h, launch_lanczos_step(cnt, y, lv.diag, v, k > 0 ? vprev : nullptr, h->red + k,
@@ -935,8 +994,10 @@ int32_t build_operators(agca_hier* h, const double* nu_fine, const double* const
         } else {
             HIPCHK(h, launch_invert_diag<double>(cnt, lv.diag, lv.dinv64, h->st));
         }
+        if (lv.w64) HIPCHK(h, launch_weights<double>(lv.n, lv.nu64, nullptr, lv.w64, h->st));
+        if (lv.w32) HIPCHK(h, launch_weights<float>(lv.n, lv.nu64, lv.nubf, lv.w32, h->st));
         if (lv.sten64) {
-            HIPCHK(h, launch_stencil_assemble(nc, lv.n, lv.nu64, scale, lv.sten64, h->st));
+            HIPCHK(h, launch_stencil_assemble(lv.n, lv.nu64, scale, lv.sten64, h->st));
             if (lv.sten32)
                 HIPCHK(h, launch_cast(AGCA_F64, AGCA_F32, lv.sten64, lv.sten32,
                                       (int64_t)nc * nc * 15 * lv.nodes, h->st));
@@ -1129,7 +1190,7 @@ int32_t agca_create(const agca_config* cfg, const double* nu_fine, const double*
         if (rc == AGCA_OK) rc = alloc_t(h, &lv.diag, nv, &lv.bytes);
         if (rc == AGCA_OK && mg32(h)) rc = alloc_t(h, &lv.dinv32, nv, &lv.bytes);
         if (rc == AGCA_OK && !mg32(h)) rc = alloc_t(h, &lv.dinv64, nv, &lv.bytes);
-        if (rc == AGCA_OK && l >= 1 && l < L && lv.n <= stencil_max_n(*cfg)) {
+        if (rc == AGCA_OK && nc == 3 && l >= 1 && l < L && lv.n <= stencil_max_n(*cfg)) {
             rc = alloc_t(h, &lv.sten64, (size_t)nv * nc * 15, &lv.bytes);
             if (rc == AGCA_OK && mg32(h)) rc = alloc_t(h, &lv.sten32, (size_t)nv * nc * 15, &lv.bytes);
         }
@@ -1140,11 +1201,25 @@ int32_t agca_create(const agca_config* cfg, const double* nu_fine, const double*
     }
     if (rc == AGCA_OK) rc = alloc_t(h, &h->ainv0, 9);
     if (rc == AGCA_OK) {
-        h->partial_cap = std::max(2 * h->nb_partial, cube_grid_blocks(h->lv[L].n));
+        h->partial_cap = std::max(2 * h->nb_partial, std::max(cube_grid_blocks(h->lv[L].n), product7_blocks(h->lv[L].n)));
         rc = alloc_t(h, &h->partial, h->partial_cap);
     }
     if (rc == AGCA_OK) rc = alloc_t(h, &h->red, AGCA_RED_SLOTS);
     if (rc == AGCA_OK) rc = alloc_t(h, &h->counter, 4);
+    if (rc == AGCA_OK && nc == 1) {
+        bool room = true;
+        for (Level& lv : h->lv) {
+            const size_t count = 3 * (size_t)lv.nodes;
+            auto take = [&](auto*& p) {
+                void* v = nullptr;
+                room = room && dev_alloc(h, &v, count * sizeof(*p), &lv.bytes, true) == AGCA_OK;
+                p = static_cast<std::remove_reference_t<decltype(p)>>(v);
+            };
+            take(lv.w64);
+            if (mg32(h)) take(lv.w32);
+        }
+        if (!room) drop_weights(h);
+    }
     if (rc == AGCA_OK) {
         hipError_t e = hipHostMalloc((void**)&h->red_host, AGCA_RED_SLOTS * sizeof(double));
         if (e != hipSuccess) rc = fail(AGCA_E_OOM, "hipHostMalloc failed");
@@ -1471,8 +1546,7 @@ int32_t agca_solve(agca_hier* h, const agca_solve_opts* o, const double* b, doub
             while (it < o->max_iter) {
                 // q = A p fused with p . q
                 int nbq = 0;
-                HIPCHK(h, launch_cube_dot(h->cfg.ncomp, level_op<double>(h, L), p, q, h->partial, &nbq,
-                                          h->st));
+                TRY(do_product_dot(h, L, p, q, &nbq));
                 TRY(reduce_to(h, h->partial, nbq, PQ));
                 // x += alpha p, r -= alpha q (and its FP32 copy), fused with r . r
                 HIPCHK(h, launch_cg_update(cnt, red + RZ, red + PQ, p, q, x, r, mixed ? r32 : nullptr,

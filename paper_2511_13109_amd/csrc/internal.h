@@ -19,6 +19,7 @@ struct LevelOp {
     int nu_kind = 0;           // AGCA_F64 / AGCA_F32 / AGCA_BF16 storage of nu
     const T* dinv = nullptr;       // inverse Jacobi diagonal, level vector (0 on the boundary)
     const T* sten = nullptr;       // assembled stencil (k_stencil.hip layout) or null
+    const T* wts = nullptr;        // scalar: edge weights (k_scalar.hip layout) or null
 };
 
 // MODE_JACOBI0: two passes from a zero guess: the input x = omega0 D^-1 b is formed on
@@ -65,12 +66,27 @@ struct Smooth2 {
 template <typename T>
 hipError_t launch_smooth2(int ncomp, bool pre, const LevelOp<T>& op, const Smooth2<T>& a, hipStream_t st);
 
+// Seven-point form of a scalar level operator (k_scalar.hip): edge weights W (3 (n+1)^3) from
+// the FP64 coefficient or a BF16 one; one pass (MODE_APPLY, MODE_RESIDUAL, MODE_JACOBI,
+// MODE_CHEB); v = A u with partial sums of u . v (product7_blocks(n) of them); two products
+// in one pass (launch_smooth2)
+template <typename T>
+hipError_t launch_weights(int n, const double* nu, const uint16_t* nu_bf16, T* W, hipStream_t st);
+template <typename T>
+hipError_t launch_product7(int mode, int n, const T* W, const T* u, const T* b, const T* dinv, T* out,
+                           const Sweep<T>& sw, hipStream_t st);
+hipError_t launch_product7_dot(int n, const double* W, const double* u, double* out, double* partial, int* nblocks,
+                               hipStream_t st);
+int product7_blocks(int n);
+template <typename T>
+hipError_t launch_two7(bool pre, int n, const T* W, const T* dinv, const Smooth2<T>& a, hipStream_t st);
+
 // assembled 15-point stencil of a coarse level (FP64)
-hipError_t launch_stencil_assemble(int ncomp, int n, const double* nu, double scale, double* S, hipStream_t st);
+hipError_t launch_stencil_assemble(int n, const double* nu, double scale, double* S, hipStream_t st);
 // apply / residual / Jacobi-type passes (MODE_APPLY, MODE_RESIDUAL, MODE_JACOBI, MODE_CHEB)
 // with an assembled stencil
 template <typename T>
-hipError_t launch_stencil(int ncomp, int mode, int n, const T* S, const T* u, const T* b,
+hipError_t launch_stencil(int mode, int n, const T* S, const T* u, const T* b,
                           const T* dinv, T* out, const Sweep<T>& sw, hipStream_t st);
 
 // transfers (Section 2.1)
@@ -83,19 +99,19 @@ hipError_t launch_prolong_add(int ncomp, int n_fine, const T* ec, T* xf, hipStre
 template <typename T>
 hipError_t launch_coarse_solve(int ncomp, const double* ainv, const T* b, T* x, hipStream_t st);
 
-// The coarse end of a V-cycle in one workgroup (k_coarse_cycle.hip): levels K..1 (all
-// assembled-stencil levels, level l with n = 2^(l+1) cells) and the level-0 solve, from
-// the level-K right-hand side b to the level-K iterate x, with every intermediate vector
-// in LDS.  Smoothing passes as in the per-launch V-cycle: pre-smoothing pass 0 is x = first_omega D^-1 b from zero (0 when
-// pre = 0), pre passes 1.. and post passes 0.. write
-// x_out = alpha x + gamma x_prev + omega D^-1 (b - A x) with the mode and coefficients
-// given per level and pass (MODE_JACOBI ignores gamma).
+// The coarse end of a V-cycle in one workgroup (k_coarse_cycle.hip): levels K..1 (level l with
+// n = 2^(l+1) cells) and the level-0 solve, from the level-K right-hand side b to the
+// level-K iterate x, boundary slots included.  Smoothing passes as in the per-launch V-cycle:
+// pre-smoothing pass 0 is x = first_omega D^-1 b from zero (0 when pre = 0), pre passes 1..
+// and post passes 0.. write x_out = alpha x + gamma x_prev + omega D^-1 (b - A x) with the
+// mode and coefficients given per level and pass (MODE_JACOBI ignores gamma).
 constexpr int kCycleLevels = 3;  // K <= 3
 constexpr int kCyclePasses = 8;  // pre, post <= 8
 template <typename T>
 struct CoarseCycle {
     int pre = 0, post = 0;
-    const T* sten[kCycleLevels + 1] = {};
+    const T* sten[kCycleLevels + 1] = {};  // vector: 15-point stencils
+    const T* wts[kCycleLevels + 1] = {};   // scalar: edge weights
     const T* dinv[kCycleLevels + 1] = {};
     T first_omega[kCycleLevels + 1] = {};
     int8_t pre_mode[kCycleLevels + 1][kCyclePasses] = {};
@@ -106,8 +122,7 @@ struct CoarseCycle {
     const T* b = nullptr;          // level K, ncomp (n+1)^3 values (device)
     T* x = nullptr;                // level K, written
 };
-// LDS bytes of the fused cycle over levels 0..K
-size_t coarse_cycle_lds(int ncomp, int K, size_t elem);
+int coarse_cycle_max_level(int ncomp, size_t elem);  // the largest K
 template <typename T>
 hipError_t launch_coarse_cycle(int ncomp, int K, const CoarseCycle<T>& a, hipStream_t st);
 

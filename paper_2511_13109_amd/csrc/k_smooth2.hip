@@ -53,34 +53,6 @@ struct Waves {
     static constexpr int value = NC == 3 && sizeof(T) == 8 ? 2 : 4;
 };
 
-// Global accesses of the march go through buffer descriptors of one node or cell layer,
-// formed per step by scalar instructions: a lane's address is one 32-bit offset, a load
-// past the layer's end returns 0 and a store there is dropped.  Lanes outside the lattice
-// or on its boundary therefore carry the offset kOut instead of selects and branches, and
-// a layer outside the lattice has length 0.
-constexpr uint32_t kOut = 0xf0000000u;
-using Rsrc = __amdgpu_buffer_rsrc_t;
-using u32x2 = uint32_t __attribute__((ext_vector_type(2)));
-using u32x3 = uint32_t __attribute__((ext_vector_type(3)));
-using u32x4 = uint32_t __attribute__((ext_vector_type(4)));
-template <typename P>
-__device__ __forceinline__ Rsrc layer_of(const P* p, bool inside, uint32_t bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<P*>(p), 0, inside ? (int)bytes : 0, 0x00027000);
-}
-template <typename T>
-__device__ __forceinline__ T bload(Rsrc r, uint32_t off) {
-    if constexpr (sizeof(T) == 8)
-        return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
-    else
-        return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
-}
-template <typename T>
-__device__ __forceinline__ void bstore(Rsrc r, uint32_t off, T v) {
-    if constexpr (sizeof(T) == 8)
-        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, off, 0, 0);
-    else
-        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, off, 0, 0);
-}
 // the six coefficients of a cell as loaded, decoded when used
 template <typename NT>
 struct CellNu;
@@ -325,41 +297,10 @@ k_smooth2(const int n, const int zc, const int gx, const int gy, const int gz, c
     }
 }
 
-// Chunks of z layers: the count that minimises rounds x steps x time of a step.  A chunk of
-// zc layers marches zc + 4 steps; a step with k workgroups on a compute unit takes about
-// (3 + 4 k) / 7 of one with a single workgroup (129^3 FP32: 2.15 us for k = 1, 3.4 us for 2).
-int pick_chunks(int n, int64_t cols, int per_cu, int64_t cus) {
-    int best = 1;
-    double cost = -1.0;
-    for (int gz = 1; gz <= n + 1; ++gz) {
-        const int zc = (n + gz) / gz;
-        if ((n + zc) / zc != gz) continue;  // the same chunk length with fewer chunks
-        const int64_t wgs = cols * gz;
-        const int64_t k = std::min<int64_t>(per_cu, (wgs + cus - 1) / cus);
-        const int64_t rounds = (wgs + k * cus - 1) / (k * cus);
-        const double c = (double)rounds * (zc + 4.5) * (3.0 + 4.0 * k);
-        if (cost < 0.0 || c < cost) {
-            cost = c;
-            best = gz;
-        }
-    }
-    return best;
-}
-
 template <int NC, typename T, typename NT, bool PRE>
 hipError_t launch_t(const LevelOp<T>& op, const Smooth2<T>& a, hipStream_t st) {
     const int n = op.n;
-    static const std::pair<int, int> fit = [] {  // workgroups per compute unit, compute units
-        int per_cu = 0, dev = 0, cus = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_smooth2<NC, T, NT, PRE>, NTH, 0) != hipSuccess ||
-            hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || per_cu < 1 ||
-            cus < 1) {
-            (void)hipGetLastError();
-            return std::make_pair(1, 256);
-        }
-        return std::make_pair(per_cu, cus);
-    }();
+    static const std::pair<int, int> fit = workgroups_fit(k_smooth2<NC, T, NT, PRE>, NTH);
     const int gx = (n + OX) / OX, gy = (n + OY) / OY;
     const int gz = pick_chunks(n, (int64_t)gx * gy, fit.first, fit.second);
     const int zc = (n + gz) / gz;

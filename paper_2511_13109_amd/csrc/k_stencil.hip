@@ -1,4 +1,4 @@
-// Assembled operators of the small coarse levels.
+// Assembled operators of the small coarse levels of vector hierarchies.
 //
 // On a level with few nodes the element loop is bound by latency, not by bandwidth: a z
 // march of a few steps per workgroup.  There the level operator of eq. (2.9) is assembled
@@ -21,12 +21,12 @@ namespace {
 
 constexpr int NT = 256;
 constexpr int NNB = kStencilPoints;
+constexpr int NC = 3;
 
 // One thread per (node, component pair c, d = blockIdx.y / NC, blockIdx.y % NC);
 // rows of boundary nodes stay zero.  Loops over the 8 cells around the node and the
 // simplices of each cell that contain it; everything that decides a neighbour index
 // is a compile-time constant after unrolling.
-template <int NC>
 __global__ void __launch_bounds__(NT)
 k_stencil_assemble(int n, const double* __restrict__ nu, double scale, double* __restrict__ S) {
     const int64_t n1 = n + 1, N = n1 * n1 * n1;
@@ -55,7 +55,7 @@ k_stencil_assemble(int n, const double* __restrict__ nu, double scale, double* _
 #pragma unroll
                     for (int bv = 0; bv < 4; ++bv) {
                         // the unit entry depends on the runtime component pair
-                        const int e = NC == 1 ? path_lap(a, bv) : unit_entry(s, c, a, d, bv);
+                        const int e = unit_entry(s, c, a, d, bv);
                         acc[nbr_of(s, a, bv)] += w * (double)e;
                     }
                 }
@@ -67,7 +67,7 @@ k_stencil_assemble(int n, const double* __restrict__ nu, double scale, double* _
 }
 
 // One thread per (node, component c = blockIdx.y); the body is stencil_node (level_ops.h).
-template <int NC, typename T, int MODE>
+template <typename T, int MODE>
 __global__ void __launch_bounds__(NT)
 k_stencil_apply(int n, const T* __restrict__ S, const T* __restrict__ u, const T* __restrict__ b,
                 const T* __restrict__ dinv, T* __restrict__ out, T omega, T alpha, T gamma,
@@ -78,55 +78,45 @@ k_stencil_apply(int n, const T* __restrict__ S, const T* __restrict__ u, const T
     stencil_node<NC, T, MODE>(n, p, (int)blockIdx.y, S, u, b, dinv, out, omega, alpha, gamma, xprev);
 }
 
-template <int NC, typename T, int MODE>
+template <typename T, int MODE>
 hipError_t launch_mode(int n, const T* S, const T* u, const T* b, const T* dinv, T* out,
                        const Sweep<T>& sw, hipStream_t st) {
     const int64_t N = (int64_t)(n + 1) * (n + 1) * (n + 1);
-    hipLaunchKernelGGL((k_stencil_apply<NC, T, MODE>), dim3((unsigned)((N + NT - 1) / NT), NC),
+    hipLaunchKernelGGL((k_stencil_apply<T, MODE>), dim3((unsigned)((N + NT - 1) / NT), NC),
                        dim3(NT), 0, st, n, S, u, b, dinv, out, sw.omega, sw.alpha, sw.gamma, sw.xprev);
     return hipGetLastError();
 }
 
-template <int NC, typename T>
-hipError_t launch_nc(int mode, int n, const T* S, const T* u, const T* b, const T* dinv, T* out,
-                     const Sweep<T>& sw, hipStream_t st) {
-    switch (mode) {
-        case MODE_APPLY: return launch_mode<NC, T, MODE_APPLY>(n, S, u, b, dinv, out, sw, st);
-        case MODE_RESIDUAL: return launch_mode<NC, T, MODE_RESIDUAL>(n, S, u, b, dinv, out, sw, st);
-        case MODE_JACOBI: return launch_mode<NC, T, MODE_JACOBI>(n, S, u, b, dinv, out, sw, st);
-        case MODE_CHEB: return launch_mode<NC, T, MODE_CHEB>(n, S, u, b, dinv, out, sw, st);
-        default: return hipErrorInvalidValue;
-    }
-}
-
 }  // namespace
 
-hipError_t launch_stencil_assemble(int ncomp, int n, const double* nu, double scale,
+hipError_t launch_stencil_assemble(int n, const double* nu, double scale,
                                    double* S, hipStream_t st) {
     if (!nu || !S || n < 2) return hipErrorInvalidValue;
     const int64_t N = (int64_t)(n + 1) * (n + 1) * (n + 1);
-    const dim3 grid((unsigned)((N + NT - 1) / NT), ncomp * ncomp);
-    if (ncomp == 1)
-        hipLaunchKernelGGL(k_stencil_assemble<1>, grid, dim3(NT), 0, st, n, nu, scale, S);
-    else
-        hipLaunchKernelGGL(k_stencil_assemble<3>, grid, dim3(NT), 0, st, n, nu, scale, S);
+    const dim3 grid((unsigned)((N + NT - 1) / NT), NC * NC);
+    hipLaunchKernelGGL(k_stencil_assemble, grid, dim3(NT), 0, st, n, nu, scale, S);
     return hipGetLastError();
 }
 
 template <typename T>
-hipError_t launch_stencil(int ncomp, int mode, int n, const T* S, const T* u, const T* b,
+hipError_t launch_stencil(int mode, int n, const T* S, const T* u, const T* b,
                           const T* dinv, T* out, const Sweep<T>& sw, hipStream_t st) {
     if (!S || !u || !out || n < 2) return hipErrorInvalidValue;
     if (mode != MODE_APPLY && !b) return hipErrorInvalidValue;
     if ((mode == MODE_JACOBI || mode == MODE_CHEB) && !dinv) return hipErrorInvalidValue;
     if (mode == MODE_CHEB && !sw.xprev) return hipErrorInvalidValue;
-    return ncomp == 1 ? launch_nc<1, T>(mode, n, S, u, b, dinv, out, sw, st)
-                      : launch_nc<3, T>(mode, n, S, u, b, dinv, out, sw, st);
+    switch (mode) {
+        case MODE_APPLY: return launch_mode<T, MODE_APPLY>(n, S, u, b, dinv, out, sw, st);
+        case MODE_RESIDUAL: return launch_mode<T, MODE_RESIDUAL>(n, S, u, b, dinv, out, sw, st);
+        case MODE_JACOBI: return launch_mode<T, MODE_JACOBI>(n, S, u, b, dinv, out, sw, st);
+        case MODE_CHEB: return launch_mode<T, MODE_CHEB>(n, S, u, b, dinv, out, sw, st);
+        default: return hipErrorInvalidValue;
+    }
 }
 
-template hipError_t launch_stencil<double>(int, int, int, const double*, const double*, const double*,
+template hipError_t launch_stencil<double>(int, int, const double*, const double*, const double*,
                                            const double*, double*, const Sweep<double>&, hipStream_t);
-template hipError_t launch_stencil<float>(int, int, int, const float*, const float*, const float*,
+template hipError_t launch_stencil<float>(int, int, const float*, const float*, const float*,
                                           const float*, float*, const Sweep<float>&, hipStream_t);
 
 }  // namespace agca

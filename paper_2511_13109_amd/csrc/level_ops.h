@@ -1,8 +1,6 @@
 // Per-node bodies of the small-level multigrid operations: the assembled-stencil pass,
 // the restriction and the prolongation of Section 2.1, and the Chebyshev pass
-// coefficients of Section 4.  The one-launch-per-operation kernels (k_stencil.hip,
-// k_vec.hip) and the fused coarse-level cycle (k_coarse_cycle.hip) run these same
-// bodies, so both forms compute the same arithmetic in the same order.
+// coefficients of Section 4 (k_stencil.hip, k_vec.hip).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -44,9 +42,7 @@ struct Cheb {
 // S in the k_stencil.hip layout S[((c NC + d) 15 + k) N + p].  Boundary rows write 0 and
 // boundary values of u count as 0.  MODE_APPLY: A u; MODE_RESIDUAL: b - A u;
 // MODE_JACOBI: alpha u + omega D^-1 (b - A u); MODE_CHEB: the same plus gamma x_prev.
-// ISSUE_ALL keeps every stencil load of the row ahead of the arithmetic (a scheduling
-// barrier: a workgroup alone on its compute unit has no other waves to hide them behind).
-template <int NC, typename T, int MODE, bool ISSUE_ALL = false>
+template <int NC, typename T, int MODE>
 __device__ __forceinline__ void stencil_node(int n, int64_t p, int c, const T* __restrict__ S,
                                              const T* u, const T* b, const T* __restrict__ dinv,
                                              T* out, T omega, T alpha, T gamma, const T* xprev) {
@@ -65,7 +61,6 @@ __device__ __forceinline__ void stencil_node(int n, int64_t p, int c, const T* _
     for (int k = 0; k < kStencilPoints; ++k)
 #pragma unroll
         for (int d = 0; d < NC; ++d) sv[k * NC + d] = S[((int64_t)(c * NC + d) * kStencilPoints + k) * N + p];
-    if constexpr (ISSUE_ALL) __builtin_amdgcn_sched_barrier(0);
     T acc = T(0);
 #pragma unroll
     for (int k = 0; k < kStencilPoints; ++k) {
