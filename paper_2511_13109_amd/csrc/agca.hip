@@ -409,7 +409,7 @@ int32_t do_smooth(agca_hier* h, int l, int sweeps, double omega, const T* b, T* 
 // (the first, x = omega0 D^-1 b, is formed while loading; Chebyshev only for degree
 // 2, whose second pass needs no stored first iterate); elsewhere the first pass is
 // the elementwise x = omega0 D^-1 b.  Where two_products holds, two passes before the
-// correction and the residual are one launch, and two passes after it another.  Every further pass writes the level's other
+// correction and the residual are one launch, and the prolongation and two passes after it another.  Every further pass writes the level's other
 // buffer (a Chebyshev pass reads the previous iterate from it at the same node), so
 // the passes ping-pong, and on the finest level the starting buffer is chosen so
 // that the last pass lands in the caller's x (no copies).
@@ -519,13 +519,15 @@ int32_t do_vcycle(agca_hier* h, const T* bL, T* xL) {
         const T* bl = (l == L) ? bL : static_cast<const T*>(h->lv[l].b);
         T* cur = xcur[l];
         T* alt = xalt[l];
-        HIPCHK(h, launch_prolong_add<T>(nc, h->lv[l].n, xcur[l - 1], cur, h->st));
-        if (post == 2 && two_products<T>(h, l)) {
+        const bool two = post == 2 && two_products<T>(h, l);
+        if (!two) HIPCHK(h, launch_prolong_add<T>(nc, h->lv[l].n, xcur[l - 1], cur, h->st));
+        if (two) {
             Sweep<T> s0, s1;
             (void)smooth_pass_coef<T>(h, l, false, 0, nullptr, &s0);
             (void)smooth_pass_coef<T>(h, l, false, 1, nullptr, &s1);
             Smooth2<T> s2;
             s2.x = cur;
+            s2.e = xcur[l - 1];
             s2.b = bl;
             s2.out = alt;
             s2.a1 = s0.alpha;

@@ -135,6 +135,58 @@ __device__ __forceinline__ void bstore(Rsrc r, uint32_t off, T v) {
     else
         __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, off, 0, 0);
 }
+// The coarse correction, added to the iterate where a two-product pass stages it: fine node X
+// takes half of e at the coarse nodes X/2 rounded down and up (k_vec.hip, Transfers).  Of the
+// coarse level a tile of TX+1 x TY+1 fine nodes needs EX x EY nodes in each of two layers, which
+// the workgroup keeps in LDS (layer m in buffer m & 1): fine layer f = 2m reads layer m, f = 2m+1
+// layers m and m+1.  Layer m+1 is loaded in the step that stages f = 2m-1 and stored in the next one, a
+// barrier after the last reads of layer m-1, whose buffer it takes.
+template <int NC, typename T, int TX, int TY>
+struct CoarseTile {
+    static constexpr int EX = TX / 2 + 2, EY = TY / 2 + 2, EN = EX * EY;
+    static_assert(EN <= 256 && EN <= TX * TY);
+    using Tile = T[2][NC][EN];
+    const T* e;
+    int nc, x0, y0;
+    // n: the fine level's; (X0, Y0): first fine node of the tile
+    __device__ __forceinline__ void init(const T* e_, int n, int X0, int Y0) {
+        e = e_;
+        nc = n >> 1;
+        x0 = X0 >> 1;
+        y0 = Y0 >> 1;
+    }
+    // The next two are constants of a thread, for the caller to keep.
+    // coarse nodes of the thread's fine nodes a and b: lower and upper one, 8 bits each
+    __device__ __forceinline__ uint32_t slots(int xa, int ya, int xb, int yb) const {
+        auto slot = [&](int X, int Y) { return (uint32_t)(((X >> 1) - x0) + EX * ((Y >> 1) - y0)); };
+        return slot(xa, ya) | slot(xa + 1, ya + 1) << 8 | slot(xb, yb) << 16 | slot(xb + 1, yb + 1) << 24;
+    }
+    // offset in a coarse layer of the value that the thread loads (boundary values count 0)
+    __device__ __forceinline__ uint32_t offset() const {
+        const int r = threadIdx.x, x = x0 + r % EX, y = y0 + r / EX;
+        return r < EN && x > 0 && x < nc && y > 0 && y < nc ? (uint32_t)(x + (nc + 1) * y) * (uint32_t)sizeof(T) : kOut;
+    }
+    // layer m's values of the thread (nothing is read unless `on`)
+    __device__ __forceinline__ void load(int m, uint32_t at, bool on, T (&v)[NC]) const {
+        // a coarse level (3 x 513^3 values at most) ends below 2^32 bytes
+        const uint32_t n1 = (uint32_t)__builtin_amdgcn_readfirstlane(nc) + 1, layer = n1 * n1 * (uint32_t)sizeof(T);
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+            v[c] = bload<T>(layer_of(reinterpret_cast<const char*>(e) + (c * n1 + (uint32_t)m) * layer, on && m > 0 && m < nc, layer), at);
+    }
+    __device__ __forceinline__ void store(Tile& es, int m, const T (&v)[NC]) const {
+        if ((int)threadIdx.x < EN)
+#pragma unroll
+            for (int c = 0; c < NC; ++c) es[m & 1][c][threadIdx.x] = v[c];
+    }
+    // the correction at the thread's fine node k (0: a, 1: b) of layer f
+    static __device__ __forceinline__ void value(const Tile& es, int f, int k, uint32_t slots, T (&out)[NC]) {
+        const int lo = (slots >> (16 * k)) & 255, hi = (slots >> (16 * k + 8)) & 255;
+#pragma unroll
+        for (int c = 0; c < NC; ++c) out[c] = T(0.5) * (es[(f >> 1) & 1][c][lo] + es[((f + 1) >> 1) & 1][c][hi]);
+    }
+};
+
 // Chunks of z layers: the count that minimises rounds x steps x time of a step.  A chunk of
 // zc layers marches zc + 4 steps; a step with k workgroups on a compute unit takes about
 // (3 + 4 k) / 7 of one with a single workgroup (129^3 FP32: 2.15 us for k = 1, 3.4 us for 2).

@@ -54,10 +54,11 @@ hipError_t launch_cube_dot(int ncomp, const LevelOp<double>& op, const double* u
 int cube_grid_blocks(int n);
 
 // Two products with the level operator in one pass (k_smooth2.hip).  pre: x1 = om0 D^-1 b, out = a1 x1 + o1 D^-1 (b - A x1), r = b - A out.
-// Otherwise: y = a1 x + o1 D^-1 (b - A x), out = a2 y + g2 x + o2 D^-1 (b - A y).
+// Otherwise, x + P e for x, e on the next coarser level: y = a1 x + o1 D^-1 (b - A x), out = a2 y + g2 x + o2 D^-1 (b - A y).
 template <typename T>
 struct Smooth2 {
     const T* x = nullptr;
+    const T* e = nullptr;
     const T* b = nullptr;
     T* out = nullptr;
     T* r = nullptr;

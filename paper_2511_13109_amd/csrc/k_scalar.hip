@@ -278,8 +278,11 @@ constexpr int TW = TX + 1, TE = (TX + 1) * (TY + 1);
 template <typename T, bool PRE>
 __global__ void __launch_bounds__(NTH)
 k_two7(const int n, const int zc, const int gx, const int gy, const int gz, const T* __restrict__ x,
-       const T* __restrict__ W, const T* __restrict__ b, const T* __restrict__ dinv, T* __restrict__ out,
-       T* __restrict__ rout, const T om0, const T a1, const T o1, const T a2, const T g2, const T o2) {
+       const T* __restrict__ ec, const T* __restrict__ W, const T* __restrict__ b, const T* __restrict__ dinv,
+       T* __restrict__ out, T* __restrict__ rout, const T om0, const T a1, const T o1, const T a2, const T g2,
+       const T o2) {
+    using Coarse = CoarseTile<1, T, TX, TY>;
+    __shared__ typename Coarse::Tile es;  // POST: the coarse correction
     __shared__ T xs[3][TE + 64];
     __shared__ T ys[2][NTH + TX + 2];
     __shared__ T fa[NTH], fb[NTH];
@@ -317,7 +320,19 @@ k_two7(const int n, const int zc, const int gx, const int gy, const int gz, cons
         t.v = bload<T>(layer_of((PRE ? b : x) + (int64_t)z * layer, zin, lbytes), off_xy);
         if constexpr (PRE) t.d = bload<T>(layer_of(dinv + (int64_t)z * layer, zin, lbytes), off_xy);
     };
-    auto stage = [&](int buf, int slot, const Node& t) { xs[buf][slot] = PRE ? om0 * t.d * t.v : t.v; };
+    Coarse coarse;
+    uint32_t slots = 0, at_e = 0;
+    if constexpr (!PRE) {
+        coarse.init(ec, n, X0 - 2, Y0 - 2);
+        slots = coarse.slots(cx, cy, has_b ? X0 - 2 + ex : cx, has_b ? Y0 - 2 + ey : cy);
+        at_e = coarse.offset();
+    }
+    // layer z of the staged vector: the thread's node k into `slot`
+    auto stage = [&](int z, int slot, const Node& t, int k) {
+        T pe[1];
+        if constexpr (!PRE) Coarse::value(es, z, k, slots, pe);
+        xs[(z + 6) % 3][slot] = PRE ? om0 * t.d * t.v : t.v + pe[0];
+    };
     struct Edges {
         T w[3];
     };
@@ -335,14 +350,30 @@ k_two7(const int n, const int zc, const int gx, const int gy, const int gz, cons
     };
     auto bidx = [](int l) { return (l + 6) % 3; };
     T ch[2] = {T(0), T(0)}, oh[2] = {T(0), T(0)};
+    Node t[2], e[2];  // node layers Z0-2 and Z0-1
 #pragma unroll
     for (int l = 0; l < 2; ++l) {
-        Node t, e;
-        load_node(Z0 - 2 + l, at, t);
-        load_node(Z0 - 2 + l, at_b, e);
-        stage(bidx(Z0 - 2 + l), sa, t);
-        stage(bidx(Z0 - 2 + l), sb, e);
-        if constexpr (PRE) ds[bidx(Z0 - 2 + l)][tid] = t.d;
+        load_node(Z0 - 2 + l, at, t[l]);
+        load_node(Z0 - 2 + l, at_b, e[l]);
+    }
+    T ev[1];  // POST: the coarse layer to be stored next
+    if constexpr (!PRE) {
+        // these layers need coarse layers m0 and m0+1, the loop's first also m0+2 (Z0 odd) or
+        // its next one (Z0 even)
+        const int m0 = (Z0 - 2) >> 1;
+        T v0[1], v1[1];
+        coarse.load(m0, at_e, true, v0);
+        coarse.load(m0 + 1, at_e, true, v1);
+        coarse.load(m0 + 2, at_e, true, ev);
+        coarse.store(es, m0, v0);
+        coarse.store(es, m0 + 1, v1);
+        __syncthreads();
+    }
+#pragma unroll
+    for (int l = 0; l < 2; ++l) {
+        stage(Z0 - 2 + l, sa, t[l], 0);
+        stage(Z0 - 2 + l, sb, e[l], 1);
+        if constexpr (PRE) ds[bidx(Z0 - 2 + l)][tid] = t[l].d;
     }
     Edges r0, r1, r2, r3;
     load_w(Z0 - 2, r2);
@@ -359,6 +390,11 @@ k_two7(const int n, const int zc, const int gx, const int gy, const int gz, cons
         if constexpr (!PRE) dv = bload<T>(layer_of(dinv + (int64_t)zq * layer, zin, lbytes), at_r);
     };
     load_rhs(Z0 - 2, bq, dq);
+    if constexpr (!PRE)
+        if (Z0 & 1) {
+            __syncthreads();
+            coarse.store(es, (Z0 + 1) >> 1, ev);
+        }
     __syncthreads();
     for (int z = Z0 - 2; z <= zend + 2; ++z) {
         T ownB, fyB, fzB, ownA, fyA, fzA;
@@ -366,7 +402,9 @@ k_two7(const int n, const int zc, const int gx, const int gy, const int gz, cons
             const int lo = z & 1, hi = lo ^ 1;  // layers z-2 and z-1
             node(ys[lo][tid], ys[lo][tid + 1], ys[lo][tid + TX], ys[hi][tid], r0, ownB, fyB, fzB);
         }
-        stage(bidx(z + 2), sb, ext);
+        if constexpr (!PRE)
+            if (!(z & 1)) coarse.store(es, (z >> 1) + 2, ev);
+        stage(z + 2, sb, ext, 1);
         load_w(z + 1, r3);
         fb[tid] = fyB;
         cb += ownB;
@@ -374,8 +412,9 @@ k_two7(const int n, const int zc, const int gx, const int gy, const int gz, cons
         const T self = xs[lo][sa];
         node(self, xs[lo][sa + 1], xs[lo][sa + TW], xs[hi][sa], r2, ownA, fyA, fzA);
         fa[tid] = fyA;
-        stage(bidx(z + 2), sa, own);
+        stage(z + 2, sa, own, 0);
         if constexpr (PRE) ds[bidx(z + 2)][tid] = own.d;
+        if constexpr (!PRE) coarse.load((z + 5) >> 1, at_e, z & 1, ev);
         load_node(z + 3, at_b, ext);
         load_node(z + 3, at, own);
         T bn, dn = T(0);
@@ -414,7 +453,7 @@ hipError_t launch_two(int n, const T* W, const T* dinv, const Smooth2<T>& a, hip
     const int gx = (n + OX) / OX, gy = (n + OY) / OY;
     const int gz = pick_chunks(n, (int64_t)gx * gy, fit.first, fit.second);
     hipLaunchKernelGGL((k_two7<T, PRE>), dim3((unsigned)(gx * gy * gz)), dim3(NTH), 0, st, n, (n + gz) / gz, gx, gy, gz,
-                       a.x, W, a.b, dinv, a.out, a.r, a.om0, PRE ? a.a1 + a.o1 / a.om0 : a.a1, a.o1, a.a2, a.g2, a.o2);
+                       a.x, a.e, W, a.b, dinv, a.out, a.r, a.om0, PRE ? a.a1 + a.o1 / a.om0 : a.a1, a.o1, a.a2, a.g2, a.o2);
     return hipGetLastError();
 }
 
@@ -460,7 +499,7 @@ int product7_blocks(int n) {
 
 template <typename T>
 hipError_t launch_two7(bool pre, int n, const T* W, const T* dinv, const Smooth2<T>& a, hipStream_t st) {
-    if (!W || !dinv || n < 2 || !a.b || !a.out || (pre ? !a.r : !a.x || a.x == a.out)) return hipErrorInvalidValue;
+    if (!W || !dinv || n < 2 || !a.b || !a.out || (pre ? !a.r : !a.x || !a.e || a.x == a.out)) return hipErrorInvalidValue;
     return pre ? launch_two<T, true>(n, W, dinv, a, st) : launch_two<T, false>(n, W, dinv, a, st);
 }
 

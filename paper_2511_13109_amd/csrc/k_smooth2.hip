@@ -28,7 +28,9 @@
 //
 // Measured (MI355X, Chebyshev V(2,2), V-cycle before -> after): vector 513^3 FP64 23.2 ->
 // 17.0 ms, FP32/BF16 11.5 -> 8.9 ms; 129^3 FP64 500 -> 416 us, FP32/BF16 269 -> 237 us;
-// scalar 257^3 FP64 1.61 -> 1.04 ms.  At 513^3 the two FP64 passes take 6.2 and 5.6 ms and
+// scalar 257^3 FP64 1.61 -> 1.04 ms.  Adding the coarse correction here instead of in a pass of
+// its own (x read and written once more): vector 129^3 FP64 394 -> 384 us, FP32/BF16 237 -> 231,
+// 513^3 15.3 -> 14.7 and 7.93 -> 7.84 ms, scalar 257^3 (k_scalar.hip) 803 -> 736 us.  At 513^3 the two FP64 passes take 6.2 and 5.6 ms and
 // request 82 and 72 KB per workgroup and step, 5.0-5.2 TB/s: the streaming rate of a copy.
 #include <hip/hip_runtime.h>
 
@@ -91,8 +93,8 @@ struct CellNu<uint16_t> {
 template <int NC, typename T, typename NT, bool PRE>
 __global__ void __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(Waves<NC, T>::value)))
 k_smooth2(const int n, const int zc, const int gx, const int gy, const int gz, const T* __restrict__ x,
-          const NT* __restrict__ nu, const T* __restrict__ b, const T* __restrict__ dinv, T* __restrict__ out,
-          T* __restrict__ rout, const T scale, const T om0, const T a1, const T o1, const T a2, const T g2,
+          const T* __restrict__ ec, const NT* __restrict__ nu, const T* __restrict__ b, const T* __restrict__ dinv,
+          T* __restrict__ out, T* __restrict__ rout, const T scale, const T om0, const T a1, const T o1, const T a2, const T g2,
           const T o2) {
     __shared__ T xs[3][NC][TE + 64];       // staged x layers (64 slots absorb idle second stores)
     __shared__ T ys[2][NC][NTH + TX + 2];  // the first product's result, one value per thread
@@ -100,6 +102,11 @@ k_smooth2(const int n, const int zc, const int gx, const int gy, const int gz, c
     __shared__ T fb[NC][2][NTH];           // second product
     // PRE: inverse diagonal of the own node, from its layer's load to its use two steps later
     __shared__ T ds[PRE ? 3 : 1][PRE ? NC : 1][PRE ? NTH : 1];
+    using Coarse = CoarseTile<NC, T, TX, TY>;
+    __shared__ typename Coarse::Tile es;  // POST: the coarse correction
+    // POST: constants of a thread that are read back when used (in registers they spill, and a
+    // reload from memory waits for every load in flight)
+    __shared__ u32x4 lc[PRE ? 1 : NTH];
     const int cols = gx * gy;
     const int lin = tile_lin(cols, gz);
     const int bz = lin / cols, bc = lin - bz * cols;
@@ -142,9 +149,19 @@ k_smooth2(const int n, const int zc, const int gx, const int gy, const int gz, c
             if constexpr (PRE) t.d[c] = bload<T>(layer_of(dinv + off + c * N, zin, lbytes), off_xy);
         }
     };
-    auto stage = [&](int buf, int slot, const Node& t) {
+    Coarse coarse;
+    if constexpr (!PRE) {
+        coarse.init(ec, n, X0 - 2, Y0 - 2);
+        lc[tid] = u32x4{at_b, (uint32_t)sb, coarse.slots(cx, cy, has_b ? X0 - 2 + ex : cx, has_b ? Y0 - 2 + ey : cy), coarse.offset()};
+    }
+    auto ext_offset = [&] { return PRE ? at_b : lc[PRE ? 0 : tid].x; };
+    auto ext_slot = [&] { return PRE ? sb : (int)lc[PRE ? 0 : tid].y; };
+    // layer z of the staged vector: the thread's node k into `slot`
+    auto stage = [&](int z, int slot, const Node& t, int k) {
+        T pe[NC];
+        if constexpr (!PRE) Coarse::value(es, z, k, lc[tid].z, pe);
 #pragma unroll
-        for (int c = 0; c < NC; ++c) xs[buf][c][slot] = PRE ? om0 * t.d[c] * t.v[c] : t.v[c];
+        for (int c = 0; c < NC; ++c) xs[(z + 6) % 3][c][slot] = PRE ? om0 * t.d[c] * t.v[c] : t.v[c] + pe[c];
     };
     auto load_nu = [&](int z, CellNu<NT>& r) {
         r.load(layer_of(nu + (int64_t)z * clayer * 6, z >= 0 && z < n && z <= zend + 1, cbytes), cat);
@@ -169,16 +186,32 @@ k_smooth2(const int n, const int zc, const int gx, const int gy, const int gz, c
     // POST: the terms of the second pass known after the first, layers z-2 and z-1:
     // out = ch - oh (A y), ch = a2 y + g2 x + o2 D^-1 b
     T ch[2][NC], oh[2][NC];
+    Node t[2], e[2];  // node layers Z0-2 and Z0-1
 #pragma unroll
     for (int l = 0; l < 2; ++l) {
-        Node t, e;
-        load_node(Z0 - 2 + l, at, t);
-        load_node(Z0 - 2 + l, at_b, e);
-        stage(bidx(Z0 - 2 + l), sa, t);
-        stage(bidx(Z0 - 2 + l), sb, e);
+        load_node(Z0 - 2 + l, at, t[l]);
+        load_node(Z0 - 2 + l, ext_offset(), e[l]);
+    }
+    T ev[NC];  // POST: the coarse layer to be stored next
+    if constexpr (!PRE) {
+        // these layers need coarse layers m0 and m0+1, the loop's first also m0+2 (Z0 odd) or
+        // its next one (Z0 even)
+        const int m0 = (Z0 - 2) >> 1;
+        T v0[NC], v1[NC];
+        coarse.load(m0, lc[tid].w, true, v0);
+        coarse.load(m0 + 1, lc[tid].w, true, v1);
+        coarse.load(m0 + 2, lc[tid].w, true, ev);
+        coarse.store(es, m0, v0);
+        coarse.store(es, m0 + 1, v1);
+        __syncthreads();
+    }
+#pragma unroll
+    for (int l = 0; l < 2; ++l) {
+        stage(Z0 - 2 + l, sa, t[l], 0);
+        stage(Z0 - 2 + l, ext_slot(), e[l], 1);
 #pragma unroll
         for (int c = 0; c < NC; ++c)
-            if constexpr (PRE) ds[bidx(Z0 - 2 + l)][c][tid] = t.d[c];
+            if constexpr (PRE) ds[bidx(Z0 - 2 + l)][c][tid] = t[l].d[c];
     }
     CellNu<NT> r0, r1, r2, r3;  // layers z-2, z-1, z, z+1
     load_nu(Z0 - 2, r2);
@@ -190,7 +223,7 @@ k_smooth2(const int n, const int zc, const int gx, const int gy, const int gz, c
         ch[0][c] = ch[1][c] = oh[0][c] = oh[1][c] = T(0);
     }
     Node own, ext;  // node layer z+2
-    load_node(Z0, at_b, ext);
+    load_node(Z0, ext_offset(), ext);
     load_node(Z0, at, own);
     T bq[NC], dq[NC];  // POST: right-hand side and inverse diagonal of layer z; PRE: right-hand side of z-2
     auto load_rhs = [&](int z, T (&bv)[NC], T (&dv)[NC]) {
@@ -204,6 +237,11 @@ k_smooth2(const int n, const int zc, const int gx, const int gy, const int gz, c
         }
     };
     load_rhs(Z0 - 2, bq, dq);
+    if constexpr (!PRE)
+        if (Z0 & 1) {
+            __syncthreads();
+            coarse.store(es, (Z0 + 1) >> 1, ev);
+        }
     __syncthreads();
 
     for (int z = Z0 - 2; z <= zend + 2; ++z) {
@@ -221,7 +259,9 @@ k_smooth2(const int n, const int zc, const int gx, const int gy, const int gz, c
                 }
             cell(U, r0, PB);
         }
-        stage(bidx(z + 2), sb, ext);
+        if constexpr (!PRE)
+            if (!(z & 1)) coarse.store(es, (z >> 1) + 2, ev);
+        stage(z + 2, ext_slot(), ext, 1);
         __builtin_amdgcn_sched_barrier(0);
         load_nu(z + 1, r3);
 #pragma unroll
@@ -250,12 +290,13 @@ k_smooth2(const int n, const int zc, const int gx, const int gy, const int gz, c
             fa[c][0][tid] = PA[1][0][c];
             fa[c][1][tid] = PA[1][1][c];
         }
-        stage(bidx(z + 2), sa, own);
+        stage(z + 2, sa, own, 0);
         if constexpr (PRE) {
 #pragma unroll
             for (int c = 0; c < NC; ++c) ds[bidx(z + 2)][c][tid] = own.d[c];
         }
-        load_node(z + 3, at_b, ext);
+        if constexpr (!PRE) coarse.load((z + 5) >> 1, lc[tid].w, z & 1, ev);
+        load_node(z + 3, ext_offset(), ext);
         load_node(z + 3, at, own);
         T bn[NC], dn[NC];
         load_rhs(z + 1, bn, dn);
@@ -304,7 +345,7 @@ hipError_t launch_t(const LevelOp<T>& op, const Smooth2<T>& a, hipStream_t st) {
     const int gx = (n + OX) / OX, gy = (n + OY) / OY;
     const int gz = pick_chunks(n, (int64_t)gx * gy, fit.first, fit.second);
     const int zc = (n + gz) / gz;
-    hipLaunchKernelGGL((k_smooth2<NC, T, NT, PRE>), dim3((unsigned)(gx * gy * gz)), dim3(NTH), 0, st, n, zc, gx, gy, gz, a.x, reinterpret_cast<const NT*>(op.nu), a.b, op.dinv, a.out, a.r, T(1.0 / (6.0 * n)), a.om0,
+    hipLaunchKernelGGL((k_smooth2<NC, T, NT, PRE>), dim3((unsigned)(gx * gy * gz)), dim3(NTH), 0, st, n, zc, gx, gy, gz, a.x, a.e, reinterpret_cast<const NT*>(op.nu), a.b, op.dinv, a.out, a.r, T(1.0 / (6.0 * n)), a.om0,
                        PRE ? a.a1 + a.o1 / a.om0 : a.a1, a.o1, a.a2, a.g2, a.o2);
     return hipGetLastError();
 }
@@ -323,7 +364,7 @@ hipError_t launch_nu(const LevelOp<T>& op, const Smooth2<T>& a, hipStream_t st) 
 
 template <typename T>
 hipError_t launch_smooth2(int ncomp, bool pre, const LevelOp<T>& op, const Smooth2<T>& a, hipStream_t st) {
-    if (!op.nu || !op.dinv || op.n < 2 || !a.b || !a.out || (pre ? !a.r : !a.x || a.x == a.out))
+    if (!op.nu || !op.dinv || op.n < 2 || !a.b || !a.out || (pre ? !a.r : !a.x || !a.e || a.x == a.out))
         return hipErrorInvalidValue;
     if (ncomp == 1) return pre ? launch_nu<1, T, true>(op, a, st) : launch_nu<1, T, false>(op, a, st);
     return pre ? launch_nu<3, T, true>(op, a, st) : launch_nu<3, T, false>(op, a, st);
