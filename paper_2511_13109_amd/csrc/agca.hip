@@ -65,12 +65,14 @@ struct agca_hier {
     hipStream_t st = nullptr;
     std::vector<Level> lv;
     double* ainv0 = nullptr;
-    double* partial = nullptr;
     int nb_partial = 1024;       // workgroups of the grid-stride reduction kernels
-    int partial_cap = 0;
+    double* partial = nullptr;   // partial sums: one per workgroup of a product or reduction
+    double* partial2 = nullptr;  // another 2 nb_partial, for sums that are read while partial is written
     double* red = nullptr;       // reduction results (device)
     int* counter = nullptr;      // invalid-coefficient counter (device)
     double* red_host = nullptr;  // pinned host mirror
+    double* red_map = nullptr;   // its device address
+    hipEvent_t fetched = nullptr;  // a mirror's values are there
     // FP64 solver vectors on the finest level
     double* s_r = nullptr;
     double* s_z = nullptr;
@@ -550,22 +552,37 @@ int32_t do_vcycle(agca_hier* h, const T* bL, T* xL) {
     return AGCA_OK;
 }
 
+// sum nb partials into red[slot] and bring red[first .. first + k) to the host (slot among
+// them); synchronises.  The summing kernel writes the host mirror itself: no copy after it.
+int32_t sum_fetch(agca_hier* h, const double* partial, int nb, int slot, int first, int k, double* out) {
+    HIPCHK(h, launch_sum_partials(partial, nb, h->red + slot, h->st, h->red + first, k, h->red_map + first));
+    HIPCHK(h, hipStreamSynchronize(h->st));
+    for (int i = 0; i < k; ++i) out[i] = h->red_host[first + i];
+    return AGCA_OK;
+}
+
 // x . y into reduction slot `slot` (device) and *out (host); synchronises
 template <typename T>
 int32_t do_dot(agca_hier* h, const T* x, const T* y, int64_t count, double* out, int slot = 0) {
     HIPCHK(h, launch_dot_partial<T>(x, y, count, h->partial, h->nb_partial, h->st));
-    HIPCHK(h, launch_sum_partials(h->partial, h->nb_partial, h->red + slot, h->st));
-    HIPCHK(h, hipMemcpyAsync(h->red_host + slot, h->red + slot, sizeof(double), hipMemcpyDeviceToHost,
-                             h->st));
-    HIPCHK(h, hipStreamSynchronize(h->st));
-    *out = h->red_host[slot];
-    return AGCA_OK;
+    return sum_fetch(h, h->partial, h->nb_partial, slot, slot, 1, out);
 }
 
 // sum nb partials into red[slot] (device)
 int32_t reduce_to(agca_hier* h, const double* partial, int nb, int slot) {
     HIPCHK(h, launch_sum_partials(partial, nb, h->red + slot, h->st));
     return AGCA_OK;
+}
+// the same as a scalar for the kernel that uses it: summed there (and kept in red[slot]) while
+// the partials are few enough for each of its workgroups to read
+constexpr int kScalarPartials = 4096;
+int32_t scalar_of(agca_hier* h, const double* partial, int nb, int slot, DevScalar* s) {
+    if (nb <= kScalarPartials) {
+        *s = DevScalar{partial, nb, h->red + slot};
+        return AGCA_OK;
+    }
+    *s = DevScalar{h->red + slot};
+    return reduce_to(h, partial, nb, slot);
 }
 // copy red[first .. first + k) to the host and wait
 int32_t fetch(agca_hier* h, int k, double* out, int first = 0) {
@@ -587,9 +604,8 @@ int32_t interior_norm(agca_hier* h, const double* b, double* out) {
     const int L = h->cfg.L;
     HIPCHK(h, launch_interior_dot<double>(h->cfg.ncomp, h->lv[L].n, b, b, h->partial, h->nb_partial,
                                           h->st));
-    TRY(reduce_to(h, h->partial, h->nb_partial, kSlotFloor));
     double v = 0.0;
-    TRY(fetch(h, 1, &v, kSlotFloor));
+    TRY(sum_fetch(h, h->partial, h->nb_partial, kSlotFloor, kSlotFloor, 1, &v));
     *out = std::sqrt(v);
     return AGCA_OK;
 }
@@ -607,9 +623,8 @@ int32_t floor_sums(agca_hier* h, const double* b, const double* x, double* s_sq,
     HIPCHK(h, launch_floor_terms(h->cfg.ncomp, lv.n, lv.nu64, 1.0 / (6.0 * lv.n), b, x, h->partial,
                                  h->nb_partial, h->st));
     TRY(reduce_to(h, h->partial, h->nb_partial, kSlotFloor));
-    TRY(reduce_to(h, h->partial + h->nb_partial, h->nb_partial, kSlotFloor + 1));
     double v[2] = {0.0, 0.0};
-    TRY(fetch(h, 2, v, kSlotFloor));
+    TRY(sum_fetch(h, h->partial + h->nb_partial, h->nb_partial, kSlotFloor + 1, kSlotFloor, 2, v));
     *s_sq = v[0];
     *b_sq = v[1];
     return AGCA_OK;
@@ -731,27 +746,25 @@ int32_t estimate_eigenvalues(agca_hier* h) {
         HIPCHK(h, launch_alternating(nc, lv.n, w, h->st));
         HIPCHK(h, launch_mul(cnt, lv.diag, w, y, h->st));
         HIPCHK(h, launch_dot_partial<double>(w, y, cnt, h->partial, h->nb_partial, h->st));
-        TRY(reduce_to(h, h->partial, h->nb_partial, 2 * K));
-        HIPCHK(h, launch_scale_rsqrt(cnt, w, h->red + 2 * K, v, h->st));
+        const int nb = h->nb_partial;
+        HIPCHK(h, launch_scale_rsqrt(cnt, w, DevScalar{h->partial, nb, h->red + 2 * K}, v, nb, h->st));
         const LevelOp<double> op = level_op<double>(h, l);
         for (int k = 0; k < K; ++k) {
+            int nbq = nb;
             if (op.sten) {
                 TRY(do_cube<double>(h, l, MODE_APPLY, v, nullptr, y, 0.0));
-                HIPCHK(h, launch_dot_partial<double>(v, y, cnt, h->partial, h->nb_partial, h->st));
-                TRY(reduce_to(h, h->partial, h->nb_partial, k));
+                HIPCHK(h, launch_dot_partial<double>(v, y, cnt, h->partial, nb, h->st));
             } else {
-                // element-loop level: y = A v with v . A v in the same pass
-                int nbq = 0;
+                // y = A v with v . A v in the same pass
                 TRY(do_product_dot(h, l, v, y, &nbq));
-                TRY(reduce_to(h, h->partial, nbq, k));
             }
-            HIPCHK(h, launch_lanczos_step(cnt, y, lv.diag, v, k > 0 ? vprev : nullptr, h->red + k,
-                                          k > 0 ? h->red + K + k - 1 : nullptr, w, h->partial,
-                                          h->nb_partial, h->st));
-            TRY(reduce_to(h, h->partial, h->nb_partial, K + k));
+            DevScalar alpha;
+            TRY(scalar_of(h, h->partial, nbq, k, &alpha));
+            HIPCHK(h, launch_lanczos_step(cnt, y, lv.diag, v, k > 0 ? vprev : nullptr, alpha,
+                                          DevScalar{k > 0 ? h->red + K + k - 1 : nullptr}, w, h->partial2, nb, h->st));
             // after a breakdown (beta_k = 0) the later steps compute non-finite values that
             // are never read: the host cuts the sequence at the breakdown
-            HIPCHK(h, launch_scale_rsqrt(cnt, w, h->red + K + k, vprev, h->st));
+            HIPCHK(h, launch_scale_rsqrt(cnt, w, DevScalar{h->partial2, nb, h->red + K + k}, vprev, nb, h->st));
             std::swap(v, vprev);
         }
         TRY(fetch(h, 2 * K + 1, co.data()));
@@ -1019,6 +1032,8 @@ void free_all(agca_hier* h) {
     h->allocs.clear();
     if (h->red_host) (void)hipHostFree(h->red_host);
     h->red_host = nullptr;
+    if (h->fetched) (void)hipEventDestroy(h->fetched);
+    h->fetched = nullptr;
 }
 
 int32_t free_blocks(agca_hier* h) {
@@ -1203,8 +1218,11 @@ int32_t agca_create(const agca_config* cfg, const double* nu_fine, const double*
     }
     if (rc == AGCA_OK) rc = alloc_t(h, &h->ainv0, 9);
     if (rc == AGCA_OK) {
-        h->partial_cap = std::max(2 * h->nb_partial, std::max(cube_grid_blocks(h->lv[L].n), product7_blocks(h->lv[L].n)));
-        rc = alloc_t(h, &h->partial, h->partial_cap);
+        // as many workgroups as the finest level's vectors fill, up to 1024
+        h->nb_partial = (int)std::min<int64_t>(1024, (nc * h->lv[L].nodes + 255) / 256);
+        const int cap = std::max(2 * h->nb_partial, std::max(cube_grid_blocks(h->lv[L].n), product7_blocks(h->lv[L].n)));
+        rc = alloc_t(h, &h->partial, cap + 2 * h->nb_partial);
+        if (rc == AGCA_OK) h->partial2 = h->partial + cap;
     }
     if (rc == AGCA_OK) rc = alloc_t(h, &h->red, AGCA_RED_SLOTS);
     if (rc == AGCA_OK) rc = alloc_t(h, &h->counter, 4);
@@ -1224,6 +1242,8 @@ int32_t agca_create(const agca_config* cfg, const double* nu_fine, const double*
     }
     if (rc == AGCA_OK) {
         hipError_t e = hipHostMalloc((void**)&h->red_host, AGCA_RED_SLOTS * sizeof(double));
+        if (e == hipSuccess) e = hipHostGetDevicePointer((void**)&h->red_map, h->red_host, 0);
+        if (e == hipSuccess) e = hipEventCreateWithFlags(&h->fetched, hipEventDisableTiming);
         if (e != hipSuccess) rc = fail(AGCA_E_OOM, "hipHostMalloc failed");
     }
     if (rc != AGCA_OK) return bail(rc);
@@ -1517,44 +1537,70 @@ int32_t agca_solve(agca_hier* h, const agca_solve_opts* o, const double* b, doub
             // also writes the V-cycle's FP32 input, and z stays in FP32: the dot products
             // and the direction update widen it on the fly.
             const bool mixed = mg32(h);
+            const int nb = h->nb_partial;
             float *r32 = h->s_r32, *z32 = h->s_z32;
             auto vcycle = [&]() -> int32_t {
                 return mixed ? do_vcycle<float>(h, r32, z32) : do_vcycle<double>(h, r, z);
             };
             auto dots = [&](const double* qq) -> hipError_t {
-                return mixed ? launch_dot2<float>(cnt, z32, r, qq, h->partial, h->nb_partial, h->st)
-                             : launch_dot2<double>(cnt, z, r, qq, h->partial, h->nb_partial, h->st);
+                return mixed ? launch_dot2<float>(cnt, z32, r, qq, h->partial2, nb, h->st)
+                             : launch_dot2<double>(cnt, z, r, qq, h->partial2, nb, h->st);
             };
             auto direction = [&](double beta) -> hipError_t {
                 return mixed ? launch_zpbp<float>(cnt, z32, beta, p, h->st)
                              : launch_zpbp<double>(cnt, z, beta, p, h->st);
             };
-            // The scalars stay in reduction slots on the device (alpha = rz / pq and beta are
-            // formed by the kernels that use them); the host reads p.q, r.r and z.r once per
-            // iteration for the stopping test and the breakdown checks.
-            auto direction_dev = [&](const double* num, const double* den, double sign) -> hipError_t {
-                return mixed ? launch_zpbp_dev<float>(cnt, z32, num, den, sign, p, h->st)
-                             : launch_zpbp_dev<double>(cnt, z, num, den, sign, p, h->st);
+            // The scalars stay on the device (alpha = rz / pq and beta are formed by the kernels
+            // that use them, from the partial sums); the host reads p.q, r.r and z.r once per
+            // iteration for the stopping test and the breakdown checks.  p.q sums into partial;
+            // z.r and z.q into the two halves of partial2, the second of which holds r.r between
+            // the update of r and the next z.
+            auto direction_dev = [&](DevScalar num, DevScalar den, double sign) -> hipError_t {
+                return mixed ? launch_zpbp_dev<float>(cnt, z32, num, den, sign, p, nb, h->st)
+                             : launch_zpbp_dev<double>(cnt, z, num, den, sign, p, nb, h->st);
             };
-            constexpr int PQ = 0, RR = 1, ZR = 2, ZQ = 3, RZ = 4;
+            constexpr int PQ = 0, RR = 1, RZ = 2;
             double* red = h->red;
-            double tmp[5];
+            double* partial_rr = h->partial2 + nb;
+            double tmp[3];
+            // Waits for the sums that the stream has been given to bring to the host.  ahead: the
+            // host expects to go on with this r, and the preconditioner is given to the stream
+            // before the wait, so the GPU does not idle over the host's look (about 20 us per
+            // iteration); a step that then changes r or stops leaves its result unused.
+            auto fetched = [&](bool ahead, bool* applied) -> int32_t {
+                *applied = ahead;
+                if (!ahead) {
+                    HIPCHK(h, hipStreamSynchronize(h->st));
+                    return AGCA_OK;
+                }
+                HIPCHK(h, hipEventRecord(h->fetched, h->st));
+                TRY(vcycle());
+                HIPCHK(h, dots(q));
+                HIPCHK(h, hipEventSynchronize(h->fetched));
+                return AGCA_OK;
+            };
+            double rel_prev = rel;
             double anchor = rel;  // true residual at the last replacement
             if (mixed) HIPCHK(h, launch_cast(AGCA_F64, AGCA_F32, r, r32, cnt, h->st));
             TRY(vcycle());
             HIPCHK(h, dots(nullptr));
-            TRY(reduce_to(h, h->partial, h->nb_partial, RZ));
             HIPCHK(h, direction(0.0));
             while (it < o->max_iter) {
                 // q = A p fused with p . q
                 int nbq = 0;
                 TRY(do_product_dot(h, L, p, q, &nbq));
-                TRY(reduce_to(h, h->partial, nbq, PQ));
+                DevScalar pq;
+                TRY(scalar_of(h, h->partial, nbq, PQ, &pq));
                 // x += alpha p, r -= alpha q (and its FP32 copy), fused with r . r
-                HIPCHK(h, launch_cg_update(cnt, red + RZ, red + PQ, p, q, x, r, mixed ? r32 : nullptr,
-                                           h->partial, h->nb_partial, h->st));
-                TRY(reduce_to(h, h->partial, h->nb_partial, RR));
-                TRY(fetch(h, 5, tmp));
+                HIPCHK(h, launch_cg_update(cnt, DevScalar{h->partial2, nb, red + RZ}, pq, p, q, x, r,
+                                           mixed ? r32 : nullptr, partial_rr, nb, h->st));
+                HIPCHK(h, launch_sum_partials(partial_rr, nb, red + RR, h->st, red, 3, h->red_map));
+                // no replacement and no stop while r.r falls at most twice as fast as before
+                const double expect = it > 0 ? rel * std::min(1.0, 0.5 * rel / rel_prev) : 0.0;
+                bool applied = false;
+                TRY(fetched(expect > o->tol && expect > kReplaceEvery * anchor && !milestone_due(expect) &&
+                            it + 1 < o->max_iter, &applied));
+                for (int i = 0; i < 3; ++i) tmp[i] = h->red_host[i];
                 if (!(tmp[RZ] > 0.0) || !std::isfinite(tmp[RZ])) {
                     status = fail(AGCA_E_NUMERIC, "preconditioned residual is not positive");
                     break;
@@ -1565,6 +1611,7 @@ int32_t agca_solve(agca_hier* h, const agca_solve_opts* o, const double* b, doub
                 }
                 rr = tmp[RR];
                 ++it;
+                rel_prev = rel;
                 rel = rec_rel = std::sqrt(rr) / bn;
                 record(rel);
                 if (!std::isfinite(rel) || rel > 1e30) {
@@ -1576,8 +1623,13 @@ int32_t agca_solve(agca_hier* h, const agca_solve_opts* o, const double* b, doub
                     // residual replacement: r = b - A x (and its FP32 copy); r . r goes to a
                     // slot of its own (FCG's next beta still reads p . q from slot PQ)
                     TRY(do_cube<double>(h, L, MODE_RESIDUAL, x, b, r, 0.0));
-                    TRY(do_dot<double>(h, r, r, cnt, &rr, kSlotReplace));
-                    if (mixed) HIPCHK(h, launch_cast(AGCA_F64, AGCA_F32, r, r32, cnt, h->st));
+                    HIPCHK(h, mixed ? launch_norm_cast(cnt, r, r32, h->partial, nb, h->st)
+                                    : launch_dot_partial<double>(r, r, cnt, h->partial, nb, h->st));
+                    HIPCHK(h, launch_sum_partials(h->partial, nb, red + kSlotReplace, h->st, red + kSlotReplace, 1,
+                                                  h->red_map + kSlotReplace));
+                    // the true residual of a recurrence above tol is hardly below it
+                    TRY(fetched(rel > o->tol && it < o->max_iter, &applied));
+                    rr = h->red_host[kSlotReplace];
                     const double rel_true = std::sqrt(rr) / bn;
                     ++replacements;
                     anchor = rel_true;
@@ -1598,7 +1650,6 @@ int32_t agca_solve(agca_hier* h, const agca_solve_opts* o, const double* b, doub
                     }
                     rel = rec_rel = rel_true;
                 }
-                TRY(vcycle());
                 // The new direction is A-orthogonalised against the previous one, beta =
                 // -z.q / p.q, in both solvers: for PCG (fixed SPD preconditioner) that equals
                 // z.r / rz_old in exact arithmetic, but the latter takes r orthogonal to the
@@ -1606,12 +1657,12 @@ int32_t agca_solve(agca_hier* h, const agca_solve_opts* o, const double* b, doub
                 // not; with it PCG stalled above the floor (513^3 sinkers: 1.3e-6 against a
                 // floor of 7.3e-7, where the A-orthogonal form reaches 1.9e-7)
                 // z . r and z . q in one pass
-                HIPCHK(h, dots(q));
-                TRY(reduce_to(h, h->partial, h->nb_partial, ZR));
-                TRY(reduce_to(h, h->partial + h->nb_partial, h->nb_partial, ZQ));
+                if (!applied) {
+                    TRY(vcycle());
+                    HIPCHK(h, dots(q));
+                }
                 // beta = -alpha z.q / rz_old = -z.q / p.q
-                HIPCHK(h, direction_dev(red + ZQ, red + PQ, -1.0));
-                HIPCHK(h, hipMemcpyAsync(red + RZ, red + ZR, sizeof(double), hipMemcpyDeviceToDevice, h->st));
+                HIPCHK(h, direction_dev(DevScalar{h->partial2 + nb, nb}, DevScalar{red + PQ}, -1.0));
             }
         } else {
             // iterative refinement / stationary: x += B r, r = b - A x (the residual is exact)
@@ -1972,28 +2023,24 @@ static int32_t z_solve_mg(agca_hier* h, const Bfbt& w, const double* r, double* 
     HIPCHK(h, launch_fill<double>(np, 0.0, y, h->st));
     HIPCHK(h, launch_axpby<double>(np, 1.0, r, 0.0, w.zr, h->st));
     TRY(zmg_cycle(h, z, coarse, h->cfg.L - 1, w.zr, w.zz));
-    HIPCHK(h, launch_dot2<double>(np, w.zz, w.zr, nullptr, h->partial, nb, h->st));
-    HIPCHK(h, launch_sum_partials(h->partial, nb, w.zred, h->st));
+    HIPCHK(h, launch_dot2<double>(np, w.zz, w.zr, nullptr, h->partial2, nb, h->st));
     HIPCHK(h, launch_axpby<double>(np, 1.0, w.zz, 0.0, w.zp, h->st));
-    int cur = 0;
     for (int k = 0; k < iters; ++k) {
         HIPCHK(h, launch_zstencil(0, T.n, T.S, w.zp, nullptr, 0.0, w.zq, h->st));
         HIPCHK(h, launch_dot2<double>(np, w.zp, w.zq, nullptr, h->partial, nb, h->st));
-        HIPCHK(h, launch_sum_partials(h->partial, nb, w.zred + 2, h->st));
-        HIPCHK(h, launch_cg_update(np, w.zred + cur, w.zred + 2, w.zp, w.zq, y, w.zr, nullptr,
-                                   h->partial, nb, h->st));
+        HIPCHK(h, launch_cg_update(np, DevScalar{h->partial2, nb, w.zred}, DevScalar{h->partial, nb}, w.zp, w.zq, y,
+                                   w.zr, nullptr, h->partial2 + nb, nb, h->st));
         if (k == iters - 1) break;
         TRY(zmg_cycle(h, z, coarse, h->cfg.L - 1, w.zr, w.zz));
-        HIPCHK(h, launch_dot2<double>(np, w.zz, w.zr, nullptr, h->partial, nb, h->st));
-        HIPCHK(h, launch_sum_partials(h->partial, nb, w.zred + (1 - cur), h->st));
-        HIPCHK(h, launch_zpbp_dev<double>(np, w.zz, w.zred + (1 - cur), w.zred + cur, 1.0, w.zp, h->st));
-        cur = 1 - cur;
+        HIPCHK(h, launch_dot2<double>(np, w.zz, w.zr, nullptr, h->partial2, nb, h->st));
+        HIPCHK(h, launch_zpbp_dev<double>(np, w.zz, DevScalar{h->partial2, nb}, DevScalar{w.zred}, 1.0, w.zp, nb, h->st));
     }
     return AGCA_OK;
 }
 
 // y = iters steps of Jacobi-preconditioned CG on Z y = r from y = 0.  The scalars stay
-// on the device: r.z alternates between zred[0] and zred[1], p.q is zred[2]; a step of
+// on the device: r.z sums into partial2 and the update keeps it in zred[0] for the next beta,
+// p.q sums into partial; a step of
 // zero Z-energy (r = 0) has step size zero (the update kernels' guards).
 static int32_t z_solve(agca_hier* h, const Bfbt& w, const double* r, double* y, int iters) {
     const int64_t np = stokes_dims(h).np;
@@ -2001,22 +2048,17 @@ static int32_t z_solve(agca_hier* h, const Bfbt& w, const double* r, double* y, 
     HIPCHK(h, launch_fill<double>(np, 0.0, y, h->st));
     HIPCHK(h, launch_axpby<double>(np, 1.0, r, 0.0, w.zr, h->st));
     HIPCHK(h, launch_div_elementwise(np, w.zr, w.zdiag, w.zz, h->st));
-    HIPCHK(h, launch_dot2<double>(np, w.zz, w.zr, nullptr, h->partial, nb, h->st));
-    HIPCHK(h, launch_sum_partials(h->partial, nb, w.zred, h->st));
+    HIPCHK(h, launch_dot2<double>(np, w.zz, w.zr, nullptr, h->partial2, nb, h->st));
     HIPCHK(h, launch_axpby<double>(np, 1.0, w.zz, 0.0, w.zp, h->st));
-    int cur = 0;
     for (int k = 0; k < iters; ++k) {
         TRY(z_apply(h, w, w.zp, w.zq));
         HIPCHK(h, launch_dot2<double>(np, w.zp, w.zq, nullptr, h->partial, nb, h->st));
-        HIPCHK(h, launch_sum_partials(h->partial, nb, w.zred + 2, h->st));
-        HIPCHK(h, launch_cg_update(np, w.zred + cur, w.zred + 2, w.zp, w.zq, y, w.zr, nullptr,
-                                   h->partial, nb, h->st));
+        HIPCHK(h, launch_cg_update(np, DevScalar{h->partial2, nb, w.zred}, DevScalar{h->partial, nb}, w.zp, w.zq, y,
+                                   w.zr, nullptr, h->partial2 + nb, nb, h->st));
         if (k == iters - 1) break;
         HIPCHK(h, launch_div_elementwise(np, w.zr, w.zdiag, w.zz, h->st));
-        HIPCHK(h, launch_dot2<double>(np, w.zz, w.zr, nullptr, h->partial, nb, h->st));
-        HIPCHK(h, launch_sum_partials(h->partial, nb, w.zred + (1 - cur), h->st));
-        HIPCHK(h, launch_zpbp_dev<double>(np, w.zz, w.zred + (1 - cur), w.zred + cur, 1.0, w.zp, h->st));
-        cur = 1 - cur;
+        HIPCHK(h, launch_dot2<double>(np, w.zz, w.zr, nullptr, h->partial2, nb, h->st));
+        HIPCHK(h, launch_zpbp_dev<double>(np, w.zz, DevScalar{h->partial2, nb}, DevScalar{w.zred}, 1.0, w.zp, nb, h->st));
     }
     return AGCA_OK;
 }

@@ -131,18 +131,30 @@ hipError_t launch_coarse_cycle(int ncomp, int K, const CoarseCycle<T>& a, hipStr
 template <typename T>
 hipError_t launch_dot_partial(const T* x, const T* y, int64_t n, double* partial, int nblocks,
                               hipStream_t st);
-hipError_t launch_sum_partials(const double* partial, int nblocks, double* out, hipStream_t st);
+// out = sum of the partials; with host: host[0 .. k) = first[0 .. k), the result included
+// (host: device address of pinned memory, out within [first, first + k))
+hipError_t launch_sum_partials(const double* partial, int nblocks, double* out, hipStream_t st, const double* first = nullptr,
+                               int k = 0, double* host = nullptr);
+// A scalar that a kernel reads on the device: p[0] (n = 0), or the sum of the n partials at p,
+// formed by each workgroup in the order of launch_sum_partials and kept in *keep
+struct DevScalar {
+    const double* p = nullptr;
+    int n = 0;
+    double* keep = nullptr;
+};
 template <typename T>
 hipError_t launch_axpby(int64_t n, double a, const T* x, double b, T* y, hipStream_t st);  // y = a x + b y
-// CG update: x += alpha p, r -= alpha q with alpha = rz[0] / pq[0] on the device (and r32 =
+// CG update: x += alpha p, r -= alpha q with alpha = rz / pq on the device (and r32 =
 // FP32 copy of the new r if r32 != null), and partial sums of r . r over nblocks workgroups
-hipError_t launch_cg_update(int64_t n, const double* rz, const double* pq, const double* p,
+hipError_t launch_cg_update(int64_t n, DevScalar rz, DevScalar pq, const double* p,
                             const double* q, double* x, double* r, float* r32, double* partial,
                             int nblocks, hipStream_t st);
-// p = z + beta p with beta = sign num[0] / den[0] on the device
+// partial sums of r . r, r32 = FP32 copy of r
+hipError_t launch_norm_cast(int64_t n, const double* r, float* r32, double* partial, int nblocks, hipStream_t st);
+// p = z + beta p with beta = sign num / den on the device
 template <typename Z>
-hipError_t launch_zpbp_dev(int64_t n, const Z* z, const double* num, const double* den, double sign,
-                           double* p, hipStream_t st);
+hipError_t launch_zpbp_dev(int64_t n, const Z* z, DevScalar num, DevScalar den, double sign, double* p, int nblocks,
+                           hipStream_t st);
 // partial sums of z . r and z . q (two arrays of nblocks; the second only if q != null)
 template <typename Z>
 hipError_t launch_dot2(int64_t n, const Z* z, const double* r, const double* q, double* partial,
@@ -151,13 +163,13 @@ hipError_t launch_dot2(int64_t n, const Z* z, const double* r, const double* q, 
 template <typename Z>
 hipError_t launch_zpbp(int64_t n, const Z* z, double beta, double* p, hipStream_t st);
 hipError_t launch_cast(int from, int to, const void* src, void* dst, int64_t n, hipStream_t st);
-// Lanczos step with device coefficients: w = y / d - alpha[0] v - sqrt(beta2[0]) u (no u
+// Lanczos step with device coefficients: w = y / d - alpha v - sqrt(beta2) u (no u
 // term when u is null), partial sums of w . (d w) over nblocks workgroups
 hipError_t launch_lanczos_step(int64_t n, const double* y, const double* d, const double* v,
-                               const double* u, const double* alpha, const double* beta2, double* w,
+                               const double* u, DevScalar alpha, DevScalar beta2, double* w,
                                double* partial, int nblocks, hipStream_t st);
-// out = x / sqrt(s[0]) (s on the device)
-hipError_t launch_scale_rsqrt(int64_t n, const double* x, const double* s, double* out, hipStream_t st);
+// out = x / sqrt(s) (s on the device)
+hipError_t launch_scale_rsqrt(int64_t n, const double* x, DevScalar s, double* out, int nblocks, hipStream_t st);
 template <typename T>
 hipError_t launch_zero_boundary(int ncomp, int n, T* x, hipStream_t st);
 template <typename T>

@@ -60,15 +60,36 @@ __device__ __forceinline__ double wave_sum(double v) {
     return v;
 }
 
+// Grid-stride loop with the loads of four steps in flight: with one, a reduction's 4
+// wavefronts per SIMD leave the memory idle (z.r and z.q at 129^3 vector FP64: 4.1 TB/s).
+// load(i) returns the values of element i, use(...) takes them in order of i.
+template <typename Load, typename Use>
+__device__ __forceinline__ void strided4(int64_t n, const Load& load, const Use& use) {
+    const int64_t stride = (int64_t)gridDim.x * NT;
+    int64_t i = blockIdx.x * (int64_t)NT + threadIdx.x;
+    for (; i + 3 * stride < n; i += 4 * stride) {
+        const auto v0 = load(i), v1 = load(i + stride), v2 = load(i + 2 * stride), v3 = load(i + 3 * stride);
+        use(v0);
+        use(v1);
+        use(v2);
+        use(v3);
+    }
+    for (; i < n; i += stride) use(load(i));
+}
+template <typename A, typename B>
+struct Pair {
+    A a;
+    B b;
+};
+
 template <typename T>
 __global__ void __launch_bounds__(NT)
 k_dot_partial(const T* __restrict__ x, const T* __restrict__ y, int64_t n,
               double* __restrict__ partial) {
     __shared__ double red[NT / 64];
     double acc = 0.0;
-    const int64_t stride = (int64_t)gridDim.x * NT;
-    for (int64_t i = blockIdx.x * (int64_t)NT + threadIdx.x; i < n; i += stride)
-        acc += (double)x[i] * (double)y[i];
+    strided4(n, [&](int64_t i) { return Pair<T, T>{x[i], y[i]}; },
+             [&](const Pair<T, T>& v) { acc += (double)v.a * (double)v.b; });
     acc = wave_sum(acc);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
     __syncthreads();
@@ -79,19 +100,39 @@ k_dot_partial(const T* __restrict__ x, const T* __restrict__ y, int64_t n,
     }
 }
 
-__global__ void __launch_bounds__(NT)
-k_sum_partials(const double* __restrict__ partial, int nb, double* __restrict__ out) {
+// the workgroup's sum of nb partials, in a fixed order, in every thread
+__device__ __forceinline__ double total(const double* __restrict__ partial, int nb) {
     __shared__ double red[NT / 64];
     double acc = 0.0;
     for (int i = threadIdx.x; i < nb; i += NT) acc += partial[i];
     acc = wave_sum(acc);
+    __syncthreads();  // an earlier sum has been read
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        double s = 0.0;
-        for (int w = 0; w < NT / 64; ++w) s += red[w];
-        *out = s;
-    }
+    double s = 0.0;
+#pragma unroll
+    for (int w = 0; w < NT / 64; ++w) s += red[w];
+    return s;
+}
+
+// The kernel that uses a reduction's result sums the partials itself, in each of its
+// workgroups: they are in L2 (8 KB per 1024), while a launch of its own for the sum costs 4-5 us
+// of start and drain, four times per solver iteration.  Solve at 129^3 vector, BF16 V-cycle, 30
+// iterations: 15.49 -> 14.95 ms with the sums here and four loads in flight in the dot products,
+// 14.6 with the preconditioner started before the host's look at r.r (agca_solve); FP64, 25
+// iterations: 16.56 -> 15.95 -> 15.8 ms.
+__device__ __forceinline__ double dev_scalar(const DevScalar& s) {
+    if (s.n == 0) return s.p[0];
+    const double v = total(s.p, s.n);
+    if (s.keep && blockIdx.x == 0 && threadIdx.x == 0) *s.keep = v;
+    return v;
+}
+
+__global__ void __launch_bounds__(NT)
+k_sum_partials(const double* __restrict__ partial, int nb, double* out, const double* first, int k, double* host) {
+    const double s = total(partial, nb);
+    if (threadIdx.x == 0) *out = s;
+    for (int i = threadIdx.x; i < k; i += NT) host[i] = first + i == out ? s : first[i];
 }
 
 template <typename T>
@@ -121,15 +162,16 @@ __device__ __forceinline__ void block_sum_store(double v, double* __restrict__ o
     __syncthreads();
 }
 
-// x += alpha p, r -= alpha q with alpha = rz / pq read from the device, and r . r; with
+// x += alpha p, r -= alpha q with alpha = rz / pq from the device, and r . r; with
 // r32 the new residual is also stored in FP32 (the input of the FP32 V-cycle)
 __global__ void __launch_bounds__(NT)
-k_cg_update(int64_t n, const double* __restrict__ rz, const double* __restrict__ pq,
+k_cg_update(int64_t n, const DevScalar rz, const DevScalar pq,
             const double* __restrict__ p, const double* __restrict__ q,
             double* __restrict__ x, double* __restrict__ r, float* __restrict__ r32,
             double* __restrict__ partial) {
     // a direction of zero energy (p = 0) takes no step; the caller tests p . q
-    const double alpha = pq[0] != 0.0 ? rz[0] / pq[0] : 0.0;
+    const double num = dev_scalar(rz), den = dev_scalar(pq);
+    const double alpha = den != 0.0 ? num / den : 0.0;
     double acc = 0.0;
     const int64_t stride = (int64_t)gridDim.x * NT;
     for (int64_t i = blockIdx.x * (int64_t)NT + threadIdx.x; i < n; i += stride) {
@@ -148,22 +190,39 @@ __global__ void __launch_bounds__(NT)
 k_dot2(int64_t n, const Z* __restrict__ z, const double* __restrict__ r,
        const double* __restrict__ q, double* __restrict__ partial) {
     double a = 0.0, b = 0.0;
-    const int64_t stride = (int64_t)gridDim.x * NT;
-    for (int64_t i = blockIdx.x * (int64_t)NT + threadIdx.x; i < n; i += stride) {
-        const double zi = (double)z[i];
-        a += zi * r[i];
-        if (q) b += zi * q[i];
-    }
+    struct V {
+        Z z;
+        double r, q;
+    };
+    strided4(n, [&](int64_t i) { return V{z[i], r[i], q ? q[i] : 0.0}; },
+             [&](const V& v) {
+                 a += (double)v.z * v.r;
+                 b += (double)v.z * v.q;
+             });
     block_sum_store(a, partial + blockIdx.x);
-    block_sum_store(b, partial + gridDim.x + blockIdx.x);
+    if (q) block_sum_store(b, partial + gridDim.x + blockIdx.x);
 }
 
-// p = z + beta p with beta = sign num[0] / den[0] read from the device
+// partial sums of r . r, and the FP32 copy of r (the replaced residual of a mixed solve)
+__global__ void __launch_bounds__(NT)
+k_norm_cast(int64_t n, const double* __restrict__ r, float* __restrict__ r32, double* __restrict__ partial) {
+    double acc = 0.0;
+    const int64_t stride = (int64_t)gridDim.x * NT;
+    for (int64_t i = blockIdx.x * (int64_t)NT + threadIdx.x; i < n; i += stride) {
+        const double v = r[i];
+        r32[i] = (float)v;
+        acc += v * v;
+    }
+    block_sum_store(acc, partial + blockIdx.x);
+}
+
+// p = z + beta p with beta = sign num / den from the device
 template <typename Z>
 __global__ void __launch_bounds__(NT)
-k_zpbp_dev(int64_t n, const Z* __restrict__ z, const double* __restrict__ num,
-           const double* __restrict__ den, double sign, double* __restrict__ p) {
-    const double beta = den[0] != 0.0 ? sign * num[0] / den[0] : 0.0;
+k_zpbp_dev(int64_t n, const Z* __restrict__ z, const DevScalar num, const DevScalar den, double sign,
+           double* __restrict__ p) {
+    const double a = dev_scalar(num), d = dev_scalar(den);
+    const double beta = d != 0.0 ? sign * a / d : 0.0;
     const int64_t stride = (int64_t)gridDim.x * NT;
     for (int64_t i = blockIdx.x * (int64_t)NT + threadIdx.x; i < n; i += stride)
         p[i] = (double)z[i] + beta * p[i];
@@ -183,15 +242,15 @@ k_zpbp(int64_t n, const Z* __restrict__ z, double beta, double* __restrict__ p) 
 }
 
 // One Lanczos step for the pencil (A, D) with the coefficients on the device:
-// w = y / d - alpha v - beta u (0 where d = 0; beta = sqrt(beta2[0]), no u term when u is
+// w = y / d - alpha v - beta u (0 where d = 0; beta = sqrt(beta2), no u term when u is
 // null), and the partial sums of w . (d w).
 __global__ void __launch_bounds__(NT)
 k_lanczos_step(int64_t n, const double* __restrict__ y, const double* __restrict__ d,
                const double* __restrict__ v, const double* __restrict__ u,
-               const double* __restrict__ alpha, const double* __restrict__ beta2,
+               const DevScalar alpha, const DevScalar beta2,
                double* __restrict__ w, double* __restrict__ partial) {
-    const double a = alpha[0];
-    const double b = u ? sqrt(fmax(beta2[0], 0.0)) : 0.0;
+    const double a = dev_scalar(alpha);
+    const double b = u ? sqrt(fmax(dev_scalar(beta2), 0.0)) : 0.0;
     double acc = 0.0;
     const int64_t stride = (int64_t)gridDim.x * NT;
     for (int64_t i = blockIdx.x * (int64_t)NT + threadIdx.x; i < n; i += stride) {
@@ -205,11 +264,10 @@ k_lanczos_step(int64_t n, const double* __restrict__ y, const double* __restrict
     block_sum_store(acc, partial + blockIdx.x);
 }
 
-// out = x / sqrt(s[0])
+// out = x / sqrt(s)
 __global__ void __launch_bounds__(NT)
-k_scale_rsqrt(int64_t n, const double* __restrict__ x, const double* __restrict__ s,
-              double* __restrict__ out) {
-    const double r = sqrt(s[0]);
+k_scale_rsqrt(int64_t n, const double* __restrict__ x, const DevScalar s, double* __restrict__ out) {
+    const double r = sqrt(dev_scalar(s));
     const int64_t stride = (int64_t)gridDim.x * NT;
     for (int64_t i = blockIdx.x * (int64_t)NT + threadIdx.x; i < n; i += stride) out[i] = x[i] / r;
 }
@@ -524,8 +582,9 @@ hipError_t launch_dot_partial(const T* x, const T* y, int64_t n, double* partial
     hipLaunchKernelGGL(k_dot_partial<T>, dim3(nblocks), dim3(NT), 0, st, x, y, n, partial);
     return hipGetLastError();
 }
-hipError_t launch_sum_partials(const double* partial, int nblocks, double* out, hipStream_t st) {
-    hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(NT), 0, st, partial, nblocks, out);
+hipError_t launch_sum_partials(const double* partial, int nblocks, double* out, hipStream_t st, const double* first,
+                               int k, double* host) {
+    hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(NT), 0, st, partial, nblocks, out, first, host ? k : 0, host);
     return hipGetLastError();
 }
 template <typename T>
@@ -535,25 +594,28 @@ hipError_t launch_axpby(int64_t n, double a, const T* x, double b, T* y, hipStre
     hipLaunchKernelGGL(k_axpby<T>, dim3(grid_stride(n)), dim3(NT), 0, st, n, a, x, b, y);
     return hipGetLastError();
 }
-hipError_t launch_cg_update(int64_t n, const double* rz, const double* pq, const double* p,
+hipError_t launch_cg_update(int64_t n, DevScalar rz, DevScalar pq, const double* p,
                             const double* q, double* x, double* r, float* r32, double* partial,
                             int nblocks, hipStream_t st) {
-    if (!rz || !pq || !p || !q || !x || !r || !partial || nblocks <= 0) return hipErrorInvalidValue;
+    if (!rz.p || !pq.p || !p || !q || !x || !r || !partial || nblocks <= 0) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_cg_update, dim3(nblocks), dim3(NT), 0, st, n, rz, pq, p, q, x, r, r32, partial);
     return hipGetLastError();
 }
-template <typename Z>
-hipError_t launch_zpbp_dev(int64_t n, const Z* z, const double* num, const double* den, double sign,
-                           double* p, hipStream_t st) {
-    if (n <= 0) return hipSuccess;
-    if (!z || !num || !den || !p) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_zpbp_dev<Z>, dim3(grid_stride(n)), dim3(NT), 0, st, n, z, num, den, sign, p);
+hipError_t launch_norm_cast(int64_t n, const double* r, float* r32, double* partial, int nblocks, hipStream_t st) {
+    if (!r || !r32 || !partial || nblocks <= 0) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_norm_cast, dim3(nblocks), dim3(NT), 0, st, n, r, r32, partial);
     return hipGetLastError();
 }
-template hipError_t launch_zpbp_dev<double>(int64_t, const double*, const double*, const double*, double,
-                                            double*, hipStream_t);
-template hipError_t launch_zpbp_dev<float>(int64_t, const float*, const double*, const double*, double,
-                                           double*, hipStream_t);
+template <typename Z>
+hipError_t launch_zpbp_dev(int64_t n, const Z* z, DevScalar num, DevScalar den, double sign, double* p, int nblocks,
+                           hipStream_t st) {
+    if (n <= 0) return hipSuccess;
+    if (!z || !num.p || !den.p || !p || nblocks <= 0) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_zpbp_dev<Z>, dim3(nblocks), dim3(NT), 0, st, n, z, num, den, sign, p);
+    return hipGetLastError();
+}
+template hipError_t launch_zpbp_dev<double>(int64_t, const double*, DevScalar, DevScalar, double, double*, int, hipStream_t);
+template hipError_t launch_zpbp_dev<float>(int64_t, const float*, DevScalar, DevScalar, double, double*, int, hipStream_t);
 template <typename Z>
 hipError_t launch_dot2(int64_t n, const Z* z, const double* r, const double* q, double* partial,
                        int nblocks, hipStream_t st) {
@@ -575,17 +637,17 @@ hipError_t launch_zpbp(int64_t n, const Z* z, double beta, double* p, hipStream_
 template hipError_t launch_zpbp<double>(int64_t, const double*, double, double*, hipStream_t);
 template hipError_t launch_zpbp<float>(int64_t, const float*, double, double*, hipStream_t);
 hipError_t launch_lanczos_step(int64_t n, const double* y, const double* d, const double* v,
-                               const double* u, const double* alpha, const double* beta2, double* w,
+                               const double* u, DevScalar alpha, DevScalar beta2, double* w,
                                double* partial, int nblocks, hipStream_t st) {
-    if (!y || !d || !v || !alpha || (u && !beta2) || !w || !partial || nblocks <= 0)
+    if (!y || !d || !v || !alpha.p || (u && !beta2.p) || !w || !partial || nblocks <= 0)
         return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_lanczos_step, dim3(nblocks), dim3(NT), 0, st, n, y, d, v, u, alpha, beta2, w,
                        partial);
     return hipGetLastError();
 }
-hipError_t launch_scale_rsqrt(int64_t n, const double* x, const double* s, double* out, hipStream_t st) {
-    if (!x || !s || !out) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_scale_rsqrt, dim3(grid_stride(n)), dim3(NT), 0, st, n, x, s, out);
+hipError_t launch_scale_rsqrt(int64_t n, const double* x, DevScalar s, double* out, int nblocks, hipStream_t st) {
+    if (!x || !s.p || !out || nblocks <= 0) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_scale_rsqrt, dim3(nblocks), dim3(NT), 0, st, n, x, s, out);
     return hipGetLastError();
 }
 hipError_t launch_cast(int from, int to, const void* src, void* dst, int64_t n, hipStream_t st) {
