@@ -87,7 +87,6 @@ struct agca_hier {
     int64_t blocks_version = -1; // nu_version the stored Galerkin blocks were formed for
     int64_t mass_version = -1;   // nu_version the pressure mass was formed for
     double* st_mass = nullptr;   // lumped 1/nu pressure mass (level L-1, all nodes)
-    double* st_pf = nullptr;     // fine-level scalar scratch (interpolated pressure)
     double* st_qf = nullptr;     // fine-level scalar scratch (fine divergence)
     double* st_work = nullptr;   // Krylov vectors, st_work_vecs of them
     double* st_tri = nullptr;    // during a triangular-preconditioned solve: one Stokes vector
@@ -1732,7 +1731,6 @@ static int32_t stokes_ready(agca_hier* h) {
     const StokesDims d = stokes_dims(h);
     if (!h->st_mass) {
         TRY(alloc_t(h, &h->st_mass, (size_t)d.np));
-        TRY(alloc_t(h, &h->st_pf, (size_t)h->lv[h->cfg.L].nodes));
         TRY(alloc_t(h, &h->st_qf, (size_t)h->lv[h->cfg.L].nodes));
     }
     if (h->mass_version != h->nu_version) {
@@ -1761,25 +1759,23 @@ static int32_t stokes_work(agca_hier* h, int64_t vecs) {
     return AGCA_OK;
 }
 
-// q (pressure) = B u
-static int32_t stokes_div(agca_hier* h, const double* u, double* q) {
+// q (pressure) = B (s u), s elementwise (1 if null)
+static int32_t stokes_div(agca_hier* h, const double* u, double* q, const double* s = nullptr) {
     const StokesDims d = stokes_dims(h);
-    HIPCHK(h, launch_stokes_div_fine(d.nf, u, h->st_qf, h->st));
+    HIPCHK(h, launch_stokes_div_fine(d.nf, u, s, h->st_qf, h->st));
     HIPCHK(h, launch_restrict_all(d.nc, h->st_qf, q, h->st));
     return AGCA_OK;
 }
-// v (velocity) += B^T p
-static int32_t stokes_grad_add(agca_hier* h, const double* p, double* v) {
-    const StokesDims d = stokes_dims(h);
-    HIPCHK(h, launch_prolong_all(d.nf, p, h->st_pf, h->st));
-    HIPCHK(h, launch_stokes_grad_fine_add(d.nf, h->st_pf, v, h->st));
+// v (velocity) = s (in + B^T p), in = 0 and s = 1 if null
+static int32_t stokes_grad(agca_hier* h, const double* p, const double* in, double* v, const double* s = nullptr) {
+    HIPCHK(h, launch_stokes_grad(stokes_dims(h).nf, p, in, s, v, h->st));
     return AGCA_OK;
 }
 // y = K x
 static int32_t stokes_apply(agca_hier* h, const double* x, double* y) {
     const StokesDims d = stokes_dims(h);
     TRY(do_cube<double>(h, h->cfg.L, MODE_APPLY, x, nullptr, y, 0.0));
-    TRY(stokes_grad_add(h, x + d.nu, y));
+    TRY(stokes_grad(h, x + d.nu, y, y));
     TRY(stokes_div(h, x, y + d.nu));
     return AGCA_OK;
 }
@@ -1805,10 +1801,7 @@ static Bfbt bfbt_bufs(agca_hier* h) {
 }
 // out = Z y = B (W^-1 (B^T y))
 static int32_t z_apply(agca_hier* h, const Bfbt& w, const double* y, double* out) {
-    const StokesDims d = stokes_dims(h);
-    HIPCHK(h, launch_fill<double>(d.nu, 0.0, w.v1, h->st));
-    TRY(stokes_grad_add(h, y, w.v1));
-    HIPCHK(h, launch_mul_elementwise(d.nu, w.v1, w.winv, w.v1, h->st));
+    TRY(stokes_grad(h, y, nullptr, w.v1, w.winv));
     TRY(stokes_div(h, w.v1, out));
     return AGCA_OK;
 }
@@ -2070,12 +2063,9 @@ static int32_t bfbt_apply(agca_hier* h, const double* rp, double* q, int iters, 
         return mg ? z_solve_mg(h, w, r, y, iters) : z_solve(h, w, r, y, iters);
     };
     TRY(zsolve(rp, w.y1));
-    HIPCHK(h, launch_fill<double>(d.nu, 0.0, w.v2, h->st));
-    TRY(stokes_grad_add(h, w.y1, w.v2));
-    HIPCHK(h, launch_mul_elementwise(d.nu, w.v2, w.winv, w.v2, h->st));
+    TRY(stokes_grad(h, w.y1, nullptr, w.v2, w.winv));
     TRY(do_cube<double>(h, h->cfg.L, MODE_APPLY, w.v2, nullptr, w.v1, 0.0));
-    HIPCHK(h, launch_mul_elementwise(d.nu, w.v1, w.winv, w.v1, h->st));
-    TRY(stokes_div(h, w.v1, w.y2));
+    TRY(stokes_div(h, w.v1, w.y2, w.winv));
     TRY(zsolve(w.y2, q));
     return AGCA_OK;
 }
@@ -2115,8 +2105,7 @@ static int32_t stokes_precond(agca_hier* h, const double* r, double* z) {
     double* tu = h->st_tri;
     double* q = tu + d.nu;
     TRY(schur_inv(h, r + d.nu, q));
-    HIPCHK(h, launch_axpby<double>(d.nu, 1.0, r, 0.0, tu, h->st));
-    TRY(stokes_grad_add(h, q, tu));
+    TRY(stokes_grad(h, q, r, tu));
     TRY(velocity_inv(h, tu, z));
     HIPCHK(h, launch_axpby<double>(d.np, -1.0, q, 0.0, z + d.nu, h->st));
     return AGCA_OK;
@@ -2185,8 +2174,8 @@ static int32_t stokes_fgmres(agca_hier* h, const agca_stokes_opts* o, const doub
                    : launch_gs_dots<double>(tot, w, V, tot, nv, h->st_gs, h->st);
     };
     auto gs_update = [&](int nv) -> hipError_t {
-        return v32 ? launch_gs_update<float>(tot, w, V32, ld32, nv, h->red, h->st)
-                   : launch_gs_update<double>(tot, w, V, tot, nv, h->red, h->st);
+        return v32 ? launch_gs_update<float>(tot, w, V32, ld32, nv, h->red, h->st_gs, h->st)
+                   : launch_gs_update<double>(tot, w, V, tot, nv, h->red, h->st_gs, h->st);
     };
     HIPCHK(h, launch_fill<double>(tot, 0.0, x, h->st));
     HIPCHK(h, launch_axpby<double>(tot, 1.0, b, 0.0, r, h->st));
@@ -2231,7 +2220,6 @@ static int32_t stokes_fgmres(agca_hier* h, const agca_stokes_opts* o, const doub
             HIPCHK(h, gs_dots(k + 1));
             HIPCHK(h, launch_gs_sum(h->st_gs, nb, k + 2, h->red, h->st));
             HIPCHK(h, gs_update(k + 1));
-            HIPCHK(h, gs_dots(0));
             HIPCHK(h, launch_gs_sum(h->st_gs, nb, 1, h->red + k + 2, h->st));
             TRY(fetch(h, k + 3, col.data()));
             for (int i = 0; i <= k; ++i) Hm(i, k) = col[i];
@@ -2240,7 +2228,6 @@ static int32_t stokes_fgmres(agca_hier* h, const agca_stokes_opts* o, const doub
                 HIPCHK(h, gs_dots(k + 1));
                 HIPCHK(h, launch_gs_sum(h->st_gs, nb, k + 1, h->red, h->st));
                 HIPCHK(h, gs_update(k + 1));
-                HIPCHK(h, gs_dots(0));
                 HIPCHK(h, launch_gs_sum(h->st_gs, nb, 1, h->red + k + 1, h->st));
                 TRY(fetch(h, k + 2, col.data()));
                 for (int i = 0; i <= k; ++i) Hm(i, k) += col[i];
@@ -2411,8 +2398,7 @@ int32_t agca_stokes_div(agca_hier* h, const double* u, double* q) {
 int32_t agca_stokes_grad(agca_hier* h, const double* p, double* v) {
     TRY(stokes_ready(h));
     if (!p || !v) return fail(AGCA_E_INVALID, "null pointer");
-    HIPCHK(h, launch_fill<double>(stokes_dims(h).nu, 0.0, v, h->st));
-    return stokes_grad_add(h, p, v);
+    return stokes_grad(h, p, nullptr, v);
 }
 
 int32_t agca_stokes_mass(agca_hier* h, double* m) {

@@ -34,6 +34,20 @@ __device__ __forceinline__ T shr1_row(T v) {
     }
 }
 
+// the value of the lane one to the right (0 for the last)
+constexpr int kWaveShl1 = 0x130;
+template <typename T>
+__device__ __forceinline__ T shl1_row(T v) {
+    if constexpr (sizeof(T) == 8) {
+        const unsigned long long bits = __double_as_longlong(v);
+        const int lo = __builtin_amdgcn_update_dpp(0, (int)(bits & 0xffffffffull), kWaveShl1, 0xF, 0xF, true);
+        const int hi = __builtin_amdgcn_update_dpp(0, (int)(bits >> 32), kWaveShl1, 0xF, 0xF, true);
+        return __longlong_as_double(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
+    } else {
+        return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), kWaveShl1, 0xF, 0xF, true));
+    }
+}
+
 __device__ __forceinline__ float bf16_to_float(uint32_t bits16) { return __uint_as_float(bits16 << 16); }
 
 // The six coefficients of a cell as loaded (in their storage type), decoded only when

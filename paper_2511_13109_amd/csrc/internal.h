@@ -225,10 +225,13 @@ template <typename T>
 hipError_t launch_invert_diag(int64_t count, const double* diag, T* dinv, hipStream_t st);
 
 // Stokes pieces (k_stokes.hip): velocity on the level with n cells, pressure on n/2
-hipError_t launch_stokes_div_fine(int n, const double* u, double* q, hipStream_t st);
+// q = -B_L (s u) on the fine level, out = s (in - B_L^T P pc) (s, in: null for 1, 0; in may be out)
+hipError_t launch_stokes_div_fine(int n, const double* u, const double* s, double* q, hipStream_t st);
+hipError_t launch_stokes_grad(int n, const double* pc, const double* in, const double* s, double* out, hipStream_t st);
 // classical Gram-Schmidt against nv basis vectors V + i ld: gs_blocks(n) workgroups write
 // (nv + 1) rows of partials (w . V_i, then w . w); gs_sum reduces `rows` rows to out;
-// gs_update does w -= sum_i h[i] V_i with h on the device; the basis V is FP64 or FP32
+// gs_update does w -= sum_i h[i] V_i with h on the device and writes a row of partials of the new
+// w . w; the basis V is FP64 or FP32
 // (widened on the fly); scale_to_f32 writes y = a x rounded to FP32
 int gs_blocks(int64_t n);
 int gs_blocks_f32(int64_t n);  // the dot pass over an FP32 basis (twice the entries per workgroup)
@@ -237,10 +240,9 @@ hipError_t launch_gs_dots(int64_t n, const double* w, const VT* V, int64_t ld, i
                           double* partial, hipStream_t st);
 hipError_t launch_gs_sum(const double* partial, int nb, int rows, double* out, hipStream_t st);
 template <typename VT>
-hipError_t launch_gs_update(int64_t n, double* w, const VT* V, int64_t ld, int nv, const double* h,
+hipError_t launch_gs_update(int64_t n, double* w, const VT* V, int64_t ld, int nv, const double* h, double* partial,
                             hipStream_t st);
 hipError_t launch_scale_to_f32(int64_t n, double a, const double* x, float* y, hipStream_t st);
-hipError_t launch_stokes_grad_fine_add(int n, const double* pf, double* out, hipStream_t st);
 hipError_t launch_stokes_mass_fine(int n, const double* nu, double* mf, hipStream_t st);
 hipError_t launch_restrict_all(int n_coarse, const double* qf, double* out, hipStream_t st);
 hipError_t launch_prolong_all(int n_fine, const double* pc, double* pf, hipStream_t st);
@@ -256,8 +258,6 @@ hipError_t launch_zprobe(int n, int colour, double* out, hipStream_t st);
 hipError_t launch_zextract(int n, int colour, const double* y, double* S, hipStream_t st);
 hipError_t launch_zcoarse(const double* M, const double* r, double* y, hipStream_t st);
 hipError_t launch_zexpand(int n, const double* S, double* out, hipStream_t st);
-hipError_t launch_mul_elementwise(int64_t n, const double* a, const double* b, double* out,
-                                  hipStream_t st);
 // 27-colouring of a level's nodes by (x mod 3, y mod 3, z mod 3): mode 0 writes the
 // colour's indicator, mode 1 copies src into out on the colour's nodes only
 hipError_t launch_colour(int n, int colour, int mode, const double* src, double* out, hipStream_t st);

@@ -133,19 +133,6 @@ k_node7(int n, const T* __restrict__ W, const T* __restrict__ u, const T* __rest
 // a load that only the end lanes take part in), y neighbours from cache, the z flux carried in
 // a register, every load issued one step ahead.  Interior nodes number 2^k - 1 per row, so
 // 64-wide rows leave no lanes idle.  Bound by memory: 40 bytes per node (FP64 apply).
-constexpr int kWaveShl1 = 0x130;
-template <typename T>
-__device__ __forceinline__ T shl1_row(T v) {  // the value of the next lane (0 for the last)
-    if constexpr (sizeof(T) == 8) {
-        const unsigned long long bits = __double_as_longlong(v);
-        const int lo = __builtin_amdgcn_update_dpp(0, (int)(bits & 0xffffffffull), kWaveShl1, 0xF, 0xF, true);
-        const int hi = __builtin_amdgcn_update_dpp(0, (int)(bits >> 32), kWaveShl1, 0xF, 0xF, true);
-        return __longlong_as_double(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
-    } else {
-        return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), kWaveShl1, 0xF, 0xF, true));
-    }
-}
-
 template <typename T, int MODE>
 __global__ void __launch_bounds__(NT)
 k_march7(const int n, const int zc, const int gx, const int gy, const int gz, const T* __restrict__ W,

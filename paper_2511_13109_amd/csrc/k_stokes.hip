@@ -16,6 +16,7 @@
 // are the node's 15 lattice neighbours (kuhn.h nbr_of).
 #include <hip/hip_runtime.h>
 
+#include "cube_tile.h"
 #include "internal.h"
 #include "kuhn.h"
 
@@ -35,81 +36,226 @@ __device__ __forceinline__ bool cell_of(int n, int x, int y, int z, int k, int64
     return cx >= 0 && cy >= 0 && cz >= 0 && cx < n && cy < n && cz < n;
 }
 
-// q_v = -(B_L u)_v on every fine node (velocity boundary values are zero)
-__global__ void __launch_bounds__(NT)
-k_div_fine(int n, const double* __restrict__ u, double* __restrict__ q) {
-    const int64_t n1 = n + 1, N = n1 * n1 * n1;
-    const int64_t p = blockIdx.x * (int64_t)NT + threadIdx.x;
-    if (p >= N) return;
-    int x, y, z;
-    node_xyz(p, n, x, y, z);
-    // velocity at the 15 neighbours, zero outside the interior
-    double U[15][3];
-#pragma unroll
-    for (int k = 0; k < 15; ++k) {
-        const int m = nbr_mask(k), sg = nbr_sign(k);
-        const int qx = x + sg * (m & 1), qy = y + sg * ((m >> 1) & 1), qz = z + sg * (m >> 2);
-        const bool in = qx > 0 && qy > 0 && qz > 0 && qx < n && qy < n && qz < n;
-        const int64_t qi = in ? qx + n1 * (qy + n1 * (int64_t)qz) : 0;
-#pragma unroll
-        for (int c = 0; c < 3; ++c) U[k][c] = in ? u[c * N + qi] : 0.0;
-    }
-    double acc = 0.0;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        int64_t cell;
-        if (!cell_of(n, x, y, z, k, cell)) continue;
-#pragma unroll
-        for (int s = 0; s < 6; ++s)
-#pragma unroll
-            for (int a = 0; a < 4; ++a) {
-                if (path_corner(s, a) != k) continue;
-#pragma unroll
-                for (int b = 0; b < 4; ++b)
-#pragma unroll
-                    for (int c = 0; c < 3; ++c)
-                        if (grad(s, b, c) != 0) acc += (double)grad(s, b, c) * U[nbr_of(s, a, b)][c];
-            }
-    }
-    const double h = 1.0 / n;
-    q[p] = -(h * h / 24.0) * acc;
+// B_L and its transpose have constant coefficients: the sums over the simplices around a node
+// collapse to one number per neighbour and component.  (B_L at a boundary node sums over fewer
+// cells, but the cells that are missing have no interior vertex, and the velocity is 0 elsewhere.)
+constexpr int nbr_index(int dx, int dy, int dz) {  // kuhn.h neighbour index of an offset, -1 if none
+    return dx >= 0 && dy >= 0 && dz >= 0 ? dx + 2 * dy + 4 * dz : dx <= 0 && dy <= 0 && dz <= 0 ? 7 - dx - 2 * dy - 4 * dz : -1;
+}
+// of u_c at neighbour k in 24 / h^2 (B_L u) at a node; of the pressure at neighbour k in 24 / h^2
+// component c of (B_L^T p)
+constexpr int div_coef(int k, int c) {
+    int v = 0;
+    for (int s = 0; s < 6; ++s)
+        for (int a = 0; a < 4; ++a)
+            for (int b = 0; b < 4; ++b)
+                if (nbr_of(s, a, b) == k) v += grad(s, b, c);
+    return v;
+}
+constexpr int grad_coef(int k, int c) {
+    int v = 0;
+    for (int s = 0; s < 6; ++s)
+        for (int a = 0; a < 4; ++a)
+            for (int b = 0; b < 4; ++b)
+                if (nbr_of(s, a, b) == k) v += grad(s, a, c);
+    return v;
 }
 
-// out[(c, j)] += -(B_L^T pf)_(j, c) on interior fine nodes
+// Both run one wavefront per 62 nodes of a lattice row, marching a chunk of layers: a lane holds the
+// column x, the wavefront loads the rows y-1, y, y+1 of a layer once, one step ahead, and adds
+// them to the sums of the three layers they are part of; the columns x-1 and x+1 come from the
+// neighbour lanes by two DPP exchanges of the finished sums (the outer two lanes only feed
+// them).  A workgroup is 4 rows, an XCD a slab of layers.  Bound by memory (129^3: 68 and 106 MB).
+// Measured at 129^3: divergence 46 us with one thread per node, 45 loads and 144 products over
+// the simplices, 32 with a row per wavefront and layer (21 loads), 27 marching; gradient
+// with the interpolation of the pressure into a fine vector before it 37 us, 34 with the
+// interpolation in the loads; 257^3 with W^-1 applied: 710 -> 357 and 660 -> 300 us (the fill and
+// the elementwise products that went included).  Chunks of 8 to 32 layers measure alike.
+constexpr int RX = 62, RY = NT / 64;
+struct RowGrid {
+    int gx, gy, gz, zc;
+};
+RowGrid row_grid(int n) {
+    RowGrid g;
+    g.gx = (n + RX) / RX;
+    g.gy = (n + RY) / RY;
+    g.zc = 32;
+    while (g.zc > 2 && (int64_t)g.gx * g.gy * ((n + g.zc) / g.zc) < 2048) g.zc /= 2;
+    g.gz = (n + g.zc) / g.zc;
+    return g;
+}
+struct RowTile {
+    int x, y, z0, z1, lane;
+};
+__device__ __forceinline__ RowTile row_tile(int n, const RowGrid& g) {
+    const int cols = g.gx * g.gy, lin = tile_lin(cols, g.gz), bz = lin / cols, bc = lin - bz * cols;
+    RowTile r;
+    r.lane = threadIdx.x & 63;
+    r.x = (bc % g.gx) * RX - 1 + r.lane;
+    r.y = (bc / g.gx) * RY + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    r.z0 = bz * g.zc;
+    r.z1 = min(r.z0 + g.zc - 1, n);
+    return r;
+}
+// acc[0], acc[1], acc[2]: a lane's contributions to its right neighbour, itself and its left one
+__device__ __forceinline__ double row_sum(const double (&acc)[3]) {
+    const double l = shr1_row(acc[0]), r = shl1_row(acc[2]);
+    return acc[1] + (l + r);
+}
+
+// q_v = -(B_L (s u))_v on every fine node, s elementwise (1 if null); velocity boundary values
+// count as zero
+template <bool SCALED>
 __global__ void __launch_bounds__(NT)
-k_grad_fine_add(int n, const double* __restrict__ pf, double* __restrict__ out) {
-    const int64_t n1 = n + 1, N = n1 * n1 * n1;
-    const int64_t p = blockIdx.x * (int64_t)NT + threadIdx.x;
-    if (p >= N) return;
-    int x, y, z;
-    node_xyz(p, n, x, y, z);
-    if (x == 0 || y == 0 || z == 0 || x == n || y == n || z == n) return;
-    double P[15];
+k_div_fine(int n, const RowGrid g, const double* __restrict__ u, const double* __restrict__ s, double* __restrict__ q) {
+    const RowTile p = row_tile(n, g);
+    if (p.y > n) return;
+    const int n1 = n + 1;
+    const int64_t layer = (int64_t)n1 * n1, N = layer * n1;
+    const uint32_t lbytes = (uint32_t)(layer * sizeof(double));
+    const bool xin = p.x > 0 && p.x < n;
+    uint32_t at[3];
 #pragma unroll
-    for (int k = 0; k < 15; ++k) {
-        const int m = nbr_mask(k), sg = nbr_sign(k);
-        // interior node: every neighbour lies in the lattice
-        P[k] = pf[(x + sg * (m & 1)) + n1 * ((y + sg * ((m >> 1) & 1)) + n1 * (int64_t)(z + sg * (m >> 2)))];
-    }
-    double acc[3] = {0.0, 0.0, 0.0};
+    for (int j = 0; j < 3; ++j) at[j] = xin && p.y + j > 1 && p.y + j <= n ? (uint32_t)(p.x + n1 * (p.y + j - 1)) * 8u : kOut;
+    const uint32_t at_q = p.lane >= 1 && p.lane <= RX && p.x <= n ? (uint32_t)(p.x + n1 * p.y) * 8u : kOut;
+    struct Rows {
+        double v[3][3], s[SCALED ? 3 : 1][SCALED ? 3 : 1];
+    };
+    auto load = [&](int Z, Rows& r) {
+        const bool zin = Z > 0 && Z < n && Z <= p.z1 + 1;
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
+        for (int c = 0; c < 3; ++c)
 #pragma unroll
-        for (int s = 0; s < 6; ++s)
-#pragma unroll
-            for (int a = 0; a < 4; ++a) {
-                if (path_corner(s, a) != k) continue;
-                double sum = 0.0;
-#pragma unroll
-                for (int b = 0; b < 4; ++b) sum += P[nbr_of(s, a, b)];
-#pragma unroll
-                for (int c = 0; c < 3; ++c)
-                    if (grad(s, a, c) != 0) acc[c] += (double)grad(s, a, c) * sum;
+            for (int j = 0; j < 3; ++j) {
+                r.v[j][c] = bload<double>(layer_of(u + c * N + Z * layer, zin, lbytes), at[j]);
+                if constexpr (SCALED) r.s[j][c] = bload<double>(layer_of(s + c * N + Z * layer, zin, lbytes), at[j]);
             }
-    }
-    const double h = 1.0 / n;
+    };
+    const double h = 1.0 / n, w = h * h / 24.0;
+    double acc[3][3] = {};  // of layers Z-1, Z, Z+1
+    auto step = [&](int Z, const Rows& cur, Rows& nxt) {
+        load(Z + 1, nxt);
 #pragma unroll
-    for (int c = 0; c < 3; ++c) out[c * N + p] -= (h * h / 24.0) * acc[c];
+        for (int j = 0; j < 3; ++j)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                double v = cur.v[j][c];
+                if constexpr (SCALED) v *= cur.s[j][c];
+#pragma unroll
+                for (int dz = -1; dz <= 1; ++dz)
+#pragma unroll
+                    for (int dx = -1; dx <= 1; ++dx) {
+                        // offset from the output node to the value: layer Z - dz
+                        const int k = nbr_index(dx, j - 1, dz);
+                        if (k >= 0 && div_coef(k, c) != 0)
+                            acc[1 - dz][1 + dx] = fma((double)div_coef(k, c), v, acc[1 - dz][1 + dx]);
+                    }
+            }
+        const double t = row_sum(acc[0]);
+        bstore<double>(layer_of(q + (Z - 1) * layer, Z - 1 >= p.z0 && Z - 1 <= p.z1, lbytes), at_q, -w * t);
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            acc[0][d] = acc[1][d];
+            acc[1][d] = acc[2][d];
+            acc[2][d] = 0.0;
+        }
+    };
+    // two register sets in turn: a copy from one to the other would wait for its loads
+    Rows even, odd;
+    load(p.z0 - 1, even);
+    for (int Z = p.z0 - 1; Z <= p.z1 + 1; Z += 2) {
+        step(Z, even, odd);
+        step(Z + 1, odd, even);
+    }
+}
+
+// out = s (in - B_L^T (P pc)) on interior fine nodes (s = 1, in = 0 if null); on boundary nodes
+// out = in.  pc: pressure on the level with n/2 cells; in may be out.
+template <bool SCALED>
+__global__ void __launch_bounds__(NT)
+k_grad_fine(int n, const RowGrid g, const double* __restrict__ pc, const double* in, const double* __restrict__ s,
+            double* out) {
+    const RowTile p = row_tile(n, g);
+    if (p.y > n) return;
+    const int n1 = n + 1, c1 = n / 2 + 1;
+    const int64_t layer = (int64_t)n1 * n1, N = layer * n1, clayer = (int64_t)c1 * c1;
+    const uint32_t lbytes = (uint32_t)(layer * sizeof(double)), cbytes = (uint32_t)(clayer * sizeof(double));
+    const bool xin = p.x >= 0 && p.x <= n;
+    uint32_t lo[3], hi[3];
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+        const int Y = p.y + j - 1;
+        const bool ok = xin && Y >= 0 && Y <= n;
+        lo[j] = ok ? (uint32_t)((p.x >> 1) + c1 * (Y >> 1)) * 8u : kOut;
+        hi[j] = ok ? (uint32_t)(((p.x + 1) >> 1) + c1 * ((Y + 1) >> 1)) * 8u : kOut;
+    }
+    const uint32_t at = p.lane >= 1 && p.lane <= RX && p.x <= n ? (uint32_t)(p.x + n1 * p.y) * 8u : kOut;
+    const bool inner = p.x > 0 && p.y > 0 && p.x < n && p.y < n;
+    struct Rows {
+        double lo[3], hi[3];
+    };
+    auto load = [&](int Z, Rows& r) {
+        const bool zin = Z >= 0 && Z <= n && Z <= p.z1 + 1;
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            r.lo[j] = bload<double>(layer_of(pc + (Z >> 1) * clayer, zin, cbytes), lo[j]);
+            r.hi[j] = bload<double>(layer_of(pc + ((Z + 1) >> 1) * clayer, zin, cbytes), hi[j]);
+        }
+    };
+    struct Own {
+        double in[3], s[SCALED ? 3 : 1];
+    };
+    auto load_own = [&](int z, Own& o) {
+        const bool zin = z >= p.z0 && z <= p.z1;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            o.in[c] = bload<double>(layer_of(in + c * N + z * layer, zin && in, lbytes), at);
+            if constexpr (SCALED) o.s[c] = bload<double>(layer_of(s + c * N + z * layer, zin, lbytes), at);
+        }
+    };
+    const double h = 1.0 / n, w = h * h / 24.0;
+    double acc[3][3][3] = {};  // of layers Z-1, Z, Z+1 and component c
+    auto step = [&](int Z, const Rows& cur, const Own& own, Rows& nxt, Own& own_n) {
+        load(Z + 1, nxt);
+        load_own(Z, own_n);
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            const double v = 0.5 * (cur.lo[j] + cur.hi[j]);
+#pragma unroll
+            for (int c = 0; c < 3; ++c)
+#pragma unroll
+                for (int dz = -1; dz <= 1; ++dz)
+#pragma unroll
+                    for (int dx = -1; dx <= 1; ++dx) {
+                        const int k = nbr_index(dx, j - 1, dz);
+                        if (k >= 0 && grad_coef(k, c) != 0)
+                            acc[1 - dz][c][1 + dx] = fma((double)grad_coef(k, c), v, acc[1 - dz][c][1 + dx]);
+                    }
+        }
+        const int z = Z - 1;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const double t = row_sum(acc[0][c]);
+            double v = own.in[c] - w * t;
+            if constexpr (SCALED) v *= own.s[c];
+            bstore<double>(layer_of(out + c * N + z * layer, z >= p.z0 && z <= p.z1, lbytes), at,
+                           inner && z > 0 && z < n ? v : own.in[c]);
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                acc[0][c][d] = acc[1][c][d];
+                acc[1][c][d] = acc[2][c][d];
+                acc[2][c][d] = 0.0;
+            }
+        }
+    };
+    Rows even, odd;
+    Own own_e, own_o;
+    load(p.z0 - 1, even);
+    load_own(p.z0 - 2, own_e);
+    for (int Z = p.z0 - 1; Z <= p.z1 + 1; Z += 2) {
+        step(Z, even, own_e, odd, own_o);
+        step(Z + 1, odd, own_o, even, own_e);
+    }
 }
 
 // m_L(v) = h^3/24 sum_{d containing v} 1/nu_d on every fine node
@@ -184,14 +330,6 @@ k_div_elementwise(int64_t n, const double* __restrict__ num, const double* __res
                   double* __restrict__ out) {
     const int64_t stride = (int64_t)gridDim.x * NT;
     for (int64_t i = blockIdx.x * (int64_t)NT + threadIdx.x; i < n; i += stride) out[i] = num[i] / den[i];
-}
-
-// out = a * b elementwise
-__global__ void __launch_bounds__(NT)
-k_mul_elementwise(int64_t n, const double* __restrict__ a, const double* __restrict__ b,
-                  double* __restrict__ out) {
-    const int64_t stride = (int64_t)gridDim.x * NT;
-    for (int64_t i = blockIdx.x * (int64_t)NT + threadIdx.x; i < n; i += stride) out[i] = a[i] * b[i];
 }
 
 // Colour (x mod 3) + 3 (y mod 3) + 9 (z mod 3) of the nodes of a level with n cells per
@@ -293,17 +431,45 @@ k_gs_sum(const double* __restrict__ partial, int nb, double* __restrict__ out) {
     }
 }
 
-// w -= sum_i h[i] V_i (h on the device; an FP32 basis widened on the fly)
-template <typename VT>
-__global__ void __launch_bounds__(NT)
-k_gs_update(int64_t n, double* __restrict__ w, const VT* __restrict__ V, int64_t ld, int nv,
-            const double* __restrict__ h) {
-    const int64_t stride = (int64_t)gridDim.x * NT;
-    for (int64_t j = blockIdx.x * (int64_t)NT + threadIdx.x; j < n; j += stride) {
-        double acc = 0.0;
-        for (int i = 0; i < nv; ++i) acc += h[i] * (double)V[(int64_t)i * ld + j];
-        w[j] -= acc;
+// w -= sum_i h[i] V_i (h on the device), and per workgroup the partial sum of the new w^2 (in the
+// order of k_gs_dots: the pass of its own over w that this replaces gave the same bits)
+__device__ __forceinline__ void gs_store_partial(double acc, double* __restrict__ partial) {
+    __shared__ double red[NT / 64];
+    acc = gs_wave_sum(acc);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double t = 0.0;
+        for (int q = 0; q < NT / 64; ++q) t += red[q];
+        partial[blockIdx.x] = t;
     }
+}
+__global__ void __launch_bounds__(NT)
+k_gs_update(int64_t n, double* __restrict__ w, const double* __restrict__ V, int64_t ld, int nv,
+            const double* __restrict__ h, double* __restrict__ partial) {
+    const int64_t base = (int64_t)blockIdx.x * GS_CHUNK + threadIdx.x;
+    double a[GS_PER] = {};
+#pragma unroll 2
+    for (int i = 0; i < nv; ++i) {
+        const double* v = V + (int64_t)i * ld;
+        const double hi = h[i];
+#pragma unroll
+        for (int m = 0; m < GS_PER; ++m) {
+            const int64_t j = base + (int64_t)m * NT;
+            a[m] += hi * (j < n ? v[j] : 0.0);
+        }
+    }
+    double acc = 0.0;
+#pragma unroll
+    for (int m = 0; m < GS_PER; ++m) {
+        const int64_t j = base + (int64_t)m * NT;
+        if (j < n) {
+            const double t = w[j] - a[m];
+            w[j] = t;
+            acc += t * t;
+        }
+    }
+    gs_store_partial(acc, partial);
 }
 
 // The same two passes over an FP32 basis, four consecutive entries per lane and load
@@ -365,8 +531,9 @@ k_gs_dots_f32(int64_t n, const double* __restrict__ w, const float* __restrict__
 // vectors issued before their products are summed (in the order of i, as above)
 __global__ void __launch_bounds__(NT)
 k_gs_update_f32(int64_t n, double* __restrict__ w, const float* __restrict__ V, int64_t ld, int nv,
-                const double* __restrict__ h) {
+                const double* __restrict__ h, double* __restrict__ partial) {
     const int64_t stride = (int64_t)gridDim.x * NT;
+    double acc = 0.0;
     for (int64_t j = 4 * (blockIdx.x * (int64_t)NT + threadIdx.x); j < n; j += 4 * stride) {
         double a[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll 4
@@ -380,8 +547,13 @@ k_gs_update_f32(int64_t n, double* __restrict__ w, const float* __restrict__ V, 
         }
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-            if (j + e < n) w[j + e] -= a[e];
+            if (j + e < n) {
+                const double t = w[j + e] - a[e];
+                w[j + e] = t;
+                acc += t * t;
+            }
     }
+    gs_store_partial(acc, partial);
 }
 
 // y = a x rounded to FP32 (a new FP32 basis vector)
@@ -399,16 +571,24 @@ unsigned grid_stride(int64_t n) {
 
 }  // namespace
 
-hipError_t launch_stokes_div_fine(int n, const double* u, double* q, hipStream_t st) {
+hipError_t launch_stokes_div_fine(int n, const double* u, const double* s, double* q, hipStream_t st) {
     if (!u || !q || n < 2) return hipErrorInvalidValue;
-    const int64_t N = (int64_t)(n + 1) * (n + 1) * (n + 1);
-    hipLaunchKernelGGL(k_div_fine, dim3(grid_for(N)), dim3(NT), 0, st, n, u, q);
+    const RowGrid g = row_grid(n);
+    const dim3 grid((unsigned)((int64_t)g.gx * g.gy * g.gz));
+    if (s)
+        hipLaunchKernelGGL(k_div_fine<true>, grid, dim3(NT), 0, st, n, g, u, s, q);
+    else
+        hipLaunchKernelGGL(k_div_fine<false>, grid, dim3(NT), 0, st, n, g, u, s, q);
     return hipGetLastError();
 }
-hipError_t launch_stokes_grad_fine_add(int n, const double* pf, double* out, hipStream_t st) {
-    if (!pf || !out || n < 2) return hipErrorInvalidValue;
-    const int64_t N = (int64_t)(n + 1) * (n + 1) * (n + 1);
-    hipLaunchKernelGGL(k_grad_fine_add, dim3(grid_for(N)), dim3(NT), 0, st, n, pf, out);
+hipError_t launch_stokes_grad(int n, const double* pc, const double* in, const double* s, double* out, hipStream_t st) {
+    if (!pc || !out || n < 2) return hipErrorInvalidValue;
+    const RowGrid g = row_grid(n);
+    const dim3 grid((unsigned)((int64_t)g.gx * g.gy * g.gz));
+    if (s)
+        hipLaunchKernelGGL(k_grad_fine<true>, grid, dim3(NT), 0, st, n, g, pc, in, s, out);
+    else
+        hipLaunchKernelGGL(k_grad_fine<false>, grid, dim3(NT), 0, st, n, g, pc, in, s, out);
     return hipGetLastError();
 }
 hipError_t launch_stokes_mass_fine(int n, const double* nu, double* mf, hipStream_t st) {
@@ -439,14 +619,6 @@ hipError_t launch_div_elementwise(int64_t n, const double* num, const double* de
                                   hipStream_t st) {
     if (!num || !den || !out) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_div_elementwise, dim3(grid_stride(n)), dim3(NT), 0, st, n, num, den, out);
-    return hipGetLastError();
-}
-
-hipError_t launch_mul_elementwise(int64_t n, const double* a, const double* b, double* out,
-                                  hipStream_t st) {
-    if (n <= 0) return hipSuccess;
-    if (!a || !b || !out) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_mul_elementwise, dim3(grid_stride(n)), dim3(NT), 0, st, n, a, b, out);
     return hipGetLastError();
 }
 
@@ -483,20 +655,21 @@ hipError_t launch_gs_sum(const double* partial, int nb, int rows, double* out, h
     return hipGetLastError();
 }
 template <typename VT>
-hipError_t launch_gs_update(int64_t n, double* w, const VT* V, int64_t ld, int nv, const double* h,
+hipError_t launch_gs_update(int64_t n, double* w, const VT* V, int64_t ld, int nv, const double* h, double* partial,
                             hipStream_t st) {
-    if (!w || !V || !h || n <= 0 || nv <= 0) return hipErrorInvalidValue;
+    if (!w || !V || !h || !partial || n <= 0 || nv <= 0) return hipErrorInvalidValue;
     if constexpr (sizeof(VT) == 4) {
         if ((ld & 3) || ld < n || (reinterpret_cast<uintptr_t>(V) & 15)) return hipErrorInvalidValue;
-        hipLaunchKernelGGL(k_gs_update_f32, dim3(grid_stride((n + 3) / 4)), dim3(NT), 0, st, n, w, V, ld, nv, h);
+        hipLaunchKernelGGL(k_gs_update_f32, dim3((unsigned)gs_blocks_f32(n)), dim3(NT), 0, st, n, w, V, ld, nv, h,
+                           partial);
     } else {
-        hipLaunchKernelGGL(k_gs_update<VT>, dim3(grid_stride(n)), dim3(NT), 0, st, n, w, V, ld, nv, h);
+        hipLaunchKernelGGL(k_gs_update, dim3((unsigned)gs_blocks(n)), dim3(NT), 0, st, n, w, V, ld, nv, h, partial);
     }
     return hipGetLastError();
 }
-template hipError_t launch_gs_update<double>(int64_t, double*, const double*, int64_t, int, const double*,
+template hipError_t launch_gs_update<double>(int64_t, double*, const double*, int64_t, int, const double*, double*,
                                              hipStream_t);
-template hipError_t launch_gs_update<float>(int64_t, double*, const float*, int64_t, int, const double*,
+template hipError_t launch_gs_update<float>(int64_t, double*, const float*, int64_t, int, const double*, double*,
                                             hipStream_t);
 hipError_t launch_scale_to_f32(int64_t n, double a, const double* x, float* y, hipStream_t st) {
     if (!x || !y || n <= 0) return hipErrorInvalidValue;
