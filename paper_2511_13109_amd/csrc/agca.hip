@@ -328,9 +328,9 @@ bool fusable(const agca_hier* h, int l) {
 // Whether two consecutive products on level l run as one pass (k_smooth2.hip): the levels of
 // `fusable`, except small FP64 vector ones.  There every form is bound by the latency of its
 // z steps, and a step with two products at 2 wavefronts per SIMD is the longer one (V-cycle
-// with a finest level of 16 / 32 / 64 cells per axis: 76.2 / 102.6 / 165.9 us against 70.8 /
-// 97.3 / 167.7 as single passes; scalar and FP32: 34.5 against 35.5 and 56.2 against 57.4 us
-// at 16 cells, and the gain grows with the size).
+// with a finest level of 32 cells per axis 88.7 us against 85.3 as single passes, of 64 cells
+// with the 32-cell level in one or the other form 147.8 against 144.8; FP32 at 16 cells 56.2
+// against 57.4 us, and the gain grows with the size).
 template <typename T>
 bool two_products(const agca_hier* h, int l) {
     if (level_op<T>(h, l).wts) return true;

@@ -185,15 +185,14 @@ k_march7(const int n, const int zc, const int gx, const int gy, const int gz, co
         return bload<T>(layer_of(u + (int64_t)z * layer, z > 0 && z < n && z <= zend + 1, lbytes), at);
     };
     double dot = 0.0;
-    Step cur, nxt;
     const T wz0 = bload<T>(layer_of(W + 2 * N + (int64_t)(Z0 - 1) * layer, Z0 > 0, lbytes), at);
     const T um = load_u(Z0 - 1);
-    T uc = load_u(Z0), uq = load_u(Z0 + 1);
-    load(Z0, cur);
+    const T uc = load_u(Z0), uq = load_u(Z0 + 1);
     T fz = wz0 * (uc - um);  // flux from layer z-1 into z
-    for (int z = Z0; z <= zend; ++z) {
+    // layer z, its values in cur and u(z), u(z+1) in uc, uq; loads layer z+1's into nxt, u(z+2) into un
+    auto step = [&](int z, const Step& cur, Step& nxt, const T uc, const T uq, T& un) {
         load(z + 1, nxt);
-        const T un = load_u(z + 2);
+        un = load_u(z + 2);
         // (every lane takes part in the exchanges; the ends then replace what they got)
         const T right = shl1_row(uc);
         const T fx = cur.wx * ((lane == 63 ? cur.e : right) - uc);
@@ -209,9 +208,24 @@ k_march7(const int n, const int zc, const int gx, const int gy, const int gz, co
         const Rsrc ro = layer_of(out + (int64_t)z * layer, true, lbytes);
         bstore<T>(ro, at_w, in ? v : T(0));
         bstore<T>(ro, at_wb, T(0));
-        uc = uq;
-        uq = un;
-        cur = nxt;
+    };
+    // registers in turn: a copy from those just loaded would wait for the loads
+    Step s0, s1;
+    T u0 = uc, u1 = uq, u2;
+    load(Z0, s0);
+    for (int z = Z0;;) {
+        step(z, s0, s1, u0, u1, u2);
+        if (++z > zend) break;
+        step(z, s1, s0, u1, u2, u0);
+        if (++z > zend) break;
+        step(z, s0, s1, u2, u0, u1);
+        if (++z > zend) break;
+        step(z, s1, s0, u0, u1, u2);
+        if (++z > zend) break;
+        step(z, s0, s1, u1, u2, u0);
+        if (++z > zend) break;
+        step(z, s1, s0, u2, u0, u1);
+        if (++z > zend) break;
     }
     if (MODE == MODE_APPLY_DOT) store_partial(dot, partial + blockIdx.x);
 }
@@ -376,7 +390,6 @@ k_two7(const int n, const int zc, const int gx, const int gy, const int gz, cons
         bv = bload<T>(layer_of(b + (int64_t)zq * layer, zin, lbytes), at_r);
         if constexpr (!PRE) dv = bload<T>(layer_of(dinv + (int64_t)zq * layer, zin, lbytes), at_r);
     };
-    load_rhs(Z0 - 2, bq, dq);
     if constexpr (!PRE)
         if (Z0 & 1) {
             __syncthreads();
@@ -384,6 +397,7 @@ k_two7(const int n, const int zc, const int gx, const int gy, const int gz, cons
         }
     __syncthreads();
     for (int z = Z0 - 2; z <= zend + 2; ++z) {
+        load_rhs(z, bq, dq);
         T ownB, fyB, fzB, ownA, fyA, fzA;
         {
             const int lo = z & 1, hi = lo ^ 1;  // layers z-2 and z-1
@@ -404,8 +418,6 @@ k_two7(const int n, const int zc, const int gx, const int gy, const int gz, cons
         if constexpr (!PRE) coarse.load((z + 5) >> 1, at_e, z & 1, ev);
         load_node(z + 3, at_b, ext);
         load_node(z + 3, at, own);
-        T bn, dn = T(0);
-        load_rhs(z + 1, bn, dn);
         __syncthreads();
         const bool wA = z >= Z0 && z <= zend, wB = z - 2 >= Z0 && z - 2 <= zend;
         const T av = ca + (ownA + fa[up]);
@@ -427,8 +439,6 @@ k_two7(const int n, const int zc, const int gx, const int gy, const int gz, cons
             ch[1] = a2 * y + g2 * self + oh[1] * bq;
         }
         ys[z & 1][tid] = y;
-        bq = bn;
-        dq = dn;
         r0 = r1; r1 = r2; r2 = r3;
         __syncthreads();
     }

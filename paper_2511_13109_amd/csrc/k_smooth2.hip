@@ -20,9 +20,12 @@
 // Why this shape: 32-wide rows (a wavefront covers two) and 16 rows are the largest tile
 // whose vector FP64 state fits without spills: two products' carried sums, three coefficient
 // layers and the loads in flight take 231-248 of the 256 registers of 2 wavefronts per SIMD
-// (one workgroup per compute unit, 118-154 KB of LDS); FP32 runs two workgroups per unit
-// within 128 registers.  All loads of a step are issued one step ahead, before the barrier,
-// in the order of their use (the wait counter is in order).  Ordering the tiles in bands of
+// (one workgroup per compute unit, 137-157 KB of LDS); FP32 runs two workgroups per unit
+// within 128 registers.  Node loads are issued one step ahead, in the order of their use (the
+// wait counter is in order), right-hand side and inverse diagonal at the start of the step that
+// ends with them: no register is copied from one that was just loaded, a copy would wait for
+// every load in flight at the end of each step (vector FP64 V-cycle at 129^3 383 us with such
+// copies, 360 without; 257^3 1970 and 1836; 513^3 BF16/FP32 7.55 and 7.32 ms).  Ordering the tiles in bands of
 // rows so that the y halos are found in L2 measured slower (513^3 FP64 V-cycle, bands of
 // 1 / 4 / 16 rows: 17.0 / 17.2 / 18.2 ms), as in k_apply.hip.
 //
@@ -236,7 +239,6 @@ k_smooth2(const int n, const int zc, const int gx, const int gy, const int gz, c
             if constexpr (!PRE) dv[c] = bload<T>(layer_of(dinv + off + c * N, zin, lbytes), at_r);
         }
     };
-    load_rhs(Z0 - 2, bq, dq);
     if constexpr (!PRE)
         if (Z0 & 1) {
             __syncthreads();
@@ -245,6 +247,7 @@ k_smooth2(const int n, const int zc, const int gx, const int gy, const int gz, c
     __syncthreads();
 
     for (int z = Z0 - 2; z <= zend + 2; ++z) {
+        load_rhs(z, bq, dq);
         // second product: cell layer z-2 of the first pass's result
         T PB[2][2][NC];
         {
@@ -298,8 +301,6 @@ k_smooth2(const int n, const int zc, const int gx, const int gy, const int gz, c
         if constexpr (!PRE) coarse.load((z + 5) >> 1, lc[tid].w, z & 1, ev);
         load_node(z + 3, ext_offset(), ext);
         load_node(z + 3, at, own);
-        T bn[NC], dn[NC];
-        load_rhs(z + 1, bn, dn);
         __builtin_amdgcn_sched_barrier(0);
         __syncthreads();
         // boundary nodes have self = dinv = b = 0, hence y = 0
@@ -327,11 +328,6 @@ k_smooth2(const int n, const int zc, const int gx, const int gy, const int gz, c
                 ch[1][c] = a2 * y + g2 * self + od * bq[c];
             }
             ys[z & 1][c][tid] = y;
-        }
-#pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            bq[c] = bn[c];
-            if constexpr (!PRE) dq[c] = dn[c];
         }
         r0 = r1; r1 = r2; r2 = r3;
         __syncthreads();
