@@ -362,8 +362,8 @@ int smooth_pass_coef(const agca_hier* h, int l, bool pre, int k, const T* xprev,
 }
 
 // Levels 1..K that the coarse end of a V-cycle runs in one workgroup (k_coarse_cycle.hip):
-// consecutive levels from level 1 up that have their operator in the form it reads (scalar:
-// edge weights, up to the finest level; vector: assembled stencils, below the finest level),
+// consecutive levels from level 1 up, the finest included, that have their operator in the form
+// it reads (scalar: edge weights; vector: the FP64 coefficient, so not a finest level in BF16),
 // as many as its registers and LDS take (coarse_cycle_max_level), with at most
 // AGCA_FUSE_MAX_N cells per axis (default no bound; 0 turns the fused cycle off); 0 when level
 // 1 does not qualify or a smoothing phase has more passes than the fused cycle takes.
@@ -379,9 +379,9 @@ int coarse_cycle_levels(const agca_hier* h) {
     if (h->cfg.pre_sweeps > kCyclePasses || h->cfg.post_sweeps > kCyclePasses) return 0;
     const int nc = h->cfg.ncomp;
     int K = 0;
-    for (int l = 1; l <= coarse_cycle_max_level(nc, sizeof(T)) && l <= h->cfg.L; ++l) {
+    for (int l = 1; l <= coarse_cycle_max_level(nc) && l <= h->cfg.L; ++l) {
         const LevelOp<T> op = level_op<T>(h, l);
-        if (!(nc == 1 ? op.wts : op.sten) || op.n != (2 << l) || op.n > fuse_max_n()) break;
+        if ((nc == 1 ? !op.wts : op.nu_kind == AGCA_BF16) || op.n != (2 << l) || op.n > fuse_max_n()) break;
         K = l;
     }
     return K;
@@ -486,7 +486,7 @@ int32_t do_vcycle(agca_hier* h, const T* bL, T* xL) {
         cc.post = post;
         for (int l = 1; l <= K; ++l) {
             const LevelOp<T> op = level_op<T>(h, l);
-            cc.sten[l] = op.sten;
+            cc.nu[l] = h->lv[l].nu64;
             cc.wts[l] = op.wts;
             cc.dinv[l] = op.dinv;
             cc.first_omega[l] = cheb ? T(1.0 / Cheb(h->lam[l]).theta) : om;

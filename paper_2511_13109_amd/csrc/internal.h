@@ -111,8 +111,8 @@ constexpr int kCyclePasses = 8;  // pre, post <= 8
 template <typename T>
 struct CoarseCycle {
     int pre = 0, post = 0;
-    const T* sten[kCycleLevels + 1] = {};  // vector: 15-point stencils
-    const T* wts[kCycleLevels + 1] = {};   // scalar: edge weights
+    const double* nu[kCycleLevels + 1] = {};  // vector: coefficient
+    const T* wts[kCycleLevels + 1] = {};      // scalar: edge weights
     const T* dinv[kCycleLevels + 1] = {};
     T first_omega[kCycleLevels + 1] = {};
     int8_t pre_mode[kCycleLevels + 1][kCyclePasses] = {};
@@ -123,7 +123,7 @@ struct CoarseCycle {
     const T* b = nullptr;          // level K, ncomp (n+1)^3 values (device)
     T* x = nullptr;                // level K, written
 };
-int coarse_cycle_max_level(int ncomp, size_t elem);  // the largest K
+int coarse_cycle_max_level(int ncomp);  // the largest K
 template <typename T>
 hipError_t launch_coarse_cycle(int ncomp, int K, const CoarseCycle<T>& a, hipStream_t st);
 

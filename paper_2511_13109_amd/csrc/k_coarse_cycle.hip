@@ -7,22 +7,23 @@
 // every level: their right-hand side, inverse diagonal, iterate and previous iterate stay in
 // its registers, and only the iterate's values that neighbours read (two buffers per level)
 // are in LDS.  The operator's rows are read once: the top level's into registers (scalar: the
-// six weights of the seven-point form, k_scalar.hip; vector: of the 15-point stencil,
-// k_stencil.hip, the 37 entries that are not identically zero), the lower levels' into LDS.
+// six weights of the seven-point form, k_scalar.hip; vector: of the 15-point stencil the 37
+// entries that are not identically zero, formed from the coefficient), the lower levels' into LDS.
 // (A component couples with itself along lattice axes only: unit_entry, kuhn.h, is the path
 // Laplacian plus the product of two gradient components, which for equal components is
 // non-zero only across a step along that axis.)
 //
-// K: scalar hierarchies up to 17^3 nodes (K = 3; the whole cycle where that is the finest
-// level), FP64 vector ones up to 9^3 (K = 2: the 1029 rows of 37 entries are what the registers
-// of 512 threads hold; the five rows beyond stay in LDS), FP32 vector ones up to 5^3: there K = 2
-// gains 4 us with the stencils in cache, but after fine levels that push them out, one compute
-// unit's reads of them take longer than the launches saved (17^3 / 129^3 cycle from cold
-// caches 67.4 / 281 us at K = 2, 58.9 / 273 at K = 1; FP64 69.6 / 431 and 73.2 / 435).  A pass is bound by the LDS reads of
-// the neighbours (9^3 vector FP64: 37 per row, about 1 us) and the barrier.
-// Whole cycles, Chebyshev (2, 2), before (one launch per pass above 5^3 / 9^3) and now:
-// scalar 9^3 27 -> 6 us, 17^3 FP64 36 -> 17, FP32 32 -> 14; vector 17^3 FP64 72 -> 58, FP32
-// 56 -> 53.
+// K: scalar hierarchies up to 17^3 nodes (K = 3), vector ones up to 9^3 (K = 2: the 1029 rows of
+// 37 entries are what the registers of 512 threads hold; the five rows beyond stay in LDS); the
+// whole cycle where that is the finest level.  The vector rows are formed here, from the 24 KB
+// of coefficients of a 9^3 level: read as an assembled stencil they are 0.8 MB (FP64), after
+// fine levels that push them out of the caches more than one compute unit reads in the time
+// of the launches it saves (FP32 17^3 cycle from cold caches 67 us, 59 with launches for the 9^3
+// level, 52 this way; FP64 70, 73 and 62).
+// A pass is bound by the LDS reads of the neighbours (9^3 vector FP64: 37 per row, about
+// 1 us) and the barrier.  Whole cycles, Chebyshev (2, 2), before (one launch per pass above
+// 5^3 / 9^3) and now: scalar 9^3 27 -> 6 us, 17^3 FP64 36 -> 17, FP32 32 -> 14; vector
+// 9^3 FP64 47 -> 21, FP32 36 -> 16, 17^3 72 -> 56 and 56 -> 46.
 #include <hip/hip_runtime.h>
 
 #include "internal.h"
@@ -39,7 +40,7 @@ constexpr int ct(int nc, size_t elem) { return nc == 1 && elem == 4 ? 1024 : 512
 constexpr int row_regs(int nc, size_t elem) { return nc == 1 ? 4096 / ct(nc, elem) : 2; }
 
 constexpr int kReads = 8;  // a vector row's neighbour reads in flight (all 37: the registers of a row)
-constexpr int max_level(int nc, size_t elem) { return nc == 1 ? 3 : elem == 8 ? 2 : 1; }
+constexpr int max_level(int nc) { return nc == 1 ? 3 : 2; }
 
 constexpr int lvl_n(int l) { return 2 << l; }
 constexpr int lvl_nodes(int l) { return (lvl_n(l) + 1) * (lvl_n(l) + 1) * (lvl_n(l) + 1); }
@@ -90,9 +91,45 @@ constexpr int axis_nbr(int q) { return q == 0 ? 0 : q < 4 ? 1 << (q - 1) : 7 + (
 constexpr int term_nbr(int t) { return t < 7 ? axis_nbr(t) : (t - 7) % kStencilPoints; }
 constexpr int term_comp(int t) { return t < 7 ? 0 : 1 + (t - 7) / kStencilPoints; }
 
+// term of neighbour k (kuhn.h) and component d of a row of component c
+constexpr int term_of(int k, int d, int c) {
+    const int rel = (d - c + 3) % 3;
+    if (rel > 0) return 7 + (rel - 1) * kStencilPoints + k;
+    for (int q = 0; q < 7; ++q)
+        if (axis_nbr(q) == k) return q;
+    return -1;
+}
+
+// the entries of the row (C, p) of the vector operator from the coefficient, in FP64: the
+// assembly of k_stencil.hip, in its order
+template <int C, int LV>
+__device__ __forceinline__ void assemble_row(const double* __restrict__ nu, int p, double (&acc)[37]) {
+    constexpr int n = lvl_n(LV), n1 = n + 1;
+    const double scale = 1.0 / (6.0 * n);
+    const int z = p / (n1 * n1), r = p - z * n1 * n1, y = r / n1, x = r - y * n1;
+#pragma unroll
+    for (int t = 0; t < 37; ++t) acc[t] = 0.0;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        const int cell = x - (k & 1) + n * (y - ((k >> 1) & 1) + n * (z - (k >> 2)));
+#pragma unroll
+        for (int s = 0; s < 6; ++s)
+#pragma unroll
+            for (int a = 0; a < 4; ++a) {
+                if (path_corner(s, a) != k) continue;
+                const double w = nu[elem_slot(s, cell, n * n * n)] * scale;
+#pragma unroll
+                for (int b = 0; b < 4; ++b)
+#pragma unroll
+                    for (int d = 0; d < 3; ++d)
+                        if (unit_entry(s, C, a, d, b) != 0)
+                            acc[term_of(nbr_of(s, a, b), d, C)] += w * (double)unit_entry(s, C, a, d, b);
+            }
+    }
+}
+
 // the entries of row (c, p): scalar, the weights of the edges to x-1, x+1, y-1, y+1, z-1, z+1;
-// vector, the terms of the stencil row.  put(t, value) for each; a scalar base and one 32-bit
-// offset per component keep the 37 loads' addresses out of the registers.
+// vector, the terms of the stencil row.  put(t, value) for each.
 template <int NC, typename T, int LV, typename P>
 __device__ __forceinline__ void load_row(const CoarseCycle<T>& a, int addr, const P& put) {
     constexpr unsigned n1 = lvl_n(LV) + 1, N = lvl_nodes(LV);
@@ -103,15 +140,16 @@ __device__ __forceinline__ void load_row(const CoarseCycle<T>& a, int addr, cons
             put(t, a.wts[LV][ax * N + (unsigned)addr - ((t & 1) ? 0u : step)]);
         }
     } else {
-        const unsigned c = (unsigned)addr / N, p = (unsigned)addr - c * N;
-        unsigned first[3];
+        const int c = addr / (int)N, p = addr - c * (int)N;
+        double e[37];
+        if (c == 0)
+            assemble_row<0, LV>(a.nu[LV], p, e);
+        else if (c == 1)
+            assemble_row<1, LV>(a.nu[LV], p, e);
+        else
+            assemble_row<2, LV>(a.nu[LV], p, e);
 #pragma unroll
-        for (unsigned j = 0; j < 3; ++j) first[j] = (c * NC + (c + j) % NC) * kStencilPoints * N + p;
-#pragma unroll
-        for (int t = 0; t < row_terms(NC); ++t) {
-            put(t, (a.sten[LV] + term_nbr(t) * N)[first[term_comp(t)]]);
-            if (t % 8 == 7) asm volatile("" ::: "memory");  // FP64 spills without
-        }
+        for (int t = 0; t < row_terms(NC); ++t) put(t, T(e[t]));
     }
 }
 
@@ -161,6 +199,13 @@ struct LevelCycle {
     // the thread's rows; the operator rows that live in LDS are copied there
     __device__ __forceinline__ void init(const CoarseCycle<T>& a, T* lds) {
         const int tid = threadIdx.x;
+        constexpr int LR = lds_rows(NC, sizeof(T), LV, K);
+        if constexpr (LR > 0) {
+            T* S = lds + s_offset(NC, sizeof(T), LV, K);
+            for (int i = tid; i < LR; i += CT) {
+                load_row<NC, T, LV>(a, row_addr<NC, LV>(i + (ROWS - LR)), [&](int t, T v) { S[t * LR + i] = v; });
+            }
+        }
 #pragma unroll
         for (int s = 0; s < SLOTS; ++s) {
             // rows past the last repeat row 0; their results are never stored
@@ -168,13 +213,6 @@ struct LevelCycle {
             d[s] = a.dinv[LV][addr[s]];
             b[s] = cur[s] = prv[s] = T(0);
             if (s < REG) load_row<NC, T, LV>(a, addr[s], [&](int t, T v) { w[s < REG ? s : 0][t] = v; });
-        }
-        constexpr int LR = lds_rows(NC, sizeof(T), LV, K);
-        if constexpr (LR > 0) {
-            T* S = lds + s_offset(NC, sizeof(T), LV, K);
-            for (int i = tid; i < LR; i += CT) {
-                load_row<NC, T, LV>(a, row_addr<NC, LV>(i + (ROWS - LR)), [&](int t, T v) { S[t * LR + i] = v; });
-            }
         }
     }
     __device__ __forceinline__ T product(const T* lds, const T* u, int s) const {
@@ -276,8 +314,8 @@ struct Levels {
     LevelCycle<NC, T, K, LV> top;
     Levels<NC, T, K, LV - 1> lower;
     __device__ __forceinline__ void init(const CoarseCycle<T>& a, T* lds) {
+        lower.init(a, lds);  // the top level's rows fill the registers: last
         top.init(a, lds);
-        lower.init(a, lds);
     }
     __device__ __forceinline__ void take(const T* r) { top.restrict_from(r); }
     __device__ __forceinline__ const T* cycle(const CoarseCycle<T>& a, T* lds) { return top.run(a, lds, lower); }
@@ -338,14 +376,9 @@ template <int NC, typename T>
 hipError_t launch_k(int K, const CoarseCycle<T>& a, hipStream_t st) {
     switch (K) {
         case 1: hipLaunchKernelGGL((k_coarse_cycle<NC, T, 1>), dim3(1), dim3(ct(NC, sizeof(T))), 0, st, a); break;
-        case 2:
-            if constexpr (max_level(NC, sizeof(T)) >= 2) {
-                hipLaunchKernelGGL((k_coarse_cycle<NC, T, 2>), dim3(1), dim3(ct(NC, sizeof(T))), 0, st, a);
-                break;
-            }
-            return hipErrorInvalidValue;
+        case 2: hipLaunchKernelGGL((k_coarse_cycle<NC, T, 2>), dim3(1), dim3(ct(NC, sizeof(T))), 0, st, a); break;
         case 3:
-            if constexpr (max_level(NC, sizeof(T)) >= 3) {
+            if constexpr (max_level(NC) >= 3) {
                 hipLaunchKernelGGL((k_coarse_cycle<NC, T, 3>), dim3(1), dim3(ct(NC, sizeof(T))), 0, st, a);
                 break;
             }
@@ -357,15 +390,15 @@ hipError_t launch_k(int K, const CoarseCycle<T>& a, hipStream_t st) {
 
 }  // namespace
 
-int coarse_cycle_max_level(int ncomp, size_t elem) { return max_level(ncomp, elem); }
+int coarse_cycle_max_level(int ncomp) { return max_level(ncomp); }
 
 template <typename T>
 hipError_t launch_coarse_cycle(int ncomp, int K, const CoarseCycle<T>& a, hipStream_t st) {
-    if ((ncomp != 1 && ncomp != 3) || K < 1 || K > max_level(ncomp, sizeof(T))) return hipErrorInvalidValue;
+    if ((ncomp != 1 && ncomp != 3) || K < 1 || K > max_level(ncomp)) return hipErrorInvalidValue;
     if (a.pre < 0 || a.post < 0 || a.pre > kCyclePasses || a.post > kCyclePasses) return hipErrorInvalidValue;
     if (!a.ainv || !a.b || !a.x) return hipErrorInvalidValue;
     for (int l = 1; l <= K; ++l)
-        if (!(ncomp == 1 ? a.wts[l] : a.sten[l]) || !a.dinv[l]) return hipErrorInvalidValue;
+        if ((ncomp == 1 ? !a.wts[l] : !a.nu[l]) || !a.dinv[l]) return hipErrorInvalidValue;
     return ncomp == 1 ? launch_k<1, T>(K, a, st) : launch_k<3, T>(K, a, st);
 }
 
