@@ -169,7 +169,7 @@ int32_t agca_get_blocks(const agca_hier* h, int32_t level, double* blocks_host, 
 int32_t agca_get_diagonal(const agca_hier* h, int32_t level, double* diag_host, int64_t cap);
 
 /* v = A_l u (eq. (2.3) on the finest level, eq. (2.9) on coarser levels).
- * dtype AGCA_F64 uses the FP64 coefficients and blocks; AGCA_F32 needs
+ * dtype AGCA_F64 uses the FP64 coefficients; AGCA_F32 needs
  * mg_dtype == AGCA_F32 and uses the V-cycle's copies.  u, v: device level vectors. */
 int32_t agca_apply(agca_hier* h, int32_t level, int32_t dtype, const void* u, void* v);
 

@@ -574,7 +574,7 @@ int32_t reduce_to(agca_hier* h, const double* partial, int nb, int slot) {
 }
 // the same as a scalar for the kernel that uses it: summed there (and kept in red[slot]) while
 // the partials are few enough for each of its workgroups to read
-constexpr int kScalarPartials = 4096;
+constexpr int kScalarPartials = 2048;
 int32_t scalar_of(agca_hier* h, const double* partial, int nb, int slot, DevScalar* s) {
     if (nb <= kScalarPartials) {
         *s = DevScalar{partial, nb, h->red + slot};
