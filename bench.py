@@ -51,7 +51,7 @@ MILESTONES = (1e-5, 1e-6, 1e-7)
 # reported while their hash equals the one recorded next to the counters
 KERNEL_SOURCES = ["paper_2511_13109_amd/csrc/k_apply.hip", "paper_2511_13109_amd/csrc/kuhn.h",
                   "paper_2511_13109_amd/csrc/cube_math.h"]
-FINE_APPLY_KERNEL = "k_cube<3, double, double, 0, false>"
+FINE_APPLY_KERNEL = "k_cube<3, double, double, 0>"
 
 
 def apply_bytes(L: int, ncomp: int, vec_bytes: int = 8, nu_bytes: int = 8) -> int:
@@ -102,19 +102,17 @@ def _vec(vb: int, nvec: int, nc: int = 3) -> int:
 
 
 SOLVER_KERNEL_BYTES = {
-    # k_cube<ncomp, vector type, coefficient type, mode, blocks>: mode 0 apply (u in, v out),
-    # 1 residual (+b), 2 Jacobi-type pass (u, b, D^-1 in, out), 3 apply + dot, 4 first two
-    # passes from zero (b, D^-1 in, out), 5 Chebyshev pass (+ previous iterate)
-    "k_cube<3, double, double, 0, false>": ("apply", _vec(8, 2), 48),
-    "k_cube<3, double, double, 1, false>": ("residual", _vec(8, 3), 48),
-    "k_cube<3, double, double, 2, false>": ("Jacobi-type pass", _vec(8, 4), 48),
-    "k_cube<3, double, double, 3, false>": ("apply + p.Ap", _vec(8, 2), 48),
-    "k_cube<3, double, double, 4, false>": ("first two passes", _vec(8, 3), 48),
-    "k_cube<3, double, double, 5, false>": ("Chebyshev pass", _vec(8, 5), 48),
-    "k_cube<3, float, unsigned short, 1, false>": ("FP32/BF16 residual", _vec(4, 3), 12),
-    "k_cube<3, float, unsigned short, 2, false>": ("FP32/BF16 Jacobi-type pass", _vec(4, 4), 12),
-    "k_cube<3, float, unsigned short, 4, false>": ("FP32/BF16 first two passes", _vec(4, 3), 12),
-    "k_cube<3, float, unsigned short, 5, false>": ("FP32/BF16 Chebyshev pass", _vec(4, 5), 12),
+    # the kernels that run on the finest level with two passes before and after the correction;
+    # k_cube<ncomp, vector type, coefficient type, mode>: mode 0 apply (u in, v out),
+    # 1 residual (+b), 3 apply + dot
+    "k_cube<3, double, double, 0>": ("apply", _vec(8, 2), 48),
+    "k_cube<3, double, double, 1>": ("residual", _vec(8, 3), 48),
+    "k_cube<3, double, double, 3>": ("apply + p.Ap", _vec(8, 2), 48),
+    # two products per pass: b, D^-1 in, x, r out; x, b, D^-1 in, x out (+ the coarse correction)
+    "k_smooth2<3, double, double, true>": ("two passes and residual", _vec(8, 4), 48),
+    "k_smooth2<3, double, double, false>": ("correction and two passes", _vec(8, 4), 48),
+    "k_smooth2<3, float, unsigned short, true>": ("FP32/BF16 two passes and residual", _vec(4, 4), 12),
+    "k_smooth2<3, float, unsigned short, false>": ("FP32/BF16 correction and two passes", _vec(4, 4), 12),
     "k_cg_update": ("x += a p, r -= a q, r.r (mixed: + FP32 r)", 3 * 6 * 8, 0),
     "k_dot2<double>": ("z.r, z.q (PCG)", 3 * 24, 0),
     "k_dot2<float>": ("z.r, z.q (FCG, FP32 z)", 3 * 20, 0),
@@ -123,8 +121,6 @@ SOLVER_KERNEL_BYTES = {
     # per fine node; the coarse vector (1/8 of the nodes) is added below
     "k_restrict<3, double>": ("restriction to the next coarser level", 3 * 8, 0),
     "k_restrict<3, float>": ("restriction to the next coarser level, FP32", 3 * 4, 0),
-    "k_prolong_add<3, double>": ("prolongation from the next coarser level", 3 * 16, 0),
-    "k_prolong_add<3, float>": ("prolongation from the next coarser level, FP32", 3 * 8, 0),
     "k_floor_terms<3>": ("rounding floor terms (|b| + sum |A_e||x_e|)", 3 * 16, 48),
 }
 
