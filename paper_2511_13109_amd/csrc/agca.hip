@@ -484,26 +484,20 @@ int32_t do_vcycle(agca_hier* h, const T* bL, T* xL) {
         CoarseCycle<T> cc;
         cc.pre = pre;
         cc.post = post;
+        cc.cheb = cheb;
         for (int l = 1; l <= K; ++l) {
             const LevelOp<T> op = level_op<T>(h, l);
             cc.nu[l] = h->lv[l].nu64;
             cc.wts[l] = op.wts;
             cc.dinv[l] = op.dinv;
-            cc.first_omega[l] = cheb ? T(1.0 / Cheb(h->lam[l]).theta) : om;
-            for (int k = 0; k < kCyclePasses; ++k) {
+            // a pass k has the same coefficients before and after the correction, but for pass 1
+            // before it, whose x_prev is zero there
+            for (int k = 0; k < std::max(1, std::max(pre, post)); ++k) {
                 Sweep<T> sw;
-                if (k >= 1 && k < pre) {
-                    cc.pre_mode[l][k] = (int8_t)smooth_pass_coef<T>(h, l, true, k, nullptr, &sw);
-                    cc.pre_c[l][k][0] = sw.alpha;
-                    cc.pre_c[l][k][1] = sw.gamma;
-                    cc.pre_c[l][k][2] = sw.omega;
-                }
-                if (k < post) {
-                    cc.post_mode[l][k] = (int8_t)smooth_pass_coef<T>(h, l, false, k, nullptr, &sw);
-                    cc.post_c[l][k][0] = sw.alpha;
-                    cc.post_c[l][k][1] = sw.gamma;
-                    cc.post_c[l][k][2] = sw.omega;
-                }
+                (void)smooth_pass_coef<T>(h, l, false, k, nullptr, &sw);
+                cc.c[l - 1][k][0] = sw.alpha;
+                cc.c[l - 1][k][1] = sw.gamma;
+                cc.c[l - 1][k][2] = sw.omega;
             }
         }
         cc.ainv = h->ainv0;

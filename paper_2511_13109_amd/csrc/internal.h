@@ -103,26 +103,30 @@ hipError_t launch_coarse_solve(int ncomp, const double* ainv, const T* b, T* x, 
 // The coarse end of a V-cycle in one workgroup (k_coarse_cycle.hip): levels K..1 (level l with
 // n = 2^(l+1) cells) and the level-0 solve, from the level-K right-hand side b to the
 // level-K iterate x, boundary slots included.  Smoothing passes as in the per-launch V-cycle:
-// pre-smoothing pass 0 is x = first_omega D^-1 b from zero (0 when pre = 0), pre passes 1..
-// and post passes 0.. write x_out = alpha x + gamma x_prev + omega D^-1 (b - A x) with the
-// mode and coefficients given per level and pass (MODE_JACOBI ignores gamma).
+// pass k of a phase writes x_out = alpha x + gamma x_prev + omega D^-1 (b - A x) with the
+// coefficients c[l - 1][k] = (alpha, gamma, omega), gamma counting from pass 1 of a Chebyshev phase
+// on; pass 0 before the correction starts from zero, x = omega D^-1 b (x = 0 when pre = 0), with
+// x_prev = 0 after it.
+//
+// One set of coefficients serves both phases because the argument block has to be small: with
+// 1.8 KB of arguments (two sets, FP64) the launch call of a first cycle after a rebuild took 58 us
+// on the host (9^3 scalar, median of 40 new hierarchies; 17^3 19 us, one in ten 79), against 7 us
+// in a loop and 7 with the present 0.7 KB.
 constexpr int kCycleLevels = 3;  // K <= 3
 constexpr int kCyclePasses = 8;  // pre, post <= 8
 template <typename T>
 struct CoarseCycle {
     int pre = 0, post = 0;
+    int cheb = 0;
     const double* nu[kCycleLevels + 1] = {};  // vector: coefficient
     const T* wts[kCycleLevels + 1] = {};      // scalar: edge weights
     const T* dinv[kCycleLevels + 1] = {};
-    T first_omega[kCycleLevels + 1] = {};
-    int8_t pre_mode[kCycleLevels + 1][kCyclePasses] = {};
-    int8_t post_mode[kCycleLevels + 1][kCyclePasses] = {};
-    T pre_c[kCycleLevels + 1][kCyclePasses][3] = {};   // alpha, gamma, omega
-    T post_c[kCycleLevels + 1][kCyclePasses][3] = {};
-    const double* ainv = nullptr;  // level-0 inverse, ncomp x ncomp
+    T c[kCycleLevels][kCyclePasses][3] = {};
+    const double* ainv = nullptr;  // level-0 inverse (row major)
     const T* b = nullptr;          // level K, ncomp (n+1)^3 values (device)
     T* x = nullptr;                // level K, written
 };
+static_assert(sizeof(CoarseCycle<double>) <= 768, "see above");
 int coarse_cycle_max_level(int ncomp);  // the largest K
 template <typename T>
 hipError_t launch_coarse_cycle(int ncomp, int K, const CoarseCycle<T>& a, hipStream_t st);

@@ -228,12 +228,12 @@ struct LevelCycle {
             if (has(s)) u[addr[s]] = cur[s];
     }
     // x <- alpha x + gamma x_prev + omega D^-1 (b - A x), from buffer u into buffer v
-    __device__ __forceinline__ void pass(T* lds, const T* u, T* v, int8_t mode, const T (&c)[3]) {
+    __device__ __forceinline__ void pass(T* lds, const T* u, T* v, bool cheb, const T (&c)[3]) {
 #pragma unroll
         for (int s = 0; s < SLOTS; ++s) {
             if (!has(s)) continue;
             const T r = b[s] - product(lds, u, s);
-            const T nx = fma(c[2] * d[s], r, mode == MODE_CHEB ? fma(c[1], prv[s], c[0] * cur[s]) : c[0] * cur[s]);
+            const T nx = fma(c[2] * d[s], r, cheb ? fma(c[1], prv[s], c[0] * cur[s]) : c[0] * cur[s]);
             prv[s] = cur[s];
             cur[s] = nx;
             // two scalar rows' reads in flight
@@ -252,13 +252,13 @@ struct LevelCycle {
         T* v = u + VEC;
 #pragma unroll
         for (int s = 0; s < SLOTS; ++s) {
-            cur[s] = a.pre > 0 ? a.first_omega[LV] * d[s] * b[s] : T(0);
+            cur[s] = a.pre > 0 ? a.c[LV - 1][0][2] * d[s] * b[s] : T(0);
             prv[s] = T(0);
         }
         put(u);
         __syncthreads();
         for (int k = 1; k < a.pre; ++k) {
-            pass(lds, u, v, a.pre_mode[LV][k], a.pre_c[LV][k]);
+            pass(lds, u, v, a.cheb != 0, a.c[LV - 1][k]);
             T* t = u; u = v; v = t;
         }
         // residual into the free buffer, restricted by the rows' owners on the level below
@@ -283,7 +283,7 @@ struct LevelCycle {
         put(u);
         __syncthreads();
         for (int k = 0; k < a.post; ++k) {
-            pass(lds, u, v, a.post_mode[LV][k], a.post_c[LV][k]);
+            pass(lds, u, v, a.cheb != 0 && k > 0, a.c[LV - 1][k]);
             T* t = u; u = v; v = t;
         }
         return u;
