@@ -63,6 +63,9 @@ struct Smooth2 {
     T* out = nullptr;
     T* r = nullptr;
     T om0 = T(0), a1 = T(1), o1 = T(0), a2 = T(1), g2 = T(0), o2 = T(0);
+    // pre: the factor of x1 with the term o1 D^-1 b taken as o1 / om0 x1 (a damping that is zero in
+    // T makes x1 and that term zero)
+    T first() const { return om0 != T(0) ? a1 + o1 / om0 : a1; }
 };
 template <typename T>
 hipError_t launch_smooth2(int ncomp, bool pre, const LevelOp<T>& op, const Smooth2<T>& a, hipStream_t st);

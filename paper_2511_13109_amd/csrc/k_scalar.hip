@@ -450,7 +450,7 @@ hipError_t launch_two(int n, const T* W, const T* dinv, const Smooth2<T>& a, hip
     const int gx = (n + OX) / OX, gy = (n + OY) / OY;
     const int gz = pick_chunks(n, (int64_t)gx * gy, fit.first, fit.second);
     hipLaunchKernelGGL((k_two7<T, PRE>), dim3((unsigned)(gx * gy * gz)), dim3(NTH), 0, st, n, (n + gz) / gz, gx, gy, gz,
-                       a.x, a.e, W, a.b, dinv, a.out, a.r, a.om0, PRE ? a.a1 + a.o1 / a.om0 : a.a1, a.o1, a.a2, a.g2, a.o2);
+                       a.x, a.e, W, a.b, dinv, a.out, a.r, a.om0, PRE ? a.first() : a.a1, a.o1, a.a2, a.g2, a.o2);
     return hipGetLastError();
 }
 

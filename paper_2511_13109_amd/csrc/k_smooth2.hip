@@ -342,7 +342,7 @@ hipError_t launch_t(const LevelOp<T>& op, const Smooth2<T>& a, hipStream_t st) {
     const int gz = pick_chunks(n, (int64_t)gx * gy, fit.first, fit.second);
     const int zc = (n + gz) / gz;
     hipLaunchKernelGGL((k_smooth2<NC, T, NT, PRE>), dim3((unsigned)(gx * gy * gz)), dim3(NTH), 0, st, n, zc, gx, gy, gz, a.x, a.e, reinterpret_cast<const NT*>(op.nu), a.b, op.dinv, a.out, a.r, T(1.0 / (6.0 * n)), a.om0,
-                       PRE ? a.a1 + a.o1 / a.om0 : a.a1, a.o1, a.a2, a.g2, a.o2);
+                       PRE ? a.first() : a.a1, a.o1, a.a2, a.g2, a.o2);
     return hipGetLastError();
 }
 
