@@ -36,8 +36,8 @@ struct Level {
     // finest: nu_L; coarse: the level operator's coefficient, the caller's DCA value on
     // unflagged elements and the descendant mean of nu_L on flagged ones
     double* nu64 = nullptr;
-    float* nu32 = nullptr;       // FP32 copy (FP32 V-cycle)
-    uint16_t* nubf = nullptr;    // BF16 copy of the finest coefficient (FP32 V-cycle option)
+    float* nu32 = nullptr;       // FP32 copy (FP32 V-cycle), times nu_copy_factor
+    uint16_t* nubf = nullptr;    // BF16 copy of the finest coefficient (FP32 V-cycle option), times nu_copy_factor
     int32_t* flag = nullptr;     // by element id
     int32_t* blk = nullptr;      // by element id: flagged element's index or -1
     int32_t* ids = nullptr;
@@ -219,6 +219,7 @@ LevelOp<double> level_op<double>(const agca_hier* h, int l) {
     op.n = L.n;
     op.nu = L.nu64;
     op.nu_kind = AGCA_F64;
+    op.scale = nu_scale(L.n, false);
     op.dinv = L.dinv64;
     op.sten = L.sten64;
     op.wts = L.w64;
@@ -236,6 +237,7 @@ LevelOp<float> level_op<float>(const agca_hier* h, int l) {
         op.nu = L.nu32;
         op.nu_kind = AGCA_F32;
     }
+    op.scale = nu_scale(L.n, true);
     op.dinv = L.dinv32;
     op.sten = L.sten32;
     op.wts = L.w32;
@@ -996,9 +998,9 @@ int32_t build_operators(agca_hier* h, const double* nu_fine, const double* const
             HIPCHK(h, launch_invert_diag<float>(cnt, lv.diag, lv.dinv32, h->st));
             // the finest level holds either an FP32 or a BF16 copy, coarse levels an FP32 one
             if (l == L && h->cfg.mg_nu_dtype == AGCA_BF16)
-                HIPCHK(h, launch_cast(AGCA_F64, AGCA_BF16, lv.nu64, lv.nubf, lv.elems, h->st));
+                HIPCHK(h, launch_cast(AGCA_F64, AGCA_BF16, lv.nu64, lv.nubf, lv.elems, h->st, nu_copy_factor(lv.n)));
             else
-                HIPCHK(h, launch_cast(AGCA_F64, AGCA_F32, lv.nu64, lv.nu32, lv.elems, h->st));
+                HIPCHK(h, launch_cast(AGCA_F64, AGCA_F32, lv.nu64, lv.nu32, lv.elems, h->st, nu_copy_factor(lv.n)));
         } else {
             HIPCHK(h, launch_invert_diag<double>(cnt, lv.diag, lv.dinv64, h->st));
         }

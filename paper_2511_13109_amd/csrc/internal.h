@@ -17,10 +17,17 @@ struct LevelOp {
     int n = 0;                 // cells per axis
     const void* nu = nullptr;  // 6 n^3 coefficients, internal layout (T, or uint16 bf16 bits)
     int nu_kind = 0;           // AGCA_F64 / AGCA_F32 / AGCA_BF16 storage of nu
+    double scale = 0.0;        // nu * scale = coefficient * h/6
     const T* dinv = nullptr;       // inverse Jacobi diagonal, level vector (0 on the boundary)
     const T* sten = nullptr;       // assembled stencil (k_stencil.hip layout) or null
     const T* wts = nullptr;        // scalar: edge weights (k_scalar.hip layout) or null
 };
+
+// The FP32 and BF16 copies of a coefficient hold nu / (8 n): a power of two, so they round as nu
+// does, and near h/6 = 1 / (6 n) of eq. (2.3), so that a product formed with the copy, h/6 left for
+// its result (k_smooth2.hip), overflows no sooner than one formed with nu h/6.
+inline double nu_copy_factor(int n) { return 1.0 / (8.0 * n); }
+inline double nu_scale(int n, bool copy) { return copy ? 4.0 / 3.0 : 1.0 / (6.0 * n); }
 
 // MODE_JACOBI0: two passes from a zero guess: the input x = omega0 D^-1 b is formed on
 //               the fly (u unused; element loop only)
@@ -75,7 +82,7 @@ hipError_t launch_smooth2(int ncomp, bool pre, const LevelOp<T>& op, const Smoot
 // MODE_CHEB); v = A u with partial sums of u . v (product7_blocks(n) of them); two products
 // in one pass (launch_smooth2)
 template <typename T>
-hipError_t launch_weights(int n, const double* nu, const uint16_t* nu_bf16, T* W, hipStream_t st);
+hipError_t launch_weights(int n, const double* nu, const uint16_t* nu_bf16, T* W, hipStream_t st);  // nu_bf16: times nu_copy_factor
 template <typename T>
 hipError_t launch_product7(int mode, int n, const T* W, const T* u, const T* b, const T* dinv, T* out,
                            const Sweep<T>& sw, hipStream_t st);
@@ -169,7 +176,8 @@ hipError_t launch_dot2(int64_t n, const Z* z, const double* r, const double* q, 
 // p = z + beta p (beta = 0 overwrites p without reading it)
 template <typename Z>
 hipError_t launch_zpbp(int64_t n, const Z* z, double beta, double* p, hipStream_t st);
-hipError_t launch_cast(int from, int to, const void* src, void* dst, int64_t n, hipStream_t st);
+// dst = src rounded to the type `to` (FP64 sources times f first)
+hipError_t launch_cast(int from, int to, const void* src, void* dst, int64_t n, hipStream_t st, double f = 1.0);
 // Lanczos step with device coefficients: w = y / d - alpha v - sqrt(beta2) u (no u
 // term when u is null), partial sums of w . (d w) over nblocks workgroups
 hipError_t launch_lanczos_step(int64_t n, const double* y, const double* d, const double* v,

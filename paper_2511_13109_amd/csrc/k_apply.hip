@@ -474,7 +474,7 @@ hipError_t launch_t(const LevelOp<T>& op, const T* u, const T* b, T* out, const 
     const int nwg = (g.gx * g.gy + g.gs) * gz;
     const dim3 block = CubeStrip<MODE>::value ? dim3(NTHREADS, 1, 1) : dim3(TX, TY, 1);
     dim3 grid((unsigned)nwg, 1, 1);
-    const T scale = T(1.0 / (6.0 * n));
+    const T scale = T(op.scale);
     static const bool xcd_map = [] {
         const char* e = getenv("AGCA_CUBE_XCD");
         return e ? atoi(e) != 0 : true;

@@ -462,9 +462,9 @@ hipError_t launch_weights(int n, const double* nu, const uint16_t* nu_bf16, T* W
     const int64_t N = (int64_t)(n + 1) * (n + 1) * (n + 1);
     const dim3 g((unsigned)((N + NT - 1) / NT));
     if (nu_bf16)
-        hipLaunchKernelGGL((k_weights<uint16_t, T>), g, dim3(NT), 0, st, n, nu_bf16, 1.0 / (6.0 * n), W);
+        hipLaunchKernelGGL((k_weights<uint16_t, T>), g, dim3(NT), 0, st, n, nu_bf16, nu_scale(n, true), W);
     else
-        hipLaunchKernelGGL((k_weights<double, T>), g, dim3(NT), 0, st, n, nu, 1.0 / (6.0 * n), W);
+        hipLaunchKernelGGL((k_weights<double, T>), g, dim3(NT), 0, st, n, nu, nu_scale(n, false), W);
     return hipGetLastError();
 }
 

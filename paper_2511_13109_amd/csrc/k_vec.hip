@@ -285,15 +285,15 @@ __device__ __forceinline__ uint16_t f64_to_bf16(double x) {
 }
 
 __global__ void __launch_bounds__(NT)
-k_cast(int from, int to, const void* __restrict__ src, void* __restrict__ dst, int64_t n) {
+k_cast(int from, int to, const void* __restrict__ src, void* __restrict__ dst, int64_t n, double f) {
     const int64_t stride = (int64_t)gridDim.x * NT;
     for (int64_t i = blockIdx.x * (int64_t)NT + threadIdx.x; i < n; i += stride) {
         if (from == AGCA_F64 && to == AGCA_F32)
-            static_cast<float*>(dst)[i] = (float)static_cast<const double*>(src)[i];
+            static_cast<float*>(dst)[i] = (float)(f * static_cast<const double*>(src)[i]);
         else if (from == AGCA_F32 && to == AGCA_F64)
             static_cast<double*>(dst)[i] = (double)static_cast<const float*>(src)[i];
         else if (from == AGCA_F64 && to == AGCA_BF16)
-            static_cast<uint16_t*>(dst)[i] = f64_to_bf16(static_cast<const double*>(src)[i]);
+            static_cast<uint16_t*>(dst)[i] = f64_to_bf16(f * static_cast<const double*>(src)[i]);
         else if (from == AGCA_F64 && to == AGCA_F64)
             static_cast<double*>(dst)[i] = static_cast<const double*>(src)[i];
         else if (from == AGCA_F32 && to == AGCA_F32)
@@ -650,10 +650,10 @@ hipError_t launch_scale_rsqrt(int64_t n, const double* x, DevScalar s, double* o
     hipLaunchKernelGGL(k_scale_rsqrt, dim3(nblocks), dim3(NT), 0, st, n, x, s, out);
     return hipGetLastError();
 }
-hipError_t launch_cast(int from, int to, const void* src, void* dst, int64_t n, hipStream_t st) {
+hipError_t launch_cast(int from, int to, const void* src, void* dst, int64_t n, hipStream_t st, double f) {
     if (n <= 0) return hipSuccess;
     if (!src || !dst) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_cast, dim3(grid_stride(n)), dim3(NT), 0, st, from, to, src, dst, n);
+    hipLaunchKernelGGL(k_cast, dim3(grid_stride(n)), dim3(NT), 0, st, from, to, src, dst, n, f);
     return hipGetLastError();
 }
 template <typename T>

@@ -9,9 +9,10 @@ from workloads import Sinkers
 pytestmark = pytest.mark.gpu
 
 
-def _make(L, ncomp, nud, **kw):
+def _make(L, ncomp, nud, factor=1.0, **kw):
     from paper_2511_13109_amd import Hierarchy, coefficients_from_field
     nu = coefficients_from_field(Sinkers(4, 2, radius=0.15, width=2.0 / 2 ** (L + 1), contrast=1e4), L)
+    nu = [v * factor for v in nu]
     H = Hierarchy(L, ncomp, nu[L], nu[:L], mg_dtype="f32", mg_nu_dtype=nud, **kw)
     n1 = H.n(L) + 1
     g = torch.Generator(device="cuda")
@@ -46,5 +47,29 @@ def test_damping_below_fp32(ncomp, nud):
         err = float((z.double() - x.double()).abs().max() / x.double().abs().max())
         print(f"error {err:.2e}", flush=True)
         assert err <= 2e-5
+    finally:
+        H.close()
+
+
+@pytest.mark.parametrize("L,ncomp,nud", [(4, 1, "f32"), (4, 3, "f32"), (6, 1, "bf16"), (6, 3, "f32"), (6, 3, "bf16")])
+def test_large_right_hand_side(L, ncomp, nud):
+    """One entry of 2^124: the sums of A x are of that size, but 6 n times larger without the factor h/6
+    of the element matrices, beyond the largest FP32 number 2^128.  Powers of two are exact: the cycle of
+    2^k b is 2^k times that of b, bit for bit."""
+    print(f"\n[large right-hand side L={L} ncomp={ncomp} {nud}]", flush=True)
+    # the coefficient at least 2^9: no iterate is larger than b
+    H, b = _make(L, ncomp, nud, factor=2.0 ** 16, smoother="chebyshev")
+    try:
+        n1 = H.n(L) + 1
+        b.zero_()
+        m = n1 // 2 - 3
+        b.view(ncomp, n1, n1, n1)[-1, m, m, m] = 1.0
+        z = H.vcycle(b)
+        big = H.vcycle(b * 2.0 ** 124)
+        print(f"max {float(big.abs().max()):.3e}", flush=True)
+        assert torch.isfinite(big).all()
+        # entries below the normal range of the small cycle aside
+        normal = z.abs() >= 2.0 ** -126
+        assert torch.equal(big[normal], z[normal] * 2.0 ** 124)
     finally:
         H.close()
