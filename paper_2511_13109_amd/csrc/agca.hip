@@ -80,7 +80,6 @@ struct agca_hier {
     double* s_q = nullptr;
     float* s_r32 = nullptr;
     float* s_z32 = nullptr;
-    double* trans[2] = {nullptr, nullptr};
     // Stokes (velocity: finest level, pressure: level L-1)
     std::vector<double> lam;     // Chebyshev: eigenvalue estimate of D^-1 A per level
     int64_t nu_version = 0;      // bumped by every coefficient rebuild
@@ -828,6 +827,65 @@ int32_t build_coarsest(agca_hier* h) {
     return AGCA_OK;
 }
 
+// Storage of a level's Galerkin blocks, and its release (the blocks are formed again when they are
+// read next).
+int32_t block_storage(agca_hier* h, Level& lv) {
+    const int M = 4 * h->cfg.ncomp;
+    if (lv.blocks64 || lv.nblk == 0) return AGCA_OK;
+    return alloc_t(h, &lv.blocks64, (size_t)lv.nblk * M * M, &lv.bytes);
+}
+bool free_blocks(agca_hier* h) {
+    bool any = false;
+    for (Level& lv : h->lv) {
+        if (!lv.blocks64) continue;
+        any = true;
+        const int64_t freed = lv.nblk * 16 * h->cfg.ncomp * h->cfg.ncomp * (int64_t)sizeof(double);
+        forget_alloc(h, lv.blocks64);
+        (void)hipFree(lv.blocks64);
+        h->bytes -= freed;
+        lv.bytes -= freed;
+        lv.blocks64 = nullptr;
+    }
+    h->blocks_version = -1;
+    return any;
+}
+
+// Device memory for the length of a call, outside mem_limit_bytes.  Where there is none left, what
+// the hierarchy can do without is given up: the edge weights, then (in a rebuild, which
+// makes them void) the stored blocks.
+class Transients {
+public:
+    explicit Transients(agca_hier* h, bool keep_blocks = false) : h_(h), keep_blocks_(keep_blocks) {}
+    Transients(const Transients&) = delete;
+    Transients& operator=(const Transients&) = delete;
+    ~Transients() { release(); }
+    int32_t take(void** p, size_t bytes) {
+        hipError_t e = hipMalloc(p, bytes);
+        while (e == hipErrorOutOfMemory && (drop_weights(h_) || (!keep_blocks_ && free_blocks(h_)))) {
+            (void)hipGetLastError();
+            e = hipMalloc(p, bytes);
+        }
+        if (e != hipSuccess) {
+            *p = nullptr;
+            (void)hipGetLastError();
+            return fail(AGCA_E_OOM, "transient hipMalloc(" + std::to_string(bytes) + ") failed: " + hipGetErrorString(e));
+        }
+        held_.push_back(*p);
+        return AGCA_OK;
+    }
+    void release() {
+        if (held_.empty()) return;
+        (void)hipStreamSynchronize(h_->st);
+        for (void* p : held_) (void)hipFree(p);
+        held_.clear();
+    }
+
+private:
+    agca_hier* h_;
+    bool keep_blocks_;
+    std::vector<void*> held_;
+};
+
 // The stored Galerkin blocks, bottom-up by the recursion (2.7) from the finest coefficient:
 // formed when they are first read after a rebuild (the operators use the equal mean
 // coefficients and never read them).
@@ -848,44 +906,31 @@ int32_t form_blocks(agca_hier* h) {
     } else {
         // levels L-2 .. lowest need the Galerkin matrices of every element of the level
         // below them while any coarser level is flagged; transient ping-pong buffers
-        std::vector<void*> tmp;
-        int32_t rc = AGCA_OK;
+        Transients tmp(h, true);
+        double* trans[2] = {nullptr, nullptr};
         for (int i = 0; i < 2; ++i) {
             const int l = L - 2 - i;
             if (l < lowest + 1) break;  // trans of level l is needed only if some level < l is flagged
-            void* p = nullptr;
-            hipError_t e = hipMalloc(&p, (size_t)h->lv[l].elems * M * M * sizeof(double));
-            if (e != hipSuccess) {
-                (void)hipGetLastError();
-                rc = fail(AGCA_E_OOM, "transient Galerkin buffer allocation failed");
-                break;
-            }
-            tmp.push_back(p);
-            h->trans[i] = static_cast<double*>(p);
+            TRY(tmp.take((void**)&trans[i], (size_t)h->lv[l].elems * M * M * sizeof(double)));
         }
-        if (rc == AGCA_OK) {
-            const int l2 = L - 2;
-            double* out2 = (l2 > lowest) ? h->trans[0] : nullptr;
-            hipError_t e = launch_gca_fused2(nc, h->lv[l2].n, h->lv[L].nu64, h_fine, h->lv[L - 1].blk,
-                                             h->lv[L - 1].blocks64, h->lv[l2].blk, h->lv[l2].blocks64,
-                                             out2, h->st);
-            int cur = 0;
-            for (int l = L - 3; l >= lowest && e == hipSuccess; --l) {
-                double* in = h->trans[cur];
-                // trans[1-cur] held level l+2 (no longer needed) and is large enough
-                double* out = (l > lowest) ? h->trans[1 - cur] : nullptr;
-                e = launch_gca_up(nc, h->lv[l].n, in, h->lv[l].blk, h->lv[l].blocks64, out, h->st);
-                cur = 1 - cur;
-            }
-            if (e == hipSuccess) e = hipStreamSynchronize(h->st);
-            if (e != hipSuccess) {
-                h->error = true;
-                rc = fail(AGCA_E_HIP, std::string("Galerkin kernels: ") + hipGetErrorString(e));
-            }
+        const int l2 = L - 2;
+        double* out2 = (l2 > lowest) ? trans[0] : nullptr;
+        hipError_t e = launch_gca_fused2(nc, h->lv[l2].n, h->lv[L].nu64, h_fine, h->lv[L - 1].blk,
+                                         h->lv[L - 1].blocks64, h->lv[l2].blk, h->lv[l2].blocks64,
+                                         out2, h->st);
+        int cur = 0;
+        for (int l = L - 3; l >= lowest && e == hipSuccess; --l) {
+            double* in = trans[cur];
+            // trans[1-cur] held level l+2 (no longer needed) and is large enough
+            double* out = (l > lowest) ? trans[1 - cur] : nullptr;
+            e = launch_gca_up(nc, h->lv[l].n, in, h->lv[l].blk, h->lv[l].blocks64, out, h->st);
+            cur = 1 - cur;
         }
-        for (void* p : tmp) (void)hipFree(p);
-        h->trans[0] = h->trans[1] = nullptr;
-        if (rc != AGCA_OK) return rc;
+        if (e == hipSuccess) e = hipStreamSynchronize(h->st);
+        if (e != hipSuccess) {
+            h->error = true;
+            return fail(AGCA_E_HIP, std::string("Galerkin kernels: ") + hipGetErrorString(e));
+        }
     }
     h->blocks_version = h->nu_version;
     return AGCA_OK;
@@ -894,7 +939,22 @@ int32_t form_blocks(agca_hier* h) {
 // log_fine: nu_fine holds log nu (exponentiated while it is copied)
 int32_t build_operators(agca_hier* h, const double* nu_fine, const double* const* nu_coarse,
                         bool log_fine = false) {
-    const int L = h->cfg.L, nc = h->cfg.ncomp, M = 4 * nc;
+    const int L = h->cfg.L, nc = h->cfg.ncomp;
+    // Buffers of the set-up, released at its end (hipMalloc, outside mem_limit_bytes): taken before
+    // anything is overwritten, so that a rebuild that finds no memory leaves the hierarchy as it was.
+    // Levels alternate between two sets, the larger one for level L-1.
+    double *mn[2] = {nullptr, nullptr}, *mx[2] = {nullptr, nullptr}, *mean[2] = {nullptr, nullptr};
+    void* scratch = nullptr;
+    size_t sbytes = 0;
+    int64_t* cnt_dev = nullptr;
+    HIPCHK(h, compact_scratch_bytes(h->lv[L - 1].elems, &sbytes));
+    Transients tmp(h);
+    for (int l = L - 1; l >= std::max(0, L - 2); --l) {
+        const size_t bytes = h->lv[l].elems * sizeof(double);
+        for (double** p : {&mn[l & 1], &mx[l & 1], &mean[l & 1]}) TRY(tmp.take((void**)p, bytes));
+    }
+    TRY(tmp.take(&scratch, sbytes));
+    TRY(tmp.take((void**)&cnt_dev, sizeof(int64_t) * 16));
     ++h->nu_version;
     // coefficients
     for (int l = 0; l <= L; ++l) {
@@ -915,43 +975,9 @@ int32_t build_operators(agca_hier* h, const double* nu_fine, const double* const
     // coarse operator (eq. (2.9)) is a coefficient per element: the mean where an element is
     // flagged, the caller's value elsewhere.
     {
-        double *mn[2] = {nullptr, nullptr}, *mx[2] = {nullptr, nullptr}, *mean[2] = {nullptr, nullptr};
-        const int64_t emax = h->lv[L - 1].elems;
-        void* scratch = nullptr;
-        size_t sbytes = 0;
-        HIPCHK(h, compact_scratch_bytes(emax, &sbytes));
-        // transient buffers: allocated with plain hipMalloc and released at the end of setup
-        std::vector<void*> tmp;
-        auto talloc = [&](void** p, size_t bytes) -> int32_t {
-            hipError_t e = hipMalloc(p, bytes);
-            if (e != hipSuccess) {
-                (void)hipGetLastError();
-                return fail(AGCA_E_OOM, "transient hipMalloc failed");
-            }
-            tmp.push_back(*p);
-            return AGCA_OK;
-        };
-        auto release = [&]() {
-            (void)hipStreamSynchronize(h->st);
-            for (void* p : tmp) (void)hipFree(p);
-            tmp.clear();
-        };
         uint64_t macro_bits = 0;
         for (int k = 0; k < 48; ++k)
             if (h->cfg.macro_flags[k]) macro_bits |= (uint64_t)1 << k;
-        int32_t rc = AGCA_OK;
-        for (int i = 0; i < 2 && rc == AGCA_OK; ++i) {
-            rc = talloc((void**)&mn[i], emax * sizeof(double));
-            if (rc == AGCA_OK) rc = talloc((void**)&mx[i], emax * sizeof(double));
-            if (rc == AGCA_OK) rc = talloc((void**)&mean[i], emax * sizeof(double));
-        }
-        if (rc == AGCA_OK) rc = talloc(&scratch, sbytes);
-        int64_t* cnt_dev = nullptr;
-        if (rc == AGCA_OK) rc = talloc((void**)&cnt_dev, sizeof(int64_t) * 16);
-        if (rc != AGCA_OK) {
-            release();
-            return rc;
-        }
         for (int l = L - 1; l >= 0; --l) {
             const int cur = l & 1, fin = (l + 1) & 1;
             const double* nuL = h->lv[L].nu64;
@@ -963,7 +989,6 @@ int32_t build_operators(agca_hier* h, const double* nu_fine, const double* const
                 e = launch_compact(h->lv[l].elems, h->lv[l].flag, h->lv[l].blk, h->lv[l].ids,
                                    cnt_dev + l, scratch, sbytes, h->st);
             if (e != hipSuccess) {
-                release();
                 h->error = true;
                 return fail(AGCA_E_HIP, std::string("flag kernels: ") + hipGetErrorString(e));
             }
@@ -972,22 +997,19 @@ int32_t build_operators(agca_hier* h, const double* nu_fine, const double* const
         hipError_t e = hipMemcpyAsync(counts.data(), cnt_dev, sizeof(int64_t) * L,
                                       hipMemcpyDeviceToHost, h->st);
         if (e == hipSuccess) e = hipStreamSynchronize(h->st);
-        release();
+        tmp.release();
         if (e != hipSuccess) {
             h->error = true;
             return fail(AGCA_E_HIP, std::string("flag count readback: ") + hipGetErrorString(e));
         }
+        free_blocks(h);
         for (int l = 0; l < L; ++l) {
             h->lv[l].nflag = counts[l];
             h->lv[l].nblk = (h->cfg.coarse_storage == AGCA_STORE_MEAN) ? 0 : counts[l];
         }
     }
     // block storage (filled by form_blocks)
-    for (int l = 0; l < L; ++l) {
-        Level& lv = h->lv[l];
-        lv.blocks64 = nullptr;
-        if (lv.nblk > 0) TRY(alloc_t(h, &lv.blocks64, (size_t)lv.nblk * M * M, &lv.bytes));
-    }
+    for (int l = 0; l < L; ++l) TRY(block_storage(h, h->lv[l]));
     // diagonals, FP32 copies
     for (int l = 0; l <= L; ++l) {
         Level& lv = h->lv[l];
@@ -1029,26 +1051,6 @@ void free_all(agca_hier* h) {
     h->red_host = nullptr;
     if (h->fetched) (void)hipEventDestroy(h->fetched);
     h->fetched = nullptr;
-}
-
-int32_t free_blocks(agca_hier* h) {
-    // blocks are re-sized on every rebuild: drop the old ones from the allocation list
-    for (auto& lv : h->lv) {
-        for (size_t i = 0; lv.blocks64 && i < h->allocs.size(); ++i)
-            if (h->allocs[i] == lv.blocks64) {
-                (void)hipFree(lv.blocks64);
-                h->allocs.erase(h->allocs.begin() + i);
-                break;
-            }
-        const int M = 4 * h->cfg.ncomp;
-        const int64_t freed = lv.blocks64 ? lv.nblk * M * M * (int64_t)sizeof(double) : 0;
-        h->bytes -= freed;
-        lv.bytes -= freed;
-        lv.blocks64 = nullptr;
-        lv.nflag = 0;
-        lv.nblk = 0;
-    }
-    return AGCA_OK;
 }
 
 }  // namespace
@@ -1259,7 +1261,6 @@ int32_t agca_set_nu(agca_hier* h, const double* nu_fine, const double* const* nu
     TRY(check_level(h, 0));
     if (!nu_fine || !nu_coarse) return fail(AGCA_E_INVALID, "null coefficient pointer");
     HIPCHK(h, hipStreamSynchronize(h->st));
-    free_blocks(h);
     return build_operators(h, nu_fine, nu_coarse);
 }
 
@@ -1267,7 +1268,6 @@ int32_t agca_set_log_nu(agca_hier* h, const double* log_nu_fine, const double* c
     TRY(check_level(h, 0));
     if (!log_nu_fine || !nu_coarse) return fail(AGCA_E_INVALID, "null coefficient pointer");
     HIPCHK(h, hipStreamSynchronize(h->st));
-    free_blocks(h);
     return build_operators(h, log_nu_fine, nu_coarse, true);
 }
 

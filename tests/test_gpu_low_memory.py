@@ -1,0 +1,123 @@
+"""Calls that find no device memory: what the hierarchy can do without is given up (the scalar
+levels' edge weights; in a rebuild the stored Galerkin blocks), and a rebuild that fails all the same
+leaves the hierarchy as it was.
+
+The test runs in a process of its own, in which hipMalloc is a function that refuses on demand (a shared
+library in the global scope, before the HIP runtime): refuse until something is freed, or always."""
+
+import os
+import shutil
+import subprocess
+import sys
+
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+SHIM = r"""
+#include <dlfcn.h>
+#include <stddef.h>
+static int mode, refused, pass;  // mode 1: refuse until a hipFree, 2: refuse, after `pass` more calls
+static void* real(const char* name) {
+    void* lib = dlopen("libamdhip64.so.7", RTLD_LAZY | RTLD_NOLOAD);
+    return lib ? dlsym(lib, name) : 0;
+}
+extern "C" void refuse(int m, int after) { mode = m; refused = 0; pass = after; }
+extern "C" int refusals() { return refused; }
+extern "C" int hipMalloc(void** p, size_t n) {
+    if (mode && pass-- <= 0) { ++refused; return 2; }  // hipErrorOutOfMemory
+    return ((int (*)(void**, size_t))real("hipMalloc"))(p, n);
+}
+extern "C" int hipFree(void* p) {
+    if (mode == 1) mode = 0;
+    return ((int (*)(void*))real("hipFree"))(p);
+}
+"""
+
+CHILD = r"""
+import ctypes, sys
+shim = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+ncomp, what = int(sys.argv[2]), sys.argv[3]
+import numpy as np, torch
+from paper_2511_13109_amd import AGCAError, Hierarchy, coefficients_from_field
+from workloads import Sinkers
+L = 4
+first, second = (coefficients_from_field(Sinkers(3, seed, radius=0.15, width=2.0 / 32, contrast=1e6), L) for seed in (2, 7))
+F, G = Hierarchy(L, ncomp, first[L], first[:L]), Hierarchy(L, ncomp, second[L], second[:L])
+H = Hierarchy(L, ncomp, first[L], first[:L])
+g = torch.Generator(device="cuda")
+g.manual_seed(5)
+n1 = H.n(L) + 1
+u = torch.zeros(ncomp, n1, n1, n1, dtype=torch.float64, device="cuda")
+u[:, 1:-1, 1:-1, 1:-1] = torch.randn(ncomp, n1 - 2, n1 - 2, n1 - 2, generator=g, dtype=torch.float64, device="cuda")
+u = u.reshape(-1)
+
+def same(A, B):
+    for op in (lambda X: X.apply(L, u), lambda X: X.vcycle(u)):
+        a, b = op(A), op(B)
+        err = float((a - b).abs().max() / b.abs().max())
+        assert err <= 1e-12, err
+    for l in range(L):
+        assert np.array_equal(A.flags(l), B.flags(l))
+        assert np.array_equal(A.blocks(l), B.blocks(l))
+
+def refused(call):
+    try:
+        call()
+    except AGCAError as e:
+        return "AGCA_E_OOM" in str(e)
+    return False
+
+full = H.device_bytes()
+if what == "rebuild":
+    # the weights or the blocks make room
+    shim.refuse(1, 0)
+    H.set_nu(second[L], second[:L])
+    assert shim.refusals() > 0
+    same(H, G)
+elif what == "blocks":
+    if ncomp == 1:
+        shim.refuse(1, 0)
+        got = H.blocks(1)
+        assert shim.refusals() > 0
+        assert H.device_bytes() < full
+        assert np.array_equal(got, F.blocks(1))
+    else:  # nothing to give up
+        shim.refuse(2, 0)
+        assert refused(lambda: H.blocks(1))
+        shim.refuse(0, 0)
+    same(H, F)
+else:
+    shim.refuse(2, 0)
+    assert refused(lambda: H.set_nu(second[L], second[:L]))
+    shim.refuse(0, 0)
+    same(H, F)
+    H.set_nu(second[L], second[:L])
+    same(H, G)
+for X in (F, G, H):
+    X.close()
+print("child ok")
+"""
+
+
+@pytest.fixture(scope="module")
+def shim(tmp_path_factory):
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("no host C++ compiler")
+    d = tmp_path_factory.mktemp("shim")
+    (d / "shim.cpp").write_text(SHIM)
+    subprocess.run([gxx, "-O1", "-shared", "-fPIC", str(d / "shim.cpp"), "-o", str(d / "shim.so"), "-ldl"], check=True)
+    return str(d / "shim.so")
+
+
+@pytest.mark.parametrize("ncomp", [1, 3])
+@pytest.mark.parametrize("what", ["rebuild", "blocks", "failed rebuild"])
+def test_no_memory(shim, what, ncomp):
+    print(f"\n[low memory {what} ncomp={ncomp}]", flush=True)
+    r = subprocess.run([sys.executable, "-c", CHILD, shim, str(ncomp), what], cwd=ROOT, capture_output=True, text=True,
+                       timeout=100)
+    print(r.stdout, flush=True)
+    assert r.returncode == 0 and "child ok" in r.stdout, r.stdout + r.stderr
