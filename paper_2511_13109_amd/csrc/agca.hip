@@ -892,6 +892,7 @@ private:
 int32_t form_blocks(agca_hier* h) {
     const int L = h->cfg.L, nc = h->cfg.ncomp, M = 4 * nc;
     if (h->blocks_version == h->nu_version || h->cfg.coarse_storage == AGCA_STORE_MEAN) return AGCA_OK;
+    for (int l = 0; l < L; ++l) TRY(block_storage(h, h->lv[l]));
     int lowest = -1;  // coarsest... any flagged level <= L-2 ?
     for (int l = 0; l <= L - 2; ++l)
         if (h->lv[l].nblk > 0) {
@@ -1008,8 +1009,6 @@ int32_t build_operators(agca_hier* h, const double* nu_fine, const double* const
             h->lv[l].nblk = (h->cfg.coarse_storage == AGCA_STORE_MEAN) ? 0 : counts[l];
         }
     }
-    // block storage (filled by form_blocks)
-    for (int l = 0; l < L; ++l) TRY(block_storage(h, h->lv[l]));
     // diagonals, FP32 copies
     for (int l = 0; l <= L; ++l) {
         Level& lv = h->lv[l];
@@ -1038,6 +1037,9 @@ int32_t build_operators(agca_hier* h, const double* nu_fine, const double* const
     TRY(build_coarsest(h));
     if (h->cfg.smoother == AGCA_SMOOTH_CHEBYSHEV) TRY(estimate_eigenvalues(h));
     HIPCHK(h, hipStreamSynchronize(h->st));
+    // block storage, filled by form_blocks; after the operators, which do not need it: a level that
+    // finds no memory for it leaves them whole
+    for (int l = 0; l < L; ++l) TRY(block_storage(h, h->lv[l]));
     return AGCA_OK;
 }
 

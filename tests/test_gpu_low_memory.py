@@ -90,12 +90,22 @@ elif what == "blocks":
         shim.refuse(0, 0)
     same(H, F)
 else:
-    shim.refuse(2, 0)
-    assert refused(lambda: H.set_nu(second[L], second[:L]))
-    shim.refuse(0, 0)
-    same(H, F)
-    H.set_nu(second[L], second[:L])
-    same(H, G)
+    # every allocation of a rebuild in turn is the first that is refused
+    for after in range(30):
+        shim.refuse(2, after)
+        failed = refused(lambda: H.set_nu(second[L], second[:L]))
+        assert failed == (shim.refusals() > 0)
+        shim.refuse(0, 0)
+        # the old operators or the new ones, with their flags and blocks
+        old = all(np.array_equal(H.flags(l), F.flags(l)) for l in range(L))
+        same(H, F if old else G)
+        print("refused after", after, "failed" if failed else "done", "old" if old else "new", flush=True)
+        if not failed:
+            assert not old and after > 0
+            break
+        H.close()
+        H = Hierarchy(L, ncomp, first[L], first[:L])
+    assert not failed
 for X in (F, G, H):
     X.close()
 print("child ok")
