@@ -131,7 +131,8 @@ void forget_alloc(agca_hier* h, void* p) {
 
 // The scalar levels' edge weights are a faster form of an operator that the element
 // coefficients give as well: they are taken while memory is left, and given up (all of them)
-// when an allocation that a call cannot do without fails beside them.  True if there were any.
+// when an allocation that a call cannot do without fails beside them.  The next rebuild takes
+// them again if there is room.  True if there were any.
 bool drop_weights(agca_hier* h) {
     bool any = false;
     for (Level& lv : h->lv) {
@@ -827,6 +828,29 @@ int32_t build_coarsest(agca_hier* h) {
     return AGCA_OK;
 }
 
+// The scalar levels' edge weights, if there is room for all of them
+bool take_weights(agca_hier* h) {
+    if (h->cfg.ncomp != 1) return false;
+    bool room = true;
+    for (Level& lv : h->lv) {
+        const size_t count = 3 * (size_t)lv.nodes;
+        auto take = [&](auto*& p) {
+            void* v = nullptr;
+            room = room && dev_alloc(h, &v, count * sizeof(*p), &lv.bytes, true) == AGCA_OK;
+            p = static_cast<std::remove_reference_t<decltype(p)>>(v);
+        };
+        take(lv.w64);
+        if (mg32(h)) take(lv.w32);
+    }
+    if (!room) drop_weights(h);
+    return room;
+}
+int32_t form_weights(agca_hier* h, const Level& lv) {
+    if (lv.w64) HIPCHK(h, launch_weights<double>(lv.n, lv.nu64, nullptr, lv.w64, h->st));
+    if (lv.w32) HIPCHK(h, launch_weights<float>(lv.n, lv.nu64, lv.nubf, lv.w32, h->st));
+    return AGCA_OK;
+}
+
 // Storage of a level's Galerkin blocks, and its release (the blocks are formed again when they are
 // read next).
 int32_t block_storage(agca_hier* h, Level& lv) {
@@ -1025,8 +1049,7 @@ int32_t build_operators(agca_hier* h, const double* nu_fine, const double* const
         } else {
             HIPCHK(h, launch_invert_diag<double>(cnt, lv.diag, lv.dinv64, h->st));
         }
-        if (lv.w64) HIPCHK(h, launch_weights<double>(lv.n, lv.nu64, nullptr, lv.w64, h->st));
-        if (lv.w32) HIPCHK(h, launch_weights<float>(lv.n, lv.nu64, lv.nubf, lv.w32, h->st));
+        TRY(form_weights(h, lv));
         if (lv.sten64) {
             HIPCHK(h, launch_stencil_assemble(lv.n, lv.nu64, scale, lv.sten64, h->st));
             if (lv.sten32)
@@ -1040,6 +1063,11 @@ int32_t build_operators(agca_hier* h, const double* nu_fine, const double* const
     // block storage, filled by form_blocks; after the operators, which do not need it: a level that
     // finds no memory for it leaves them whole
     for (int l = 0; l < L; ++l) TRY(block_storage(h, h->lv[l]));
+    // weights that an earlier call gave up, now that everything else has its memory
+    if (!h->lv[L].w64 && take_weights(h)) {
+        for (const Level& lv : h->lv) TRY(form_weights(h, lv));
+        HIPCHK(h, hipStreamSynchronize(h->st));
+    }
     return AGCA_OK;
 }
 
@@ -1225,20 +1253,7 @@ int32_t agca_create(const agca_config* cfg, const double* nu_fine, const double*
     }
     if (rc == AGCA_OK) rc = alloc_t(h, &h->red, AGCA_RED_SLOTS);
     if (rc == AGCA_OK) rc = alloc_t(h, &h->counter, 4);
-    if (rc == AGCA_OK && nc == 1) {
-        bool room = true;
-        for (Level& lv : h->lv) {
-            const size_t count = 3 * (size_t)lv.nodes;
-            auto take = [&](auto*& p) {
-                void* v = nullptr;
-                room = room && dev_alloc(h, &v, count * sizeof(*p), &lv.bytes, true) == AGCA_OK;
-                p = static_cast<std::remove_reference_t<decltype(p)>>(v);
-            };
-            take(lv.w64);
-            if (mg32(h)) take(lv.w32);
-        }
-        if (!room) drop_weights(h);
-    }
+    if (rc == AGCA_OK) (void)take_weights(h);
     if (rc == AGCA_OK) {
         hipError_t e = hipHostMalloc((void**)&h->red_host, AGCA_RED_SLOTS * sizeof(double));
         if (e == hipSuccess) e = hipHostGetDevicePointer((void**)&h->red_map, h->red_host, 0);

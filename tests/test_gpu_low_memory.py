@@ -1,5 +1,5 @@
 """Calls that find no device memory: what the hierarchy can do without is given up (the scalar
-levels' edge weights; in a rebuild the stored Galerkin blocks), and a rebuild that fails all the same
+levels' edge weights, until a rebuild finds room for them; in a rebuild the stored Galerkin blocks), and a rebuild that fails all the same
 leaves the hierarchy as it was.
 
 The test runs in a process of its own, in which hipMalloc is a function that refuses on demand (a shared
@@ -77,6 +77,9 @@ if what == "rebuild":
     H.set_nu(second[L], second[:L])
     assert shim.refusals() > 0
     same(H, G)
+    # and are there again
+    assert H.device_bytes() == G.device_bytes()
+    assert torch.equal(H.apply(L, u), G.apply(L, u))
 elif what == "blocks":
     if ncomp == 1:
         shim.refuse(1, 0)
@@ -84,6 +87,9 @@ elif what == "blocks":
         assert shim.refusals() > 0
         assert H.device_bytes() < full
         assert np.array_equal(got, F.blocks(1))
+        H.set_nu(first[L], first[:L])
+        assert H.device_bytes() == full
+        assert torch.equal(H.apply(L, u), F.apply(L, u))
     else:  # nothing to give up
         shim.refuse(2, 0)
         assert refused(lambda: H.blocks(1))
