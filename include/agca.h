@@ -104,7 +104,12 @@ typedef struct {
     int32_t smoother;        /* AGCA_SMOOTH_*                                               */
     double flag_ratio;       /* tau (10 in the paper's experiments)                         */
     double omega;            /* Jacobi damping (2/3)                                        */
-    uint64_t mem_limit_bytes;/* 0 = unlimited; larger totals fail with AGCA_E_OOM           */
+    uint64_t mem_limit_bytes;/* 0 = unlimited; larger totals fail with AGCA_E_OOM.  Scalar
+                                hierarchies also hold edge weights (24 bytes per node, 36
+                                with an FP32 cycle) while there is room: a call that needs
+                                their memory frees them, unless a stream capture of
+                                apply, residual, smooth or vcycle may read them, and the
+                                next rebuild takes them again                            */
     uint8_t macro_flags[48]; /* AGCA_FLAG_MACRO: nonzero = Galerkin-coarsen that macro element */
     int32_t coarse_storage;  /* AGCA_STORE_*                                                */
 } agca_config;

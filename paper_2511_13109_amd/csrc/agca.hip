@@ -82,6 +82,7 @@ struct agca_hier {
     float* s_z32 = nullptr;
     // Stokes (velocity: finest level, pressure: level L-1)
     std::vector<double> lam;     // Chebyshev: eigenvalue estimate of D^-1 A per level
+    bool weights_captured = false;  // scalar: a stream capture holds kernels that read the edge weights
     int64_t nu_version = 0;      // bumped by every coefficient rebuild
     int64_t blocks_version = -1; // nu_version the stored Galerkin blocks were formed for
     int64_t mass_version = -1;   // nu_version the pressure mass was formed for
@@ -133,7 +134,9 @@ void forget_alloc(agca_hier* h, void* p) {
 // coefficients give as well: they are taken while memory is left, and given up (all of them)
 // when an allocation that a call cannot do without fails beside them.  The next rebuild takes
 // them again if there is room.  True if there were any.
+// Weights that a captured graph may read stay: its replays would read freed memory.
 bool drop_weights(agca_hier* h) {
+    if (h->weights_captured) return false;
     bool any = false;
     for (Level& lv : h->lv) {
         const size_t count = 3 * (size_t)nodes_of(lv.n);
@@ -249,6 +252,16 @@ int32_t check_level(const agca_hier* h, int level) {
     if (h->error) return fail(AGCA_E_STATE, "hierarchy is in an error state");
     if (level < 0 || level > h->cfg.L) return fail(AGCA_E_INVALID, "level out of range");
     return AGCA_OK;
+}
+
+// called where kernels that read the edge weights may be captured
+void note_capture(agca_hier* h) {
+    if (h->weights_captured || !h->st || !h->lv[h->cfg.L].w64) return;
+    hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(h->st, &s) != hipSuccess)
+        (void)hipGetLastError();
+    else
+        h->weights_captured = s != hipStreamCaptureStatusNone;
 }
 
 int32_t check_dtype(const agca_hier* h, int dtype, bool need_mg) {
@@ -1351,6 +1364,7 @@ int32_t agca_apply(agca_hier* h, int32_t level, int32_t dtype, const void* u, vo
     TRY(check_level(h, level));
     TRY(check_dtype(h, dtype, false));
     if (!u || !v || u == v) return fail(AGCA_E_INVALID, "u and v must be distinct non-null vectors");
+    note_capture(h);
     if (dtype == AGCA_F64)
         return do_cube<double>(h, level, MODE_APPLY, (const double*)u, nullptr, (double*)v, 0.0);
     return do_cube<float>(h, level, MODE_APPLY, (const float*)u, nullptr, (float*)v, 0.0f);
@@ -1360,6 +1374,7 @@ int32_t agca_residual(agca_hier* h, int32_t level, int32_t dtype, const void* b,
     TRY(check_level(h, level));
     TRY(check_dtype(h, dtype, false));
     if (!b || !x || !r || r == x) return fail(AGCA_E_INVALID, "bad vector pointers");
+    note_capture(h);
     if (dtype == AGCA_F64)
         return do_cube<double>(h, level, MODE_RESIDUAL, (const double*)x, (const double*)b, (double*)r, 0.0);
     return do_cube<float>(h, level, MODE_RESIDUAL, (const float*)x, (const float*)b, (float*)r, 0.0f);
@@ -1372,6 +1387,7 @@ int32_t agca_smooth(agca_hier* h, int32_t level, int32_t dtype, int32_t sweeps, 
     if (level == 0) return fail(AGCA_E_INVALID, "level 0 is solved directly");
     if (!b || !x || b == x) return fail(AGCA_E_INVALID, "bad vector pointers");
     if (sweeps < 0) return fail(AGCA_E_INVALID, "sweeps must be >= 0");
+    note_capture(h);
     if (dtype == AGCA_F64) return do_smooth<double>(h, level, sweeps, omega, (const double*)b, (double*)x);
     return do_smooth<float>(h, level, sweeps, omega, (const float*)b, (float*)x);
 }
@@ -1405,6 +1421,7 @@ int32_t agca_vcycle(agca_hier* h, int32_t dtype, const void* b, void* x) {
     TRY(check_level(h, 0));
     TRY(check_dtype(h, dtype, true));
     if (!b || !x || b == x) return fail(AGCA_E_INVALID, "bad vector pointers");
+    note_capture(h);
     if (dtype == AGCA_F64) return do_vcycle<double>(h, (const double*)b, (double*)x);
     return do_vcycle<float>(h, (const float*)b, (float*)x);
 }

@@ -1,6 +1,6 @@
 """Calls that find no device memory: what the hierarchy can do without is given up (the scalar
 levels' edge weights, until a rebuild finds room for them; in a rebuild the stored Galerkin blocks), and a rebuild that fails all the same
-leaves the hierarchy as it was.
+leaves the hierarchy as it was.  Weights that a captured graph reads stay.
 
 The test runs in a process of its own, in which hipMalloc is a function that refuses on demand (a shared
 library in the global scope, before the HIP runtime): refuse until something is freed, or always."""
@@ -57,6 +57,7 @@ u = u.reshape(-1)
 def same(A, B):
     for op in (lambda X: X.apply(L, u), lambda X: X.vcycle(u)):
         a, b = op(A), op(B)
+        torch.cuda.synchronize()  # the two may have streams of their own
         err = float((a - b).abs().max() / b.abs().max())
         assert err <= 1e-12, err
     for l in range(L):
@@ -95,6 +96,31 @@ elif what == "blocks":
         assert refused(lambda: H.blocks(1))
         shim.refuse(0, 0)
     same(H, F)
+elif what == "captured":
+    # weights that a captured cycle reads are not given up; its replays follow a rebuild
+    st = torch.cuda.Stream()
+    with torch.cuda.stream(st):
+        C = Hierarchy(L, 1, first[L], first[:L], stream=st)
+        x = torch.empty_like(u)
+        C.vcycle(u, x)
+        graph = torch.cuda.CUDAGraph()
+        st.synchronize()
+        with torch.cuda.graph(graph, stream=st):
+            C.vcycle(u, x)
+        held = C.device_bytes()
+        shim.refuse(1, 0)
+        assert refused(lambda: C.blocks(1))
+        shim.refuse(0, 0)
+        assert C.device_bytes() == held
+        for X, nu in ((F, first), (G, second), (F, first)):
+            C.set_nu(nu[L], nu[:L])
+            for _ in range(2):
+                x.zero_()
+                graph.replay()
+                st.synchronize()
+                assert torch.equal(x, C.vcycle(u))
+            same(C, X)
+    C.close()
 else:
     # every allocation of a rebuild in turn is the first that is refused
     for after in range(30):
@@ -129,8 +155,8 @@ def shim(tmp_path_factory):
     return str(d / "shim.so")
 
 
-@pytest.mark.parametrize("ncomp", [1, 3])
-@pytest.mark.parametrize("what", ["rebuild", "blocks", "failed rebuild"])
+@pytest.mark.parametrize("what,ncomp", [("rebuild", 1), ("rebuild", 3), ("blocks", 1), ("blocks", 3), ("failed rebuild", 1),
+                                        ("failed rebuild", 3), ("captured", 1)])
 def test_no_memory(shim, what, ncomp):
     print(f"\n[low memory {what} ncomp={ncomp}]", flush=True)
     r = subprocess.run([sys.executable, "-c", CHILD, shim, str(ncomp), what], cwd=ROOT, capture_output=True, text=True,
