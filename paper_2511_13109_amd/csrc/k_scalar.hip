@@ -93,11 +93,12 @@ __device__ __forceinline__ void store_partial(double v, double* __restrict__ out
 }
 
 // One product on a small level, one thread per node: every load of a node in flight at once,
-// no march.  Bound by latency.
+// no march.  Bound by latency.  out may be b or xprev (a residual in place, a Chebyshev pass into
+// the previous iterate's buffer): a node's values are read before its result is written.
 template <typename T, int MODE>
 __global__ void __launch_bounds__(NT)
-k_node7(int n, const T* __restrict__ W, const T* __restrict__ u, const T* __restrict__ b,
-        const T* __restrict__ dinv, T* __restrict__ out, T omega, T alpha, T gamma, const T* __restrict__ xprev,
+k_node7(int n, const T* __restrict__ W, const T* __restrict__ u, const T* b,
+        const T* __restrict__ dinv, T* out, T omega, T alpha, T gamma, const T* xprev,
         double* __restrict__ partial) {
     const int n1 = n + 1;
     const uint32_t N = (uint32_t)n1 * n1 * n1, p = blockIdx.x * NT + threadIdx.x;
@@ -132,12 +133,13 @@ k_node7(int n, const T* __restrict__ W, const T* __restrict__ u, const T* __rest
 // chunk of z layers, no LDS and no barriers: x neighbours by DPP (the row's two outer ones by
 // a load that only the end lanes take part in), y neighbours from cache, the z flux carried in
 // a register, every load issued one step ahead.  Interior nodes number 2^k - 1 per row, so
-// 64-wide rows leave no lanes idle.  Bound by memory: 40 bytes per node (FP64 apply).
+// 64-wide rows leave no lanes idle.  Bound by memory: 40 bytes per node (FP64 apply).  out may be b
+// or xprev, as in k_node7.
 template <typename T, int MODE>
 __global__ void __launch_bounds__(NT)
 k_march7(const int n, const int zc, const int gx, const int gy, const int gz, const T* __restrict__ W,
-         const T* __restrict__ u, const T* __restrict__ b, const T* __restrict__ dinv, T* __restrict__ out,
-         const T omega, const T alpha, const T gamma, const T* __restrict__ xprev, double* __restrict__ partial) {
+         const T* __restrict__ u, const T* b, const T* __restrict__ dinv, T* out,
+         const T omega, const T alpha, const T gamma, const T* xprev, double* __restrict__ partial) {
     const int cols = gx * gy, lin = tile_lin(cols, gz), bz = lin / cols, bc = lin - bz * cols;
     const int lane = threadIdx.x & 63;
     const int x = 1 + 64 * (bc % gx) + lane;
