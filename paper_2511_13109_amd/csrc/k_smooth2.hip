@@ -58,7 +58,8 @@ struct Waves {
     static constexpr int value = NC == 3 && sizeof(T) == 8 ? 2 : 4;
 };
 
-// the six coefficients of a cell as loaded, decoded when used
+// the six coefficients of a cell as loaded, decoded when used; a cell's are consecutive
+static_assert(AGCA_ELEM_SOA == 0, "the two-product passes read a cell's six coefficients as one run");
 template <typename NT>
 struct CellNu;
 template <>
