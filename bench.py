@@ -50,7 +50,7 @@ MILESTONES = (1e-5, 1e-6, 1e-7)
 # sources whose text determines the fine-apply kernel; counter traffic is only
 # reported while their hash equals the one recorded next to the counters
 KERNEL_SOURCES = ["paper_2511_13109_amd/csrc/k_apply.hip", "paper_2511_13109_amd/csrc/kuhn.h",
-                  "paper_2511_13109_amd/csrc/cube_math.h"]
+                  "paper_2511_13109_amd/csrc/cube_math.h", "paper_2511_13109_amd/csrc/cube_tile.h"]
 FINE_APPLY_KERNEL = "k_cube<3, double, double, 0>"
 
 
