@@ -683,18 +683,14 @@ int32_t count_invalid(agca_hier* h, const double* v, int64_t n, int* out) {
     return AGCA_OK;
 }
 
-// level-0 operator on its single free node (1,1,1): ncomp x ncomp, inverted on the host
 int32_t ensure_solver_vectors(agca_hier* h) {
-    if (h->s_r) return AGCA_OK;
     const int64_t cnt = (int64_t)h->cfg.ncomp * h->lv[h->cfg.L].nodes;
-    TRY(alloc_t(h, &h->s_r, cnt));
-    TRY(alloc_t(h, &h->s_z, cnt));
-    TRY(alloc_t(h, &h->s_p, cnt));
-    TRY(alloc_t(h, &h->s_q, cnt));
-    if (mg32(h)) {
-        TRY(alloc_t(h, &h->s_r32, cnt));
-        TRY(alloc_t(h, &h->s_z32, cnt));
-    }
+    // each by itself: an earlier call may have found memory for some
+    for (double** p : {&h->s_r, &h->s_z, &h->s_p, &h->s_q})
+        if (!*p) TRY(alloc_t(h, p, cnt));
+    if (mg32(h))
+        for (float** p : {&h->s_r32, &h->s_z32})
+            if (!*p) TRY(alloc_t(h, p, cnt));
     return AGCA_OK;
 }
 
@@ -795,6 +791,7 @@ int32_t estimate_eigenvalues(agca_hier* h) {
     return AGCA_OK;
 }
 
+// level-0 operator on its single free node (1,1,1): ncomp x ncomp, inverted on the host
 int32_t build_coarsest(agca_hier* h) {
     const int nc = h->cfg.ncomp;
     Level& L0 = h->lv[0];
@@ -1759,10 +1756,8 @@ static int32_t stokes_ready(agca_hier* h) {
     if (h->cfg.ncomp != 3) return fail(AGCA_E_INVALID, "Stokes needs the vector hierarchy (ncomp = 3)");
     if (h->cfg.L < 2) return fail(AGCA_E_INVALID, "Stokes needs L >= 2");
     const StokesDims d = stokes_dims(h);
-    if (!h->st_mass) {
-        TRY(alloc_t(h, &h->st_mass, (size_t)d.np));
-        TRY(alloc_t(h, &h->st_qf, (size_t)h->lv[h->cfg.L].nodes));
-    }
+    if (!h->st_mass) TRY(alloc_t(h, &h->st_mass, (size_t)d.np));
+    if (!h->st_qf) TRY(alloc_t(h, &h->st_qf, (size_t)h->lv[h->cfg.L].nodes));
     if (h->mass_version != h->nu_version) {
         HIPCHK(h, launch_stokes_mass_fine(d.nf, h->lv[h->cfg.L].nu64, h->st_qf, h->st));
         HIPCHK(h, launch_restrict_all(d.nc, h->st_qf, h->st_mass, h->st));

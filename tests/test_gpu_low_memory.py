@@ -1,6 +1,6 @@
 """Calls that find no device memory: what the hierarchy can do without is given up (the scalar
 levels' edge weights, until a rebuild finds room for them; in a rebuild the stored Galerkin blocks), and a rebuild that fails all the same
-leaves the hierarchy as it was.  Weights that a captured graph reads stay.
+leaves the hierarchy as it was, a solve what a later one needs.  Weights that a captured graph reads stay.
 
 The test runs in a process of its own, in which hipMalloc is a function that refuses on demand (a shared
 library in the global scope, before the HIP runtime): refuse until something is freed, or always."""
@@ -41,7 +41,7 @@ import ctypes, sys
 shim = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
 ncomp, what = int(sys.argv[2]), sys.argv[3]
 import numpy as np, torch
-from paper_2511_13109_amd import AGCAError, Hierarchy, coefficients_from_field
+from paper_2511_13109_amd import AGCAError, Hierarchy, Stokes, coefficients_from_field
 from workloads import Sinkers
 L = 4
 first, second = (coefficients_from_field(Sinkers(3, seed, radius=0.15, width=2.0 / 32, contrast=1e6), L) for seed in (2, 7))
@@ -96,6 +96,37 @@ elif what == "blocks":
         assert refused(lambda: H.blocks(1))
         shim.refuse(0, 0)
     same(H, F)
+elif what == "solve":
+    # the first solve (and the first Stokes operation), refused at each of its allocations, then again
+    b = u
+    want = F.solve(b, tol=1e-8)[0]
+    M = Hierarchy(L, ncomp, first[L], first[:L], mg_dtype="f32")
+    mixed = M.solve(b, solver="fcg", tol=1e-8)[0]
+    M.close()
+    for kind in ("f64", "f32") + (("stokes",) if ncomp == 3 else ()):
+        for after in range(12):
+            X = Hierarchy(L, ncomp, first[L], first[:L], mg_dtype="f32" if kind == "f32" else "f64")
+            y = torch.empty_like(b)
+            if kind == "stokes":
+                S, q = Stokes(X), torch.empty((X.n(L - 1) + 1) ** 3, dtype=torch.float64, device="cuda")
+                call = lambda: S.div(b, q)
+            else:
+                call = lambda: X.solve(b, y, solver="pcg" if kind == "f64" else "fcg", tol=1e-8)
+            shim.refuse(2, after)
+            failed = refused(call)
+            assert failed == (shim.refusals() > 0)
+            shim.refuse(0, 0)
+            y.zero_()
+            call()
+            if kind == "stokes":
+                assert torch.equal(q, Stokes(F).div(b))
+            else:
+                ref = want if kind == "f64" else mixed
+                assert float((y - ref).abs().max()) <= 1e-6 * float(ref.abs().max())
+            X.close()
+            if not failed:
+                break
+        assert not failed and after > 0
 elif what == "captured":
     # weights that a captured cycle reads are not given up; its replays follow a rebuild
     st = torch.cuda.Stream()
@@ -156,7 +187,7 @@ def shim(tmp_path_factory):
 
 
 @pytest.mark.parametrize("what,ncomp", [("rebuild", 1), ("rebuild", 3), ("blocks", 1), ("blocks", 3), ("failed rebuild", 1),
-                                        ("failed rebuild", 3), ("captured", 1)])
+                                        ("failed rebuild", 3), ("solve", 1), ("solve", 3), ("captured", 1)])
 def test_no_memory(shim, what, ncomp):
     print(f"\n[low memory {what} ncomp={ncomp}]", flush=True)
     r = subprocess.run([sys.executable, "-c", CHILD, shim, str(ncomp), what], cwd=ROOT, capture_output=True, text=True,
