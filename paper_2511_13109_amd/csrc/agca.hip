@@ -856,8 +856,10 @@ bool take_weights(agca_hier* h) {
     return room;
 }
 int32_t form_weights(agca_hier* h, const Level& lv) {
-    if (lv.w64) HIPCHK(h, launch_weights<double>(lv.n, lv.nu64, nullptr, lv.w64, h->st));
-    if (lv.w32) HIPCHK(h, launch_weights<float>(lv.n, lv.nu64, lv.nubf, lv.w32, h->st));
+    // both in one launch where both come from the FP64 coefficient (a launch is most of it on small
+    // levels: rebuild of an FP32 5^3 hierarchy 162 us with two per level)
+    if (lv.w64) HIPCHK(h, launch_weights<double>(lv.n, lv.nu64, nullptr, lv.w64, lv.nubf ? nullptr : lv.w32, h->st));
+    if (lv.w32 && lv.nubf) HIPCHK(h, launch_weights<float>(lv.n, nullptr, lv.nubf, lv.w32, nullptr, h->st));
     return AGCA_OK;
 }
 

@@ -77,12 +77,12 @@ struct Smooth2 {
 template <typename T>
 hipError_t launch_smooth2(int ncomp, bool pre, const LevelOp<T>& op, const Smooth2<T>& a, hipStream_t st);
 
-// Seven-point form of a scalar level operator (k_scalar.hip): edge weights W (3 (n+1)^3) from
-// the FP64 coefficient or a BF16 one; one pass (MODE_APPLY, MODE_RESIDUAL, MODE_JACOBI,
+// Seven-point form of a scalar level operator (k_scalar.hip): edge weights W (3 (n+1)^3; W32 the same in
+// FP32 if not null) from the FP64 coefficient or a BF16 one (times nu_copy_factor); one pass (MODE_APPLY, MODE_RESIDUAL, MODE_JACOBI,
 // MODE_CHEB); v = A u with partial sums of u . v (product7_blocks(n) of them); two products
 // in one pass (launch_smooth2)
 template <typename T>
-hipError_t launch_weights(int n, const double* nu, const uint16_t* nu_bf16, T* W, hipStream_t st);  // nu_bf16: times nu_copy_factor
+hipError_t launch_weights(int n, const double* nu, const uint16_t* nu_bf16, T* W, float* W32, hipStream_t st);
 template <typename T>
 hipError_t launch_product7(int mode, int n, const T* W, const T* u, const T* b, const T* dinv, T* out,
                            const Sweep<T>& sw, hipStream_t st);

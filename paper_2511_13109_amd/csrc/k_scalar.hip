@@ -42,7 +42,7 @@ __device__ __forceinline__ double nu_value(uint16_t v) { return (double)bf16_to_
 
 template <typename NT_, typename T>
 __global__ void __launch_bounds__(NT)
-k_weights(int n, const NT_* __restrict__ nu, double scale, T* __restrict__ W) {
+k_weights(int n, const NT_* __restrict__ nu, double scale, T* __restrict__ W, float* __restrict__ W32) {
     const int64_t n1 = n + 1, N = n1 * n1 * n1, cells = (int64_t)n * n * n;
     const int64_t p = blockIdx.x * (int64_t)NT + threadIdx.x;
     if (p >= N) return;
@@ -66,6 +66,7 @@ k_weights(int n, const NT_* __restrict__ nu, double scale, T* __restrict__ W) {
             }
         }
         W[a * N + p] = T(w * scale);
+        if (W32) W32[a * N + p] = float(w * scale);
     }
 }
 
@@ -459,14 +460,14 @@ hipError_t launch_two(int n, const T* W, const T* dinv, const Smooth2<T>& a, hip
 }  // namespace
 
 template <typename T>
-hipError_t launch_weights(int n, const double* nu, const uint16_t* nu_bf16, T* W, hipStream_t st) {
+hipError_t launch_weights(int n, const double* nu, const uint16_t* nu_bf16, T* W, float* W32, hipStream_t st) {
     if ((!nu && !nu_bf16) || !W || n < 2) return hipErrorInvalidValue;
     const int64_t N = (int64_t)(n + 1) * (n + 1) * (n + 1);
     const dim3 g((unsigned)((N + NT - 1) / NT));
     if (nu_bf16)
-        hipLaunchKernelGGL((k_weights<uint16_t, T>), g, dim3(NT), 0, st, n, nu_bf16, nu_scale(n, true), W);
+        hipLaunchKernelGGL((k_weights<uint16_t, T>), g, dim3(NT), 0, st, n, nu_bf16, nu_scale(n, true), W, W32);
     else
-        hipLaunchKernelGGL((k_weights<double, T>), g, dim3(NT), 0, st, n, nu, nu_scale(n, false), W);
+        hipLaunchKernelGGL((k_weights<double, T>), g, dim3(NT), 0, st, n, nu, nu_scale(n, false), W, W32);
     return hipGetLastError();
 }
 
@@ -503,7 +504,7 @@ hipError_t launch_two7(bool pre, int n, const T* W, const T* dinv, const Smooth2
 }
 
 #define AGCA_INST(T)                                                                                       \
-    template hipError_t launch_weights<T>(int, const double*, const uint16_t*, T*, hipStream_t);            \
+    template hipError_t launch_weights<T>(int, const double*, const uint16_t*, T*, float*, hipStream_t);    \
     template hipError_t launch_product7<T>(int, int, const T*, const T*, const T*, const T*, T*,           \
                                            const Sweep<T>&, hipStream_t);                                  \
     template hipError_t launch_two7<T>(bool, int, const T*, const T*, const Smooth2<T>&, hipStream_t);
