@@ -186,7 +186,7 @@ def summarize_profile(d: str, command_prefix: str) -> str:
               "V-cycles of 3 steps, the FP64-MG PCG and FP32-MG FCG solves, the 129^3 extra keys).  "
               "k_cube template arguments: <components, vector type, coefficient type, mode (0 apply, "
               "1 residual, 2 Jacobi-type pass, 3 apply with dot, 4 first two passes from zero, "
-              "5 Chebyshev pass), stored blocks>.",
+              "5 Chebyshev pass)>.",
               "",
               "| kernel | calls | avg us | total ms | % |",
               "|---|---|---|---|---|"]
@@ -385,23 +385,26 @@ VCYCLE_COUNTERS = [
 
 
 def summarize_counters(d: str, L: int) -> str:
-    """Markdown table of the instruction counters of the finest-level element-loop passes
-    in the counter runs under <d> (one sub-directory per run, rocprofv3 csv output)."""
+    """Markdown table of the instruction counters of the finest-level element-loop and
+    two-product passes in the counter runs under <d> (one sub-directory per run, rocprofv3 csv output)."""
     import csv
     import collections
     import glob
+    kernels = ("k_cube<3", "k_smooth2<3")
     vals = collections.defaultdict(lambda: collections.defaultdict(list))
-    grids = collections.defaultdict(int)
     for path in glob.glob(os.path.join(d, "*", "*counter_collection.csv")):
-        rows = list(csv.DictReader(open(path)))
+        rows = [r for r in csv.DictReader(open(path)) if _short(r["Kernel_Name"]).startswith(kernels)]
+        # the finest level: the launch grid that takes longest (a coarser level may have more workgroups)
+        took = collections.defaultdict(list)
+        for r in rows:
+            took[_short(r["Kernel_Name"]), int(r["Grid_Size"])].append(int(r["End_Timestamp"]) - int(r["Start_Timestamp"]))
+        grids = {}
+        for (k, g), ds in took.items():
+            if k not in grids or np.mean(ds) > np.mean(took[k, grids[k]]):
+                grids[k] = g
         for r in rows:
             k = _short(r["Kernel_Name"])
-            if not k.startswith("k_cube<3"):
-                continue
-            grids[k] = max(grids[k], int(r["Grid_Size"]))
-        for r in rows:
-            k = _short(r["Kernel_Name"])
-            if k.startswith("k_cube<3") and int(r["Grid_Size"]) == grids[k]:
+            if int(r["Grid_Size"]) == grids[k]:
                 vals[k][r["Counter_Name"]].append(float(r["Counter_Value"]))
     lines = ["| kernel | waves | VALU / wave | FP FMA+ADD / wave | SALU / wave | VMEM / wave | "
              "LDS / wave | wait / wave cycles | VALUBusy % | LDS wait / wave cycles | "
@@ -914,7 +917,7 @@ def main():
     ap.add_argument("--profile-apply", action="store_true",
                     help="only run 5 FP64 fine applies and a 256 MiB copy (counter passes)")
     ap.add_argument("--profile-vcycle", action="store_true",
-                    help="only run 3 FP32/BF16 and 3 FP64 V-cycles of the 513^3 hierarchies (counter passes)")
+                    help="only run 3 FP32/BF16 and 3 FP64 V-cycles of the workload's hierarchies (counter passes)")
     ap.add_argument("--summarize-counters", metavar="DIR",
                     help="print the instruction-counter table of the V-cycle counter runs under DIR")
     ap.add_argument("--summarize-trace", metavar="CSV",
@@ -967,7 +970,7 @@ def main():
         profile_apply(args.workload, dev)
         return
     if args.profile_vcycle:
-        profile_vcycle("sinker513", args.smoother, dev)
+        profile_vcycle(args.workload, args.smoother, dev)
         return
     # the benchmark line: 513^3 (default) or the earlier 129^3 line; the other workloads
     # print a report line of their own

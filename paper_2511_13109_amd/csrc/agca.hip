@@ -582,7 +582,9 @@ int32_t reduce_to(agca_hier* h, const double* partial, int nb, int slot) {
     return AGCA_OK;
 }
 // the same as a scalar for the kernel that uses it: summed there (and kept in red[slot]) while
-// the partials are few enough for each of its workgroups to read
+// the partials are few enough for each of its workgroups to read.  The line decides little: with any
+// from 1 to 20000 the time of a PCG iteration moves by less than 1 % at 65^3 to 129^3 (scalar 65^3 118.6 us
+// with a kernel for every sum, 117 without) and by less than 0.2 % at 257^3 and 513^3.
 constexpr int kScalarPartials = 2048;
 int32_t scalar_of(agca_hier* h, const double* partial, int nb, int slot, DevScalar* s) {
     if (nb <= kScalarPartials) {

@@ -204,6 +204,11 @@ struct CoarseTile {
 // Chunks of z layers: the count that minimises rounds x steps x time of a step.  A chunk of
 // zc layers marches zc + 4 steps; a step with k workgroups on a compute unit takes about
 // (3 + 4 k) / 7 of one with a single workgroup (129^3 FP32: 2.15 us for k = 1, 3.4 us for 2).
+// Against sweeps of 1 to 43 chunks on the finest level (V-cycle, Chebyshev (2, 2)) the count
+// is the best one at 65^3 and 129^3 in every form and precision (129^3 vector FP64 5 chunks 357 us, 4 / 10: 392 / 382;
+// BF16/FP32 10 chunks 218, 9 / 5: 229 / 232; scalar FP64 10 chunks 118, 5: 120); at 257^3 7 chunks
+// are best throughout (vector FP64 1856, chosen; BF16 983 against 1020 with the 8 chosen, FP32 1060 / 1090,
+// scalar FP64 658 / 671 with 4, FP32 424 / 436 with 4).
 inline int pick_chunks(int n, int64_t cols, int per_cu, int64_t cus) {
     int best = 1;
     double cost = -1.0;

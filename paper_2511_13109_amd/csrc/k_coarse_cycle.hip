@@ -19,11 +19,14 @@
 // of coefficients of a 9^3 level: read as an assembled stencil they are 0.8 MB (FP64), after
 // fine levels that push them out of the caches more than one compute unit reads in the time
 // of the launches it saves (FP32 17^3 cycle from cold caches 67 us, 59 with launches for the 9^3
-// level, 52 this way; FP64 70, 73 and 62).
+// level, 52 this way; FP64 70, 73 and 62).  With caches flushed between cycles (1 GB written; us with K = 3 / 2 / 1 / one
+// launch per pass above 5^3 or 9^3): scalar 17^3 FP64 23.0 / 26.6 / 40.7 / 42.8, FP32 19.1 / 25.5 / 39.0 / 38.4; 33^3
+// FP64 41.0 / 44.8 / 59.1 / 63.2, FP32 35.8 / 42.9 / 56.4 / 55.9; vector from K = 2 on: 9^3 FP64 27.4 / 45.4 / 53.6,
+// 17^3 64.0 / 72.5 / 80.8, FP32 52.8 / 59.1 / 62.0.
 // A pass is bound by the LDS reads of the neighbours (9^3 vector FP64: 37 per row, about
 // 1 us) and the barrier.  Whole cycles, Chebyshev (2, 2), before (one launch per pass above
-// 5^3 / 9^3) and now: scalar 9^3 27 -> 6 us, 17^3 FP64 36 -> 17, FP32 32 -> 14; vector
-// 9^3 FP64 47 -> 21, FP32 36 -> 16, 17^3 72 -> 56 and 56 -> 46.
+// 5^3 / 9^3) and now: scalar 9^3 27 -> 5.4 us, 17^3 FP64 36 -> 16.7, FP32 32 -> 12.5; vector
+// 9^3 FP64 47 -> 21, FP32 36 -> 15.5, 17^3 72 -> 56 and 56 -> 45.
 #include <hip/hip_runtime.h>
 
 #include "internal.h"

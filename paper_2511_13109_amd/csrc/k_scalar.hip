@@ -11,9 +11,9 @@
 // order of the additions.  The weights are formed in FP64 once per coefficient, from the
 // coefficient the operator uses (rounded to BF16 where the V-cycle's finest one is).
 //
-// Measured against the element loop: product 257^3 FP64 249 -> 166 us (680 MB: 4.1 TB/s), 513^3
-// 1945 -> 1241 us; V-cycle (Chebyshev 2, 2; before with one element-loop product per pass) 129^3
-// FP64 222 -> 137 us, 257^3 1627 -> 784, 513^3 FP64 12137 -> 5943, FP32 6536 -> 3333.
+// Measured against the element loop: product 257^3 FP64 249 -> 159 us (680 MB: 4.3 TB/s), 513^3
+// 1945 -> 1203 us; V-cycle (Chebyshev 2, 2; before with one element-loop product per pass) 129^3
+// FP64 222 -> 118 us, 257^3 1627 -> 680, 513^3 FP64 12137 -> 5390, FP32 6536 -> 2750.
 //
 // Layout: W[a * N + p], a = 0, 1, 2 the edge from node p along axis a, N = (n+1)^3; 0 where
 // the edge leaves the lattice.
@@ -237,6 +237,10 @@ k_march7(const int n, const int zc, const int gx, const int gy, const int gz, co
 struct March7Grid {
     int gx, gy, gz, zc;
 };
+// the marching kernel from here on.  At 128 cells it is the faster form (FP64 product 17.0 us, one
+// thread per node 23.8); at 64 the slower one (5.1 and 3.9, smoothing pass 5.9 and 5.2), so the
+// line could be higher; V-cycles run two products per pass there and do not notice (57.5 us with
+// either).
 constexpr int kMarchMinN = 64;
 March7Grid march7_grid(int n) {
     March7Grid g;

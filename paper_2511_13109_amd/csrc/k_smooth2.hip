@@ -19,9 +19,10 @@
 //
 // Why this shape: 32-wide rows (a wavefront covers two) and 16 rows are the largest tile
 // whose vector FP64 state fits without spills: two products' carried sums, three coefficient
-// layers and the loads in flight take 231-248 of the 256 registers of 2 wavefronts per SIMD
-// (one workgroup per compute unit, 137-157 KB of LDS); FP32 runs two workgroups per unit
-// within 128 registers.  Node loads are issued one step ahead, in the order of their use (the
+// layers and the loads in flight take 248 (before the correction) and 238 (after it) of the 256
+// registers of 2 wavefronts per SIMD (one workgroup per compute unit, 137-157 KB of LDS); FP32 runs
+// two workgroups per unit within 128 registers, of which the form with FP32 coefficients before the
+// correction spills two (coarse levels; 21.3 us against 21.0 of the form after it at 65^3).  Node loads are issued one step ahead, in the order of their use (the
 // wait counter is in order), right-hand side and inverse diagonal at the start of the step that
 // ends with them: no register is copied from one that was just loaded, a copy would wait for
 // every load in flight at the end of each step (vector FP64 V-cycle at 129^3 383 us with such
@@ -34,7 +35,10 @@
 // scalar 257^3 FP64 1.61 -> 1.04 ms.  Adding the coarse correction here instead of in a pass of
 // its own (x read and written once more): vector 129^3 FP64 394 -> 384 us, FP32/BF16 237 -> 231,
 // 513^3 15.3 -> 14.7 and 7.93 -> 7.84 ms, scalar 257^3 (k_scalar.hip) 803 -> 736 us.  At 513^3 the two FP64 passes take 6.2 and 5.6 ms and
-// request 82 and 72 KB per workgroup and step, 5.0-5.2 TB/s: the streaming rate of a copy.
+// request 82 and 72 KB per workgroup and step, 5.0-5.2 TB/s: the streaming rate of a copy.  Counters
+// (share of the time the vector ALUs issue / of a wavefront's cycles that wait for LDS): 513^3 BF16/FP32 90-98 % /
+// 7.5 %, the issue limit; FP64 51-54 % / 5-9 %; 129^3 BF16/FP32 75-80 % / 7 %; FP64 44-46 % / 5-9 % at 2.9 TB/s, neither limit:
+// two wavefronts per SIMD in steps with two barriers leave the rest idle.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -110,8 +114,8 @@ k_smooth2(const int n, const int zc, const int gx, const int gy, const int gz, c
     __shared__ T ds[PRE ? 3 : 1][PRE ? NC : 1][PRE ? NTH : 1];
     using Coarse = CoarseTile<NC, T, TX, TY>;
     __shared__ typename Coarse::Tile es;  // POST: the coarse correction
-    // POST: constants of a thread that are read back when used (in registers they spill, and a
-    // reload from memory waits for every load in flight)
+    // POST: constants of a thread that are read back when used (in registers they spill, and the
+    // reload from memory in every step waited for the loads in flight)
     __shared__ u32x4 lc[PRE ? 1 : NTH];
     const int cols = gx * gy;
     const int lin = tile_lin(cols, gz);
