@@ -147,7 +147,10 @@ int32_t agca_create(const agca_config* cfg, const double* nu_fine,
 
 int32_t agca_destroy(agca_hier* h);
 
-/* Replace the coefficients and rebuild flags, blocks and diagonals. */
+/* Replace the coefficients and rebuild flags, coefficients of flagged elements and diagonals.
+ * After AGCA_E_OOM the hierarchy has its old operators or, where only the storage of Galerkin
+ * blocks did not fit, the new ones; after AGCA_E_INVALID (a coefficient that is not finite and
+ * positive) it has to be rebuilt. */
 int32_t agca_set_nu(agca_hier* h, const double* nu_fine, const double* const* nu_coarse);
 
 /* agca_set_nu with the finest coefficient given as log nu (device, 6 n_L^3 doubles in
