@@ -133,17 +133,17 @@ class Hierarchy:
     def set_nu(self, nu_fine: torch.Tensor, nu_coarse: Sequence[torch.Tensor]):
         self._check_nu(nu_fine, nu_coarse)
         arr = (C.c_void_p * max(1, self.L))(*[t.data_ptr() for t in nu_coarse])
+        self.version += 1  # a rebuild that fails may have replaced the operators as well
         check(self._lib.agca_set_nu(self._h, _ptr(nu_fine), arr), "agca_set_nu")
         self._keep = [nu_fine] + list(nu_coarse)
-        self.version += 1
 
     def set_log_nu(self, log_nu_fine: torch.Tensor, nu_coarse: Sequence[torch.Tensor]):
         """Rebuild from log nu on the finest level (exponentiated by the library)."""
         self._check_nu(log_nu_fine, nu_coarse)
         arr = (C.c_void_p * max(1, self.L))(*[t.data_ptr() for t in nu_coarse])
+        self.version += 1
         check(self._lib.agca_set_log_nu(self._h, _ptr(log_nu_fine), arr), "agca_set_log_nu")
         self._keep = [log_nu_fine] + list(nu_coarse)
-        self.version += 1
 
     # -- sizes ------------------------------------------------------------
     def n(self, level: int) -> int:

@@ -156,9 +156,11 @@ else:
     # every allocation of a rebuild in turn is the first that is refused
     for after in range(30):
         shim.refuse(2, after)
+        version = H.version
         failed = refused(lambda: H.set_nu(second[L], second[:L]))
         assert failed == (shim.refusals() > 0)
         shim.refuse(0, 0)
+        assert H.version != version  # what a backward pass goes by
         # the old operators or the new ones, with their flags and blocks
         old = all(np.array_equal(H.flags(l), F.flags(l)) for l in range(L))
         same(H, F if old else G)
